@@ -513,7 +513,7 @@ __global__ void k_adj_tbT(LevelDev lvs, LevelDev lvt, T* __restrict__ tbT) {
 // source copies (coefficient b at src_pos(b), zero padded).
 template <typename T, int P>
 __global__ void k_adj_lbarT(LevelDev lv, T* __restrict__ lT) {
-  constexpr int K = nmi(P), STP = src_stp(P, (int)sizeof(T)), ROW = 4 * STP;
+  constexpr int K = nmi(P), ROW = full_row(P, (int)sizeof(T));
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= lv.nref * ROW) return;
   const int r = i / ROW, b = i - r * ROW;   // b runs over coefficient indices 0 .. ROW-1
@@ -748,7 +748,7 @@ __global__ __launch_bounds__(64) void k_adj_m2l_mfma(const int32_t* __restrict__
   constexpr int K = nmi(P), KS = dstage_ks(P), SDP = dstage_len(P, (int)sizeof(T));
   constexpr AdjM2LPlan<P> PL = make_adj_m2l_plan<P>();
   constexpr int RT = AdjM2LPlan<P>::RT;
-  constexpr int VW = 16 / (int)sizeof(T), STP = src_stp(P, (int)sizeof(T)), ROW = 4 * STP;
+  constexpr int VW = 16 / (int)sizeof(T), ROW = full_row(P, (int)sizeof(T));
   constexpr int NVB = (PL.kbmax + VW - 1) / VW, ND = (SDP / VW + 63) / 64;
   using V = typename Vec16<T>::type;
   __shared__ __align__(16) T sD[2][SDP];
@@ -1015,7 +1015,7 @@ static hipError_t adj_m2l_t(int p, const int32_t* tiles, int ntiles, int nsplit,
                             const int16_t* aoff, const LevelDev& lvp, const LevelDev& lvs, const LevelDev& lvt,
                             const T* Dst, hipStream_t st) {
   T* lT = (T*)lvt.lbarT;
-  const int rows = lvt.nref * src_row(p, (int)sizeof(T));
+  const int rows = lvt.nref * full_row(p, (int)sizeof(T));
 #define X(PP) \
   case PP: hipLaunchKernelGGL((k_adj_lbarT<T, PP>), dim3((rows + 255) / 256), dim3(256), 0, st, lvt, lT); break;
   AFMM_P_SWITCH(p, X)

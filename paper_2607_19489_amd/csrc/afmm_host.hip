@@ -599,6 +599,9 @@ struct HostTables {
   std::vector<int32_t> l2lT_start, l2lT_list;
   std::vector<double> l2lT_w;
   std::vector<double> nearA;        // [2][near_ksteps][64] near-field operator (A lane order)
+  std::vector<int32_t> fold_start;  // [nh + 1]
+  std::vector<int16_t> fold_list;   // coefficients a that fold onto each h
+  std::vector<double> fold_w;       // their signed binomials
 };
 
 static long double ipow(long double x, int n) {
@@ -802,18 +805,34 @@ static void build_tables(int p, HostTables& H) {
         H.tapsT.push_back(e | (oF << 5) | (di << 8));
       }
   // MFMA A-operand offsets into the staged D~ rows (sD[o][g], row stride KS, zero slot 8 KS)
-  const int KP = (K + 3) & ~3, KS = dstage_ks(p), ZERO = 8 * KS, K1 = nmi(p - 1);
+  const int KS = dstage_ks(p), ZERO = 8 * KS, K1 = nmi(p - 1), KH = nh(p), KH1 = nh(p - 1);
   auto deg = [&](int idx) { return H.mi[4 * idx + 3]; };
+  // Folds of the source coefficients: z^(k+2m) stands for (-1)^m (x^2 + y^2)^m z^k in
+  // every sum with harmonic derivatives, so coefficient (i - 2r, j - 2(m - r), k + 2m)
+  // joins (i, j, k), k <= 1, with (-1)^m C(m, r)
+  H.fold_start.assign(1, 0);
+  H.fold_list.clear();
+  H.fold_w.clear();
+  for (int h = 0; h < KH; ++h) {
+    const int* a = &H.mi[4 * h_full(h)];
+    for (int m = 0; 2 * m <= a[0] + a[1]; ++m)
+      for (int r = 0; r <= m; ++r) {
+        if (2 * r > a[0] || 2 * (m - r) > a[1]) continue;
+        H.fold_list.push_back((int16_t)mi_index(a[0] - 2 * r, a[1] - 2 * (m - r), a[2] + 2 * m));
+        H.fold_w.push_back(((m & 1) ? -1.0 : 1.0) * (double)binom(m, r));
+      }
+    H.fold_start.push_back((int32_t)H.fold_list.size());
+  }
   H.m2p_off.clear();
   for (int rt = 0; rt < 2; ++rt) {
-    const int steps = rt == 0 ? KP / 4 : (K1 + 3) / 4;
+    const int steps = ((rt == 0 ? KH : KH1) + 3) / 4;
     for (int kb = 0; kb < steps; ++kb)
       for (int lane = 0; lane < 64; ++lane) {
         const int i = lane & 15, k = 4 * kb + (lane >> 4);
         const int c = 2 * rt + (i >> 3), o = i & 7;  // c: 0 phi, 1..3 a_x..a_z
         int v = ZERO;
-        if (c == 0 && k < K) v = o * KS + k;
-        if (c > 0 && k < K1) v = o * KS + H.up[3 * k + (c - 1)];
+        if (c == 0 && k < KH) v = o * KS + h_full(k);
+        if (c > 0 && k < KH1) v = o * KS + H.up[3 * h_full(k) + (c - 1)];
         H.m2p_off.push_back((int16_t)v);
       }
   }
@@ -866,12 +885,12 @@ static void build_tables(int p, HostTables& H) {
         }
     }
   }
-  const int NT = (8 * K + 15) / 16;
+  const int NT = (8 * KH + 15) / 16;
   H.m2l_tinfo.assign(2 * NT, 0);
   H.m2l_off.clear();
   int step = 0;
   for (int T = 0; T < NT; ++T) {
-    const int ks = (nmi(p - deg(2 * T)) + 3) / 4;
+    const int ks = (nh(p - h_deg(2 * T)) + 3) / 4;
     H.m2l_tinfo[2 * T] = ks;
     H.m2l_tinfo[2 * T + 1] = step;
     step += ks;
@@ -880,8 +899,10 @@ static void build_tables(int p, HostTables& H) {
         const int R = 16 * T + (lane & 15), k = 4 * kb + (lane >> 4);
         const int b = R >> 3, o = R & 7;
         int v = ZERO;
-        if (b < K && k < K && deg(k) + deg(b) <= p)
-          v = o * KS + mi_index(H.mi[4 * k] + H.mi[4 * b], H.mi[4 * k + 1] + H.mi[4 * b + 1], H.mi[4 * k + 2] + H.mi[4 * b + 2]);
+        if (b < KH && k < KH && h_deg(k) + h_deg(b) <= p) {
+          const int *kk = &H.mi[4 * h_full(k)], *bb = &H.mi[4 * h_full(b)];
+          v = o * KS + mi_index(kk[0] + bb[0], kk[1] + bb[1], kk[2] + bb[2]);
+        }
         H.m2l_off.push_back((int16_t)v);
       }
   }
@@ -1431,7 +1452,7 @@ static size_t split_buffer_bytes(const afmm_plan* P, const int* m2l_split, const
   for (int f = 3; f <= T.lmax - 1; ++f) {
     const int pm = P->m2l_range[f][0];
     if (m2l_split[pm] > 1 && P->m2l_range[f][2] > 0)
-      total += (size_t)m2l_split[pm] * T.lv[f].nref() * P->K * (pm ? sizeof(float) : sizeof(double));
+      total += (size_t)m2l_split[pm] * T.lv[f].nref() * nh(P->opt.p) * (pm ? sizeof(float) : sizeof(double));
   }
   return total;
 }
@@ -1452,7 +1473,6 @@ static void release_split_buffers(afmm_plan* P) {
 // on failure frees what it allocated and leaves every level without buffers.
 static afmm_status place_split_buffers(afmm_plan* P) {
   const Topology& T = P->topo;
-  const int K = P->K;
   afmm_status s = AFMM_OK;
   for (int l = 3; l <= T.lmax && !s; ++l) {
     if (T.leafgrp[l].empty()) continue;
@@ -1467,7 +1487,7 @@ static afmm_status place_split_buffers(afmm_plan* P) {
   for (int f = 3; f <= T.lmax - 1 && !s; ++f) {
     const int pm = P->m2l_range[f][0];
     if (P->m2l_split[pm] > 1 && P->m2l_range[f][2] > 0) {
-      const size_t b = (size_t)P->m2l_split[pm] * T.lv[f].nref() * K * (pm ? sizeof(float) : sizeof(double));
+      const size_t b = (size_t)P->m2l_split[pm] * T.lv[f].nref() * nh(P->opt.p) * (pm ? sizeof(float) : sizeof(double));
       void* q = nullptr;
       if ((s = dev_alloc(P, &q, b))) break;
       P->lv[f].Lpart = q;
@@ -1616,6 +1636,26 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     const double* d_c2 = nullptr;
     if ((s = upload_conv<double>(P, c2, &d_c2, st))) return s;
     P->cm.cfac2 = d_c2;
+    // the folds carry the same factors; for cells whose children are all leaves
+    // every coefficient is its k = 0 entry times a signed child sum that depends
+    // only on the parity of a, which a fold keeps
+    std::vector<double> fw(H.fold_w), fp(nh(P->opt.p), 0.0);
+    for (int h = 0; h < nh(P->opt.p); ++h)
+      for (int j = H.fold_start[h]; j < H.fold_start[h + 1]; ++j) {
+        const int a = H.fold_list[j];
+        fw[j] *= c2[a];
+        fp[h] += fw[j] * H.m2m_w[H.m2m_start[a]];
+      }
+    int32_t* d_fs;
+    int16_t* d_fl;
+    double *d_fw, *d_fp;
+    if ((s = upload(P, H.fold_start, &d_fs, st)) || (s = upload(P, H.fold_list, &d_fl, st)) ||
+        (s = upload(P, fw, &d_fw, st)) || (s = upload(P, fp, &d_fp, st)))
+      return s;
+    P->cm.fold_start = d_fs;
+    P->cm.fold_list = d_fl;
+    P->cm.fold_w = d_fw;
+    P->cm.fold_p2m = d_fp;
     int32_t *d_ms, *d_ml;
     double* d_mw;
     if ((s = upload(P, H.m2m_start, &d_ms, st)) || (s = upload(P, H.m2m_list, &d_ml, st)) ||
@@ -2099,12 +2139,13 @@ static afmm_status run_solve(afmm_plan* P, const double* msrc, int fmax, int lo,
       }
     prof_end(P, a, st, pr ? kM2L32 : kM2L64, -1);
   }
-  // completion of each FMM level: tap-range partials (if split) + ShiftLocal (L2L) of the father
+  // completion of each FMM level: tap-range partials (if split), the coefficients that follow from
+  // those M2L forms, ShiftLocal (L2L) of the father
   for (int f = 3; f <= fmax; ++f) {
     const int ng = chain ? chain->ngrp[f] : (int)T.m2lgrp[f].size();
     const int32_t* grp = chain ? chain->d_grp[f] : P->d_m2lgrp[f];
     const int ns = P->m2l_split[P->m2l_range[f][0]];
-    if (ng == 0 || (f - 1 < P->l_first && ns == 1)) continue;
+    if (ng == 0) continue;
     hipEvent_t a = prof_begin(P, st);
     if ((s = dev_check(P,
                        launch_l2l(p, mixed && f > f64, mixed && (f - 1) > f64, f - 1 >= P->l_first, ns, grp, ng,
@@ -2774,7 +2815,7 @@ static size_t adjoint_layout(const afmm_plan* P, char* base, LevelDev* lw, doubl
     if (P->n_adjl[f] > 0) {
       const bool f32 = mixed && f > f64;
       lw[f].lbarT = take((size_t)T.lv[f].nref() *
-                         (f32 ? src_row(P->opt.p, 4) * sizeof(float) : src_row(P->opt.p, 8) * sizeof(double)));
+                         (f32 ? full_row(P->opt.p, 4) * sizeof(float) : full_row(P->opt.p, 8) * sizeof(double)));
     }
   *part = P->adj_part_elems ? (double*)take(P->adj_part_elems * sizeof(double)) : nullptr;
   return off;
@@ -2987,7 +3028,7 @@ static bool adjoint_noalloc_may_fit(const afmm_plan* P) {
     add(nref * K * 8);
     add(nref * K * 8);
     add(nref * 32 * 8);
-    add(nref * (size_t)src_row(P->opt.p, 8) * 8);
+    add(nref * (size_t)full_row(P->opt.p, 8) * 8);
     const size_t nt = (size_t)(T.lv[l].n() + 15) / 16 + 8;
     const size_t sp = (size_t)std::max(1, std::min(16, (int)((12 * (size_t)ncu + nt - 1) / nt)));
     part = std::max(part, sp * nt * 16 * K);

@@ -60,19 +60,46 @@ __host__ __device__ constexpr int mi_index(int a, int b, int c) {
   return (a + b + c) * (a + b + c + 1) * (a + b + c + 2) / 6 + (b + c) * (b + c + 1) / 2 + c;
 }
 
-// Layout of the scaled source copies (S32 / Sc64).  The MFMA kernels read the
+// Harmonic form.  The derivatives of 1/r obey D_{g+2ez} = -D_{g+2ex} - D_{g+2ey},
+// so of the K = C(p+3, 3) Cartesian coefficients of an expansion only the
+// (p + 1)^2 with c <= 1 (multi-index (a, b, c)) are independent in a sum with
+// them: the coefficients with c >= 2 are folded onto those of the same order
+// before the sum (source copies), and the local expansions that M2L forms obey
+// the same relation, so M2L computes only those with c <= 1 and the others
+// follow (k_l2l).  Exact at every truncation: folding keeps the order, and the
+// products of M2L and M2P shrink from 924 to 532 and from 84 + 3 56 to 49 + 3 36
+// terms at p = 6.  Position of (a, b, c), c <= 1, in the degree-graded folded order:
+__host__ __device__ constexpr int nh(int p) { return (p + 1) * (p + 1); }
+__host__ __device__ constexpr int h_index(int a, int b, int c) { return (a + b + c) * (a + b + c) + c * (a + b + c + 1) + b; }
+__host__ __device__ constexpr int h_deg(int h) {
+  int n = 0;
+  while ((n + 1) * (n + 1) <= h) ++n;
+  return n;
+}
+// position in the full order of folded coefficient h
+__host__ __device__ constexpr int h_full(int h) {
+  const int n = h_deg(h), r = h - n * n, c = r > n ? 1 : 0, b = r - c * (n + 1);
+  return mi_index(n - b - c, b, c);
+}
+
+// Layout of the scaled source copies (S32 / Sc64), KH = nh(p) folded
+// coefficients a row.  The MFMA kernels read the
 // B operand straight into registers: lane group g (lane >> 4) of a 16x16x4
 // step kb holds coefficient k = 4 kb + g.  A lane group needs STP steps
-// (STP = ceil(K/4) rounded up to whole 16-byte vectors of VW = 16/bytes
+// (STP = ceil(KH/4) rounded up to whole 16-byte vectors of VW = 16/bytes
 // values); its vector j holds steps VW j .. VW j + VW - 1.  The row stores the
 // vectors j-major: vector j of lane group g at (4 j + g) VW, so one 16-byte
 // load per lane (vector j for all 4 lane groups of a source) reads 64
 // contiguous bytes of each source row.  Coefficient k therefore sits at
 // ((k >> 2) / VW) 4 VW + (k & 3) VW + (k >> 2) % VW; unused slots are 0.
-__host__ __device__ constexpr int src_stp(int p, int bytes) {
-  return (((nmi(p) + 3) / 4) + (16 / bytes) - 1) / (16 / bytes) * (16 / bytes);
+__host__ __device__ constexpr int row_stp(int k, int bytes) {
+  return (((k + 3) / 4) + (16 / bytes) - 1) / (16 / bytes) * (16 / bytes);
 }
+__host__ __device__ constexpr int src_stp(int p, int bytes) { return row_stp(nh(p), bytes); }
 __host__ __device__ constexpr int src_row(int p, int bytes) { return 4 * src_stp(p, bytes); }
+// rows of all K coefficients in the same layout (the adjoint's local-expansion bars)
+__host__ __device__ constexpr int full_stp(int p, int bytes) { return row_stp(nmi(p), bytes); }
+__host__ __device__ constexpr int full_row(int p, int bytes) { return 4 * full_stp(p, bytes); }
 __host__ __device__ constexpr int src_pos(int k, int bytes) {
   return ((k >> 2) / (16 / bytes)) * 4 * (16 / bytes) + (k & 3) * (16 / bytes) + (k >> 2) % (16 / bytes);
 }
@@ -139,7 +166,7 @@ struct LevelDev {
   const int32_t* nbr = nullptr;      // [nref][27] neighbour cell index at this level, -1 outside box
   double* mass = nullptr;            // [n] leaf masses of this solve (0 for refined cells)
   double* S64 = nullptr;             // [nref][K] multipoles (FP64), used by the upward pass
-  float* S32 = nullptr;              // [nref][src_row(p, 4)] source copy (-1)^|a|/a! 2^|a| S~_a, FP32
+  float* S32 = nullptr;              // [nref][src_row(p, 4)] source copy (-1)^|a|/a! 2^|a| S~_a, folded, FP32
                                      // (mixed form), in the lane-group layout above
   double* Sc64 = nullptr;            // [nref][src_row(p, 8)] same source copy in FP64
   double* L64 = nullptr;             // [nref][K] local expansions (FP64 levels)
@@ -148,14 +175,14 @@ struct LevelDev {
                                      // leaf level), one set per M2P tap range
   int32_t npart = 0;
   size_t part_bytes = 0, Lpart_bytes = 0;
-  void* Lpart = nullptr;             // [nsplit][nref][K] M2L tap-range partial sums (T of the level), if split
+  void* Lpart = nullptr;             // [nsplit][nref][nh(p)] M2L tap-range partial sums (T of the level), if split
   // adjoint pass (FP64, allocated by the first adjoint call)
   double* tbar = nullptr;            // [n][4] unit-form bars of the target leaves (phi, ax, ay, az)
   double* mbar = nullptr;            // [n] mass bars of the leaves
   double* sbar = nullptr;            // [nref][K] source-copy bar, then multipole bar
   double* lbar = nullptr;            // [nref][K] local-expansion bar
   void* tbT = nullptr;               // [nref][32] target bars of the leaf children, B of the transposed M2P (T)
-  void* lbarT = nullptr;             // [nref][src_row] local-expansion bar, B of the transposed M2L (T, lane-group layout)
+  void* lbarT = nullptr;             // [nref][full_row] local-expansion bar, B of the transposed M2L (T, lane-group layout)
 };
 
 template <typename T>
@@ -176,7 +203,11 @@ struct CommonDev {
   const int16_t* up = nullptr;      // [K][3] index of a + e_i (or -1 when |a| = p)
   const int8_t* mi = nullptr;       // [K][4] (a, b, c, |a|)
   const double* binom = nullptr;    // [(kPMax+1)^2] binomial coefficients C(n, k) at n*(kPMax+1)+k
-  const double* cfac2 = nullptr;    // [K] (-1)^|a|/a! 2^|a| (FP64), applied to the source copies
+  const double* cfac2 = nullptr;    // [K] (-1)^|a|/a! 2^|a| (FP64), the factors of the source copies
+  const int32_t* fold_start = nullptr;  // [nh + 1] entry range of each folded source coefficient
+  const int16_t* fold_list = nullptr;   // entries: coefficient a
+  const double* fold_w = nullptr;       // weights cfac2_a times the signed binomial of the fold
+  const double* fold_p2m = nullptr;     // [nh] the same applied to the k = 0 entry of each a's M2M list (leaf children)
   const int32_t* m2m_start = nullptr;  // [K+1] M2M entry range of each coefficient a
   const int32_t* m2m_list = nullptr;   // entries: k | parity(a-k) << 12
   const double* m2m_w = nullptr;       // entry weights C(a,k) 4^-|a-k| 2^-|k|

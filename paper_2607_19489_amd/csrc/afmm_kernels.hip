@@ -50,43 +50,45 @@ __device__ inline void p2p(T rx, T ry, T rz, T m, T* out) {
   out[3] -= w3 * rz;
 }
 
-// Compile-time multi-index tables of order P: degree |a| and the position of
-// a + e_i (or -1 when |a| = P) for every degree-ordered position a.
+// Compile-time tables of the folded coefficients of order P: degree, position
+// in the full order, and the full position of a + e_i (or -1 when |a| = P).
 template <int P>
-struct MiTab {
-  int deg[nmi(P)];
-  int up[nmi(P)][3];
-  constexpr MiTab() : deg(), up() {
+struct HTab {
+  int deg[nh(P)];
+  int full[nh(P)];
+  int up[nh(P)][3];
+  constexpr HTab() : deg(), full(), up() {
     for (int n = 0; n <= P; ++n)
-      for (int a = n; a >= 0; --a)
-        for (int b = n - a; b >= 0; --b) {
-          const int c = n - a - b, g = mi_index(a, b, c);
-          deg[g] = n;
+      for (int c = 0; c <= (n > 0 ? 1 : 0); ++c)
+        for (int b = 0; b <= n - c; ++b) {
+          const int a = n - b - c, h = h_index(a, b, c);
+          deg[h] = n;
+          full[h] = mi_index(a, b, c);
           for (int i = 0; i < 3; ++i)
-            up[g][i] = n < P ? mi_index(a + (i == 0), b + (i == 1), c + (i == 2)) : -1;
+            up[h][i] = n < P ? mi_index(a + (i == 0), b + (i == 1), c + (i == 2)) : -1;
         }
   }
 };
 
 // M2P of one multipole with a D~ row, for the near field (VALU): fully
-// unrolled over the coefficients, so every D~ and source index (and the
+// unrolled over the folded coefficients, so every D~ and source index (and the
 // weight 2^-|a| of the same-level source copy) is a compile-time constant.
 template <typename T, int P>
 __device__ inline void m2p_row(const T* __restrict__ D, const T* __restrict__ S, T* out) {
-  constexpr int K = nmi(P);
-  constexpr int K1 = nmi(P - 1);
-  constexpr MiTab<P> mt{};
+  constexpr int K = nh(P);
+  constexpr int K1 = nh(P - 1);
+  constexpr HTab<P> mt{};
   T phi = 0, ax = 0, ay = 0, az = 0;
 #pragma unroll
   for (int a = 0; a < K1; ++a) {
     const T w = (T)(1.0 / (double)(1 << mt.deg[a])) * S[src_pos(a, (int)sizeof(T))];
-    phi += w * D[a];
+    phi += w * D[mt.full[a]];
     ax += w * D[mt.up[a][0]];
     ay += w * D[mt.up[a][1]];
     az += w * D[mt.up[a][2]];
   }
 #pragma unroll
-  for (int a = K1; a < K; ++a) phi += (T)(1.0 / (double)(1 << mt.deg[a])) * S[src_pos(a, (int)sizeof(T))] * D[a];
+  for (int a = K1; a < K; ++a) phi += (T)(1.0 / (double)(1 << mt.deg[a])) * S[src_pos(a, (int)sizeof(T))] * D[mt.full[a]];
   out[0] += phi;
   out[1] -= ax;
   out[2] -= ay;
@@ -114,6 +116,32 @@ hipError_t launch_gather_mass(const LevelDev& lv, const double* m_src, double* s
   return hipGetLastError();
 }
 
+// Folded source copies of the nc cells of a block (256 threads): cell c's row
+// index by rank(c), its folded coefficient h by coef(c, h); written slot by slot
+// in row order, so consecutive threads store consecutive addresses (0 in the
+// padding slots).
+template <int P, typename Rank, typename Coef>
+__device__ inline void store_copies(int nc, const LevelDev& lv, Rank rank, Coef coef) {
+  constexpr int KH = nh(P), R32 = src_row(P, 4), R64 = src_row(P, 8);
+  // coefficient of slot s of a lane-group-layout row (inverse of src_pos), or
+  // KH for a padding slot
+  auto slot_coef = [](int s, int vw) {
+    const int j = s / (4 * vw), g = (s % (4 * vw)) / vw, e = s % vw;
+    const int k = 4 * (vw * j + e) + g;
+    return k < KH ? k : KH;
+  };
+  if (lv.S32)
+    for (int i = threadIdx.x; i < nc * R32; i += 256) {
+      const int c = i / R32, sl = i - c * R32, h = slot_coef(sl, 4);
+      lv.S32[(size_t)rank(c) * R32 + sl] = h < KH ? (float)coef(c, h) : 0.f;
+    }
+  if (lv.Sc64)
+    for (int i = threadIdx.x; i < nc * R64; i += 256) {
+      const int c = i / R64, sl = i - c * R64, h = slot_coef(sl, 2);
+      lv.Sc64[(size_t)rank(c) * R64 + sl] = h < KH ? coef(c, h) : 0.0;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Upward pass (Alg. 2 Upward + CenterShift), FP64.  With child offsets
 // d_o = (o - 1/2)/2 the M2M weight C(a,k) d_o^(a-k) 2^-|k| splits into
@@ -126,19 +154,21 @@ hipError_t launch_gather_mass(const LevelDev& lv, const double* m_src, double* s
 // it stages the entry tables in LDS once, then for each chunk loads the
 // children's ranks and masses, forms the 8 signed child sums Y of each cell in
 // LDS and sums the entries of each coefficient.
-// The source copies are written in the lane-group layout; thread a >= K of a
-// cell writes the zero of padding slot src_pos(a).  Runs over a list of the
-// level's refined ranks (those with a refined child; k_p2m_leaf takes the
-// others).
+// The coefficients then go to LDS, from where the folded source copies are
+// formed slot by slot of the lane-group layout (0 in the padding slots).  Runs
+// over a list of the level's refined ranks (those with a refined child;
+// k_p2m_leaf takes the others).
+// (at most 32, one child per thread in the loads).
+__host__ __device__ constexpr int upward_cells(int p) { return 256 / nmi(p) < 32 ? 256 / nmi(p) : 32; }
+
 template <int P>
 __global__ __launch_bounds__(256) void k_upward(const int32_t* __restrict__ list, int nlist, LevelDev lv,
                                                 LevelDev lvc, CommonDev cm) {
   constexpr int K = nmi(P);
   constexpr int NE = nmi_entries(P);
-  constexpr int STP32 = src_stp(P, 4), STP64 = src_stp(P, 8);
-  constexpr int KP = 4 * STP32;               // threads per cell (STP32 >= STP64)
-  constexpr int CB = 256 / KP;                // cells per chunk
+  constexpr int CB = upward_cells(P);         // cells per chunk
   __shared__ double sY[CB][8][K];
+  __shared__ double sV[CB][K];
   __shared__ double sW[NE];
   __shared__ int sE[NE];
   __shared__ int sB[K + 1];
@@ -150,7 +180,7 @@ __global__ __launch_bounds__(256) void k_upward(const int32_t* __restrict__ list
     sE[i] = cm.m2m_list[i];
   }
   for (int i = t; i <= K; i += 256) sB[i] = cm.m2m_start[i];
-  const int c = t / KP, a = t - c * KP;
+  const int c = t / K, a = t - c * K;
   // children of a chunk: refined rank and mass (the gathered mass of a refined
   // child is 0 and unused), two independent loads, prefetched one chunk ahead
   auto child = [&](int i0, int& rc, double& m) {
@@ -207,28 +237,27 @@ __global__ __launch_bounds__(256) void k_upward(const int32_t* __restrict__ list
       for (int q = 0; q < 8; ++q) sY[cc][q][k] = v[q];
     }
     __syncthreads();
-    const int r = i0 + c < nlist ? list[i0 + c] : -1;
-    if (c < CB && r >= 0) {
-      if (a >= K) {  // zero padding of the source copies
-        if (lv.S32) lv.S32[(size_t)r * 4 * STP32 + src_pos(a, 4)] = 0.f;
-        if (lv.Sc64 && a < 4 * STP64) lv.Sc64[(size_t)r * 4 * STP64 + src_pos(a, 8)] = 0.0;
+    const int nc = min(CB, nlist - i0);
+    if (c < nc) {
+      double acc = 0.0;
+      if (leaf_only(c)) {
+        acc = sW[sB[a]] * sY[c][sE[sB[a]] >> 12][0];
       } else {
-        double acc = 0.0;
-        if (leaf_only(c)) {
-          acc = sW[sB[a]] * sY[c][sE[sB[a]] >> 12][0];
-        } else {
-          for (int j = sB[a]; j < sB[a + 1]; ++j) {
-            const int e = sE[j];
-            acc += sW[j] * sY[c][e >> 12][e & 4095];
-          }
+        for (int j = sB[a]; j < sB[a + 1]; ++j) {
+          const int e = sE[j];
+          acc += sW[j] * sY[c][e >> 12][e & 4095];
         }
-        lv.S64[(size_t)r * K + a] = acc;
-        // source copies for the translation kernels carry the factor (-1)^|a|/a! 2^|a|
-        const double sc = acc * cm.cfac2[a];
-        if (lv.S32) lv.S32[(size_t)r * 4 * STP32 + src_pos(a, 4)] = (float)sc;
-        if (lv.Sc64) lv.Sc64[(size_t)r * 4 * STP64 + src_pos(a, 8)] = sc;
       }
+      lv.S64[(size_t)list[i0 + c] * K + a] = acc;
+      sV[c][a] = acc;
     }
+    __syncthreads();
+    // source copies for the translation kernels carry the factor (-1)^|a|/a! 2^|a|
+    store_copies<P>(nc, lv, [&](int cc) { return list[i0 + cc]; }, [&](int cc, int h) {
+      double v = 0.0;
+      for (int j = cm.fold_start[h]; j < cm.fold_start[h + 1]; ++j) v += cm.fold_w[j] * sV[cc][cm.fold_list[j]];
+      return v;
+    });
     __syncthreads();
   }
 }
@@ -236,36 +265,46 @@ __global__ __launch_bounds__(256) void k_upward(const int32_t* __restrict__ list
 // Upward pass for the refined cells whose 8 children are leaves (P2M, Eq.
 // eq:P2M): the signed child sums vanish for k > 0, so coefficient a is the
 // k = 0 entry of its M2M list times one signed sum of the 8 masses (signs by
-// the parity of a).  A block takes kP2mCells cells of the list: their masses
-// go to LDS, thread (cell, a) forms coefficient a once, and the three copies
+// the parity of a), and a folded source coefficient, whose terms all have one
+// parity, a fixed weight times one such sum.  A block takes kP2mCells cells of
+// the list: their masses and the 8 signed sums go to LDS, and the three copies
 // (S64 in coefficient order, the scaled FP32 and FP64 copies in their
-// lane-group layouts) are written slot by slot in row order, so consecutive
-// threads store consecutive addresses (padding slots get 0).
+// lane-group layouts) are written slot by slot in row order.
 constexpr int kP2mCells = 8;
 
 template <int P>
 __global__ __launch_bounds__(256) void k_p2m_leaf(const int32_t* __restrict__ list, int nlist, LevelDev lv,
                                                   LevelDev lvc, CommonDev cm) {
   constexpr int K = nmi(P);
-  constexpr int R32 = src_row(P, 4), R64 = src_row(P, 8);
+  constexpr int KH = nh(P);
   constexpr int NC = kP2mCells;
+  constexpr HTab<P> ht{};
   __shared__ int sR[NC];
   __shared__ double sM[NC][8];
-  __shared__ double sV[NC][K];
+  __shared__ double sY[NC][8];
+  __shared__ double sW[K], sWh[KH];
+  __shared__ int8_t sQ[K], sQh[KH];
   const int t = threadIdx.x;
   const int c0 = blockIdx.x * NC;
   const int nc = min(NC, nlist - c0);
   if (t < NC) sR[t] = t < nc ? list[c0 + t] : -1;
+  if (t < K) {
+    const int e0 = cm.m2m_start[t];
+    sW[t] = cm.m2m_w[e0];
+    sQ[t] = (int8_t)(cm.m2m_list[e0] >> 12);
+  }
   __syncthreads();
   if (t < 8 * nc) sM[t >> 3][t & 7] = as_global(lvc.mass)[8 * (size_t)sR[t >> 3] + (t & 7)];
+  if (t < KH) {
+    sWh[t] = cm.fold_p2m[t];
+    sQh[t] = sQ[ht.full[t]];
+  }
   __syncthreads();
-  for (int i = t; i < nc * K; i += 256) {
-    const int c = i / K, a = i - c * K;
+  if (t < 8 * nc) {
+    const int c = t >> 3, q = t & 7;
     double v[8];
 #pragma unroll
     for (int o = 0; o < 8; ++o) v[o] = sM[c][o];
-    const int e0 = cm.m2m_start[a];
-    const int q = cm.m2m_list[e0] >> 12;
     // signed sum over the octant bits of q (the butterfly of k_upward, one output)
 #pragma unroll
     for (int bit = 0; bit < 3; ++bit) {
@@ -278,30 +317,14 @@ __global__ __launch_bounds__(256) void k_p2m_leaf(const int32_t* __restrict__ li
 #pragma unroll
       for (int o = 0; o < 8; ++o) v[o] = u[o];
     }
-    sV[c][a] = cm.m2m_w[e0] * v[q];
+    sY[c][q] = v[0];
   }
   __syncthreads();
-  // coefficient of slot s of a lane-group-layout row (inverse of src_pos), or
-  // K for a padding slot
-  auto slot_coef = [](int s, int vw) {
-    const int j = s / (4 * vw), g = (s % (4 * vw)) / vw, e = s % vw;
-    const int k = 4 * (vw * j + e) + g;
-    return k < K ? k : K;
-  };
   for (int i = t; i < nc * K; i += 256) {
     const int c = i / K, a = i - c * K;
-    lv.S64[(size_t)sR[c] * K + a] = sV[c][a];
+    lv.S64[(size_t)sR[c] * K + a] = sW[a] * sY[c][sQ[a]];
   }
-  if (lv.S32)
-    for (int i = t; i < nc * R32; i += 256) {
-      const int c = i / R32, sl = i - c * R32, k = slot_coef(sl, 4);
-      lv.S32[(size_t)sR[c] * R32 + sl] = k < K ? (float)(sV[c][k] * cm.cfac2[k]) : 0.f;
-    }
-  if (lv.Sc64)
-    for (int i = t; i < nc * R64; i += 256) {
-      const int c = i / R64, sl = i - c * R64, k = slot_coef(sl, 2);
-      lv.Sc64[(size_t)sR[c] * R64 + sl] = k < K ? sV[c][k] * cm.cfac2[k] : 0.0;
-    }
+  store_copies<P>(nc, lv, [&](int c) { return sR[c]; }, [&](int c, int h) { return sWh[h] * sY[c][sQh[h]]; });
 }
 
 __global__ void k_batch_in(int64_t nleaf, const int32_t* __restrict__ leafslot, const int32_t* __restrict__ leafhier,
@@ -346,7 +369,7 @@ hipError_t launch_batch_out(int64_t nleaf, const int32_t* leafslot, const int32_
 
 hipError_t launch_upward(int p, const int32_t* leaf, int nleaf, const int32_t* mix, int nmix, const LevelDev& lv,
                          const LevelDev& lvc, const CommonDev& cm, hipStream_t st) {
-  const int KP = src_row(p, 4), CB = 256 / KP;
+  const int CB = upward_cells(p);
   if (nleaf > 0) {
     const dim3 grid((unsigned)((nleaf + kP2mCells - 1) / kP2mCells)), block(256);
     switch (p) {
@@ -375,24 +398,26 @@ hipError_t launch_upward(int p, const int32_t* leaf, int nleaf, const int32_t* m
 
 // ---------------------------------------------------------------------------
 // Completion of the local expansions of FMM level f (one block per M2L group
-// F): L~_b[y] = sum_c Lpart[c][y]_b (the M2L tap sums, split over `nsplit`
-// tap ranges, added in fixed order; or the single sum already in L) + the
-// ShiftLocal term sum_g w_o[|b|][g] L~_{b+g}[F] (Eq. eq:L2L) when F has one.
-// Three passes over the group's 8K coefficients through LDS: the tap sums
-// and the stores run coefficient-fastest (whole child rows per wave), the
-// shift sums child-fastest; the sums and their order are unchanged.  NS
-// bounds the split (1: the single sum in L): every partial of every
-// coefficient a thread owns is loaded at once, so a block waits for one
-// round of loads rather than one per four partials and coefficient.
+// F): the M2L sums of the KH coefficients with c <= 1 (split over `nsplit`
+// tap ranges, added in fixed order; or the single sum at the front of the row
+// of L), the coefficients with c >= 2 that follow from them (harmonic
+// relation), and the ShiftLocal term sum_g w_o[|b|][g] L~_{b+g}[F] (Eq. eq:L2L)
+// when F has one.  Three passes over the group's coefficients through LDS: the
+// tap sums and the stores run coefficient-fastest (whole child rows per wave),
+// the expansion and shift sums child-fastest.  NS bounds the split (1: the
+// single sum in L): every partial of every coefficient a thread owns is loaded
+// at once, so a block waits for one round of loads rather than one per four
+// partials and coefficient.
 template <typename T, typename TL, int P, int NS>
 __global__ __launch_bounds__(kBlock) void k_l2l(const int32_t* __restrict__ grp, const TL* __restrict__ Lpar,
                                                 const int32_t* __restrict__ rank0, T* __restrict__ Lout,
                                                 const T* __restrict__ Lpart, int nsplit, size_t split_stride,
                                                 const T* __restrict__ w, const int16_t* __restrict__ sumidx,
                                                 const int8_t* __restrict__ mi) {
-  constexpr int K = nmi(P);
-  constexpr int KV = K | 1;  // odd LDS row stride: the 8 rows of a wave's loads fall in different banks
+  constexpr int K = nmi(P), KH = nh(P);
+  constexpr int KV = K | 1, KHV = KH | 1;  // odd LDS row strides: the 8 rows of a wave's accesses fall in different banks
   __shared__ T sL[K];
+  __shared__ T sH[8 * KHV];
   __shared__ T sV[8 * KV];
   __shared__ int sRy[8];
   const int F = grp[blockIdx.x];
@@ -403,22 +428,22 @@ __global__ __launch_bounds__(kBlock) void k_l2l(const int32_t* __restrict__ grp,
   // tap sums, coefficient fastest (each child's row is read contiguously);
   // a thread owns coefficients t, t + 256, ... (NI of them); a missing child
   // row reads row 0 and is not stored
-  constexpr int NI = (8 * K + kBlock - 1) / kBlock;
+  constexpr int NI = (8 * KH + kBlock - 1) / kBlock;
   {
     T x[NI][NS];
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
-      const int i = min(t + kBlock * j, 8 * K - 1), o = i / K, b = i - o * K;
+      const int i = min(t + kBlock * j, 8 * KH - 1), o = i / KH, b = i - o * KH;
       const int ry = sRy[o];
-      const size_t at = (size_t)(ry >= 0 ? ry : 0) * K + b;
+      const size_t at = (size_t)(ry >= 0 ? ry : 0) * (NS == 1 ? K : KH) + b;
 #pragma unroll
       for (int c = 0; c < NS; ++c) x[j][c] = NS == 1 ? Lout[at] : Lpart[min(c, nsplit - 1) * split_stride + at];
     }
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
       const int i = t + kBlock * j;
-      if (i >= 8 * K) break;
-      const int o = i / K, b = i - o * K;
+      if (i >= 8 * KH) break;
+      const int o = i / KH, b = i - o * KH;
       if (sRy[o] < 0) continue;
       T v = 0;
       if constexpr (NS == 1) {
@@ -428,26 +453,35 @@ __global__ __launch_bounds__(kBlock) void k_l2l(const int32_t* __restrict__ grp,
         for (int c = 0; c < NS; ++c)
           if (c < nsplit) v += x[j][c];
       }
-      sV[o * KV + b] = v;
+      sH[o * KHV + b] = v;
     }
   }
   __syncthreads();
-  // ShiftLocal, child o fastest: the lanes of a wave share few coefficients
-  // b, all of nearly the same degree, so their shift sums have nearly equal
-  // lengths
-  if (Lpar) {
-    for (int i = t; i < 8 * K; i += kBlock) {
-      const int o = i & 7, b = i >> 3;
-      if (sRy[o] < 0) continue;
-      const int nb = mi[4 * b + 3];
+  // coefficient (i, j, k + 2m), k <= 1, is (-1)^m sum_r C(m, r) of (i + 2r, j +
+  // 2(m - r), k); then ShiftLocal.  Child o fastest: the lanes of a wave share few
+  // coefficients b, all of nearly the same degree, so their sums have nearly
+  // equal lengths
+  for (int i = t; i < 8 * K; i += kBlock) {
+    const int o = i & 7, b = i >> 3;
+    if (sRy[o] < 0) continue;
+    const int nb = mi[4 * b + 3], m = mi[4 * b + 2] >> 1;
+    const T* h = sH + o * KHV + nb * nb + (mi[4 * b + 2] & 1) * (nb + 1) + mi[4 * b + 1] + 2 * m;
+    T v = h[0];
+    for (int r = 1, c = m; r <= m; ++r) {
+      v += (T)c * h[-2 * r];
+      c = c * (m - r) / (r + 1);
+    }
+    if (m & 1) v = -v;
+    if (Lpar) {
       const T* wr = w + ((size_t)o * (P + 1) + nb) * K;
       const int16_t* si = sumidx + (size_t)b * K;
       T sh = 0;
       for (int g = 0; g < nmi(P - nb); ++g) sh += wr[g] * sL[si[g]];
-      sV[o * KV + b] += sh;
+      v += sh;
     }
-    __syncthreads();
+    sV[o * KV + b] = v;
   }
+  __syncthreads();
   for (int i = t; i < 8 * K; i += kBlock) {
     const int o = i / K, b = i - o * K;
     const int ry = sRy[o];
@@ -467,9 +501,20 @@ __global__ __launch_bounds__(kBlock) void k_l2l(const int32_t* __restrict__ grp,
 //             is staged in LDS while the MFMAs of the previous tap run.
 // A fragments are read from sD through per-lane offsets that do not depend on
 // the tap (kept in registers).
+// The first k-step (monopole and dipole terms, by far the largest) and the
+// others sum into separate accumulators in M2P and in the lowest rows of M2L:
+// folded, the terms of orders >= 2 no longer come as large values of opposite
+// sign, and many are below half a unit in the last place of the running sum; in
+// one FP32 accumulator they were rounded away on one side (the potential's mean
+// error rose from 0.4e-7 to 7e-7 at p = 6).  Apart, the FP32 form's rel. L2
+// error against the FP64 form is 2.6e-7 in phi and 4.3e-7 in acc (two-level
+// 64^3, p = 6), below the 5.3e-7 and 6.0e-7 of the unfolded sums.
+// Measured: the folded products take the 8.0M-leaf p = 6 FP32 solve from 16.31
+// to 12.33 ms and the two-level one (288k leaves) from 811 to 646 us, 1289 to
+// 934 us in FP64.
 template <typename T, int P>
 struct TapStage {
-  static constexpr int K = nmi(P);
+  static constexpr int K = nh(P);            // folded coefficients
   static constexpr int KP = (K + 3) & ~3;    // coefficients covered by the k-steps
   static constexpr int KS = dstage_ks(P);    // sD row stride
   static constexpr int VW = 16 / (int)sizeof(T);
@@ -679,7 +724,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XB && sizeof
                                             const LevelDev* __restrict__ lvs, const T* __restrict__ Dst) {
   using TS = TapStage<T, P>;
   using V = typename Vec16<T>::type;
-  constexpr int K1 = nmi(P - 1);
+  constexpr int K1 = nh(P - 1);
   constexpr int ST0 = TS::KP / 4, ST1 = ((K1 + 3) & ~3) / 4;
   constexpr int NV = (ST0 + TS::VW - 1) / TS::VW;
   constexpr int ND = (TS::NDV + 63) / 64;
@@ -737,7 +782,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XB && sizeof
   }
   const int zrow = lv1.nref;
   V vD[ND];
-  typename Acc4<T>::type acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};
+  typename Acc4<T>::type acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0}, hi0 = {0, 0, 0, 0}, hi1 = {0, 0, 0, 0};
   // Taps run in pairs; an odd range ends with one empty tap (no source, so B
   // is zero; the D~ stage repeats the last tap's finite rows), so that both
   // halves of a pair and every load run unconditionally.
@@ -803,8 +848,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XB && sizeof
       const T* D = sD[b];
 #pragma unroll
       for (int kb = 0; kb < ST0; ++kb) {
-        acc0 = mfma16(D[off0[kb]], frag[kb], acc0);
-        if (kb < ST1) acc1 = mfma16(D[off1[kb]], frag[kb], acc1);
+        auto& s0 = kb == 0 ? acc0 : hi0;
+        auto& s1 = kb == 0 ? acc1 : hi1;
+        s0 = mfma16(D[off0[kb]], frag[kb], s0);
+        if (kb < ST1) s1 = mfma16(D[off1[kb]], frag[kb], s1);
       }
       __builtin_amdgcn_sched_barrier(0);  // the next fragments after the MFMAs
       take(srn, vmn);
@@ -868,8 +915,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XB && sizeof
       const T* D = sD[b];
 #pragma unroll
       for (int kb = 0; kb < ST0; ++kb) {
-        acc0 = mfma16(D[off0[kb]], frag[kb], acc0);
-        if (kb < ST1) acc1 = mfma16(D[off1[kb]], frag[kb], acc1);
+        auto& s0 = kb == 0 ? acc0 : hi0;
+        auto& s1 = kb == 0 ? acc1 : hi1;
+        s0 = mfma16(D[off0[kb]], frag[kb], s0);
+        if (kb < ST1) s1 = mfma16(D[off1[kb]], frag[kb], s1);
       }
       __builtin_amdgcn_sched_barrier(0);  // the next fragments after the MFMAs
       take(b ^ 1);
@@ -900,8 +949,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XB && sizeof
 #pragma unroll
       for (int kb = 0; kb < ST0; ++kb) {
         const T bv = kb == 0 ? bfrag_m0<T>(src, vmc, bc[0][0]) : bc[kb / TS::VW][kb % TS::VW];
-        acc0 = mfma16(D[off0[kb]], bv, acc0);
-        if (kb < ST1) acc1 = mfma16(D[off1[kb]], bv, acc1);
+        auto& s0 = kb == 0 ? acc0 : hi0;
+        auto& s1 = kb == 0 ? acc1 : hi1;
+        s0 = mfma16(D[off0[kb]], bv, s0);
+        if (kb < ST1) s1 = mfma16(D[off1[kb]], bv, s1);
       }
       store_dstage<T, P, 64>(sD[b ^ 1], vD);
       __syncthreads();
@@ -911,6 +962,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XB && sizeof
       step(k + 1, 1, bB, srB, vmB, bA, srA, vmA);
     }
   }
+  acc0 += hi0;
+  acc1 += hi1;
   const int F = sF[n];
   if (F >= 0) {
     gmut<T> out = part + (size_t)F * 32;
@@ -948,7 +1001,7 @@ __global__ __launch_bounds__(64) void k_m2p_s(const int32_t* __restrict__ tiles,
                                               const LevelDev* __restrict__ lvs, const T* __restrict__ Dst) {
   using TS = TapStage<T, P>;
   using V = typename Vec16<T>::type;
-  constexpr int K1 = nmi(P - 1);
+  constexpr int K1 = nh(P - 1);
   constexpr int ST0 = TS::KP / 4, ST1 = ((K1 + 3) & ~3) / 4;
   constexpr int NV = (ST0 + TS::VW - 1) / TS::VW;  // B vectors per lane and tile (MFMA layout)
   constexpr int ND = (TS::NDV + 63) / 64;
@@ -1017,9 +1070,9 @@ __global__ __launch_bounds__(64) void k_m2p_s(const int32_t* __restrict__ tiles,
     prow[j] = v / NVR;
     pchk[j] = v - prow[j] * NVR;
   }
-  typename Acc4<T>::type acc0[NT], acc1[NT];
+  typename Acc4<T>::type acc0[NT], acc1[NT], hi0[NT], hi1[NT];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) acc0[t] = acc1[t] = {0, 0, 0, 0};
+  for (int t = 0; t < NT; ++t) acc0[t] = acc1[t] = hi0[t] = hi1[t] = {0, 0, 0, 0};
   // fragments (per tile) of the current and the next tap, row pieces of the
   // next two taps, and each tile's column source and mass for the monopole slot
   V bA[NT][NV], bB[NT][NV];
@@ -1112,8 +1165,10 @@ __global__ __launch_bounds__(64) void k_m2p_s(const int32_t* __restrict__ tiles,
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
           const T bv = kb == 0 ? bfrag_m0<T>(srcc[t], vmc[t], bc[t][0][0]) : bc[t][kb / TS::VW][kb % TS::VW];
-          acc0[t] = mfma16(a0, bv, acc0[t]);
-          if (kb < ST1) acc1[t] = mfma16(a1, bv, acc1[t]);
+          auto& s0 = kb == 0 ? acc0[t] : hi0[t];
+          auto& s1 = kb == 0 ? acc1[t] : hi1[t];
+          s0 = mfma16(a0, bv, s0);
+          if (kb < ST1) s1 = mfma16(a1, bv, s1);
         }
         if (kb == KMID) {
           store_rows(gc);
@@ -1134,6 +1189,8 @@ __global__ __launch_bounds__(64) void k_m2p_s(const int32_t* __restrict__ tiles,
   const int krow = lane >> 4;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
+    acc0[t] += hi0[t];
+    acc1[t] += hi1[t];
     const int F = sF[16 * t + n];
     if (F < 0) continue;
     gmut<T> out = part + (size_t)F * 32;
@@ -1154,16 +1211,11 @@ __global__ __launch_bounds__(64) void k_m2p_s(const int32_t* __restrict__ tiles,
 // |a|+|b| <= p), columns = 16 groups.  The row tiles are split over the 4
 // waves by a compile-time greedy balance of their k-steps; each wave runs a
 // fully unrolled MFMA sequence with its A offsets in registers.
-constexpr int deg_of(int idx) {
-  int n = 0;
-  while (nmi(n) <= idx) ++n;
-  return n;
-}
-constexpr int m2l_ksteps(int P, int T) { return (nmi(P - deg_of(2 * T)) + 3) / 4; }
+constexpr int m2l_ksteps(int P, int T) { return (nh(P - h_deg(2 * T)) + 3) / 4; }
 
 template <int P>
 struct M2LPlan {
-  static constexpr int NT = (8 * nmi(P) + 15) / 16;
+  static constexpr int NT = (8 * nh(P) + 15) / 16;
   int n[4] = {0, 0, 0, 0};
   int tile[4][NT] = {};
   int steps[4] = {0, 0, 0, 0};
@@ -1259,7 +1311,7 @@ template <typename T, int P, int H>
 __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const int16_t* __restrict__ aoff,
                                 const int* sF, const int* sSrcT, T (*sB)[TapStage<T, P>::STP * 64],
                                 T (*sD)[TapStage<T, P>::SDP], int zrow, gptr<double> mass1,
-                                const T* __restrict__ Dst, gptr<T> S1, gptr<int32_t> rank0, gmut<T> Lout) {
+                                const T* __restrict__ Dst, gptr<T> S1, gptr<int32_t> rank0, gmut<T> Lout, int ldl) {
   using TS = TapStage<T, P>;
   using MS = M2LStage<T, P>;
   using V = typename Vec16<T>::type;
@@ -1278,7 +1330,7 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
 #pragma unroll
       for (int kb = 0; kb < m2l_ksteps(P, PL.tile[H][i]); ++kb) off[s++] = aoff[(PL.base[PL.tile[H][i]] + kb) * 64 + lane];
   }
-  typename Acc4<T>::type acc[NTH > 0 ? NTH : 1];
+  typename Acc4<T>::type acc[NTH > 0 ? NTH : 1], hi = {0, 0, 0, 0};
 #pragma unroll
   for (int i = 0; i < NTH; ++i) acc[i] = {0, 0, 0, 0};
   // register sets X (odd taps ahead) and Y; tap 1 goes to X first
@@ -1313,7 +1365,8 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
     for (int i = 0; i < NTH; ++i)
 #pragma unroll
       for (int kb = 0; kb < m2l_ksteps(P, PL.tile[H][i]); ++kb) {
-        acc[i] = mfma16(D[off[s]], bv[kb], acc[i]);
+        auto& sum = PL.tile[H][i] == 0 && kb > 0 ? hi : acc[i];
+        sum = mfma16(D[off[s]], bv[kb], sum);
         ++s;
       }
     if (k + 1 < nt2) {
@@ -1326,6 +1379,7 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
     step(k, 0, vDX, vBX, vmX, srX, vDY, vBY, vmY, srY);
     step(k + 1, 1, vDY, vBY, vmY, srY, vDX, vBX, vmX, srX);
   }
+  if (NTH > 0 && PL.tile[H][0] == 0) acc[0] += hi;
   const int F = sF[lane & 15];
   if (F < 0) return;
 #pragma unroll
@@ -1335,7 +1389,7 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
       const int R = 16 * PL.tile[H][i] + acc_row<T>(krow, r);
       if ((R >> 3) >= K) continue;
       const int ry = rank0[8 * F + (R & 7)];
-      if (ry >= 0) Lout[(size_t)ry * K + (R >> 3)] = acc[i][r];
+      if (ry >= 0) Lout[(size_t)ry * ldl + (R >> 3)] = acc[i][r];
     }
   }
 }
@@ -1352,8 +1406,9 @@ template <typename T, int P>
 constexpr int m2l_min_waves() { return sizeof(T) != 4 ? 1 : P <= 6 ? 4 : P == 8 ? 2 : 1; }
 
 // One block = one tile (16 groups) and one of `nsplit` contiguous tap ranges.
-// With nsplit == 1 the sums go straight to L; otherwise to the level's
-// partial buffer [nsplit][nref][K], reduced in fixed order by k_l2l.
+// With nsplit == 1 the sums go to the front of the rows of L; otherwise to the
+// level's partial buffer [nsplit][nref][KH], reduced in fixed order by k_l2l,
+// which also forms the coefficients that follow from these.
 template <typename T, int P>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(m2l_min_waves<T, P>())))
 void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
@@ -1414,13 +1469,14 @@ void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
   }
   __syncthreads();
   gmut<T> Lout = as_global_mut(nsplit > 1 ? (T*)lv0.Lpart + (size_t)chunk * lv0.nref * TS::K : level_L<T>(lv0));
+  const int ldl = nsplit > 1 ? TS::K : nmi(P);
   gptr<int32_t> rank0 = as_global(lv0.rank);
   // every wave runs the same number of barriers (one per tap)
   switch (w) {
-    case 0: m2l_part<T, P, 0>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout); break;
-    case 1: m2l_part<T, P, 1>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout); break;
-    case 2: m2l_part<T, P, 2>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout); break;
-    default: m2l_part<T, P, 3>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout); break;
+    case 0: m2l_part<T, P, 0>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout, ldl); break;
+    case 1: m2l_part<T, P, 1>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout, ldl); break;
+    case 2: m2l_part<T, P, 2>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout, ldl); break;
+    default: m2l_part<T, P, 3>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout, ldl); break;
   }
 }
 
@@ -1820,7 +1876,7 @@ hipError_t launch_l2l(int p, bool fp32, bool parent_fp32, bool has_parent, int n
                       const LevelDev& lv1, const LevelDev& lv0, const TablesDev<float>& t32,
                       const TablesDev<double>& t64, const CommonDev& cm, hipStream_t st) {
   if (ngrp == 0) return hipSuccess;
-  const size_t stride = (size_t)lv0.nref * nmi(p);
+  const size_t stride = (size_t)lv0.nref * nh(p);
   if (fp32) {
     if (parent_fp32)
       return l2l_dispatch<float, float>(p, grp, ngrp, has_parent ? lv1.L32 : nullptr, lv0.rank, lv0.L32,
