@@ -33,7 +33,7 @@ METRIC = "cells/sec full FMM solve (φ+accel) at rel. force err ≤1e-4, FP32 vs
 PEAK = {"fp32_mfma": 157.3, "fp64_mfma": 78.6, "fp32_vector": 157.3, "fp64_vector": 78.6, "hbm": 8000.0}
 KERNEL_NAMES = {"near_f32": "k_near<float, P>", "near_f64": "k_near<double, P>",
                 "m2l_f32": "k_m2l_mfma<float, P>", "m2l_f64": "k_m2l_mfma<double, P>",
-                "m2p_f32": "k_m2p<float, P, XB>", "m2p_f64": "k_m2p<double, P, XB>",
+                "m2p_f32": "k_m2p<float, P>", "m2p_f64": "k_m2p<double, P>",
                 "l2l": "k_l2l<T, TL, P>", "upward": "k_upward<P>", "gather": "k_gather_mass",
                 "adj_near": "k_adj_near_leaf + k_adj_near_m2p<P>", "adj_m2p": "k_adj_m2p<P>",
                 "adj_m2l": "k_adj_m2l<P>", "adj_tree": "k_adj_l2l/k_adj_down/k_adj_out"}
@@ -247,20 +247,14 @@ def run_batch(args):
         "config": {"workload": (f"cfg4: batch of {len(ws)} independent hierarchies (base level 4-6, 0-3 mass-refined "
                                 f"levels, Plummer or clumps), {nleaf} leaves, one hipGraph launch per solve"),
                    "p": args.p, "precision": "FP32 mixed", "leaves": nleaf, "hierarchies": len(ws)},
-        "roofline": roofline(res, "fp32"), "cpu_baseline": base, "autotune": tune,
+        "roofline": roofline(res, "fp32", args.p), "cpu_baseline": base, "autotune": tune,
         "algorithmic_flops_per_step": info["flops_m2l"] + info["flops_m2p"] + info["flops_p2p"] + info["flops_updown"],
         "kernels_fp32": kernel_table(res),
     }
     print(json.dumps(line), flush=True)
 
 
-def m2p_shape_ok(p, fp32, shape):
-    """Tile shapes the library runs for this order and precision (afmm_options.m2p_shape)."""
-    return shape == 0 or (shape == 3 and (fp32 or p <= 7)) or (fp32 and (shape == 1 or (shape == 2 and p <= 5)))
-
-
-def time_form(h, mass_t, p, precision, steps, warmup, overlap=False, autotune=True, graph=False, periodic=False,
-              m2p_shape=0):
+def time_form(h, mass_t, p, precision, steps, warmup, overlap=False, autotune=True, graph=False, periodic=False):
     """Autotuned plan (tap splits), timed solves (no instrumentation), then the same
     number of profiled solves: the profiled pass runs serially with hipEvents
     around every launch."""
@@ -268,7 +262,7 @@ def time_form(h, mass_t, p, precision, steps, warmup, overlap=False, autotune=Tr
     import paper_2607_19489_amd as A
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    plan = A.Plan(h, p=p, precision=precision, overlap=overlap, graph=graph, periodic=periodic, m2p_shape=m2p_shape)
+    plan = A.Plan(h, p=p, precision=precision, overlap=overlap, graph=graph, periodic=periodic)
     torch.cuda.synchronize()
     plan_ms = 1e3 * (time.perf_counter() - t0)
     info = plan.info()
@@ -290,38 +284,44 @@ def time_form(h, mass_t, p, precision, steps, warmup, overlap=False, autotune=Tr
     torch.cuda.synchronize()
     prof = plan.get_profile()
     plan.set_profiling(False)
-    # M2P tile shape that ran, [FP64 kernels, FP32 kernels]: the tuner's, or the
-    # option where the order and precision support it (else the plan used 0)
-    fixed = [m2p_shape if m2p_shape_ok(p, fp32, m2p_shape) else 0 for fp32 in (False, True)]
     out = {"ms_per_step": 1e3 * dt / steps, "value": info["nleaves"] * steps / dt, "info": info,
-           "kernels": prof, "steps": steps, "autotune": tune, "plan_create_ms": plan_ms,
-           "m2p_shape": tune["m2p_shape"] if tune else fixed}
+           "kernels": prof, "steps": steps, "autotune": tune, "plan_create_ms": plan_ms}
     phi_np, acc_np = phi.cpu().numpy(), acc.cpu().numpy()
     plan.close()
     return out, phi_np, acc_np
 
 
-SYMBOLS = {"m2p_f32": "k_m2p<float, {p}, {xb}>", "m2p_f64": "k_m2p<double, {p}, {xb}>",
+SYMBOLS = {"m2p_f32": "k_m2p<float, {p}>", "m2p_f64": "k_m2p<double, {p}>",
            "m2l_f32": "k_m2l_mfma<float, {p}>", "m2l_f64": "k_m2l_mfma<double, {p}>",
            "near_f32": "k_near<float, {p}>", "near_f64": "k_near<double, {p}>", "upward": "k_upward<{p}>"}
 
 
-def m2p_kernel_symbol(family, p, shape):
-    """rocprofv3's name of the M2P kernel that the tuned tile shape launches
-    (shapes 1 and 2 the row-staged kernel, 0 and 3 the direct one without and
-    with crossbar B fragments)."""
-    if family == "m2p_f32" and shape in (1, 2):
-        return f"k_m2p_s<float, {p}, {shape}>"
-    return SYMBOLS.get(family, "").format(p=p, xb="true" if shape == 3 else "false")
+def executed_share(family, p):
+    """Share of a family's profiled operations that its kernel executes.  The profile
+    counts the Cartesian translation of every (target, source) pair: (p+1)(p+2)(p+3)/6
+    coefficients, 189 sources per group.  The kernels work on the (p+1)^2 independent
+    coefficients, and M2P on 56 orbits of sources that share an operator."""
+    def n_full(q):
+        return (q + 1) * (q + 2) * (q + 3) // 6
+
+    def n_folded(q):
+        return (q + 1) ** 2
+    if family.startswith("m2p_"):
+        return 56 * (n_folded(p) + 3 * n_folded(p - 1)) / (189 * (n_full(p) + 3 * n_full(p - 1)))
+    if family.startswith("m2l_"):  # pairs with |a| + |b| <= p
+        def pairs(inc):
+            return sum(inc(d) * sum(inc(e) for e in range(p - d + 1)) for d in range(p + 1))
+        return pairs(lambda d: 2 * d + 1) / pairs(lambda d: (d + 1) * (d + 2) // 2)
+    return 1.0
 
 
-def measured_traffic(family, p, workload, shape=0):
+def measured_traffic(family, p, workload):
     """HBM bytes per launch from the committed FETCH_SIZE/WRITE_SIZE summary of this
     kernel and workload, or None (none taken, or the kernels changed since)."""
     import glob
     sys.path.insert(0, ROOT)
     from bench_profile import source_hash
-    want = m2p_kernel_symbol(family, p, shape)
+    want = SYMBOLS.get(family, "").format(p=p)
     for f in glob.glob(os.path.join(ROOT, "profiles", "traffic_*.json")):
         try:
             t = json.load(open(f))
@@ -332,28 +332,24 @@ def measured_traffic(family, p, workload, shape=0):
     return None, None
 
 
-def roofline(res, precision, p=None, workload=None):
+def roofline(res, precision, p, workload=None):
     """Roofline of the kernel family with the largest summed time in the timed region."""
     prof = res["kernels"]
     name, k = max(prof.items(), key=lambda kv: kv[1]["ms"])
     total_ms = sum(v["ms"] for v in prof.values())
-    shapes = res.get("m2p_shape") or (res.get("autotune") or {}).get("m2p_shape") or [0, 0]
-    shape = shapes[1 if name.endswith("f32") else 0]
-    traffic, tsrc = measured_traffic(name, p, workload, shape) if p is not None else (None, None)
+    traffic, tsrc = measured_traffic(name, p, workload)
     kname = KERNEL_NAMES.get(name, name)
-    if name.startswith("m2p_"):
-        kname = (f"k_m2p_s<float, P, {shape}>" if shape in (1, 2) and name == "m2p_f32"
-                 else kname.replace("XB", "true" if shape == 3 else "false"))
+    share = executed_share(name, p)
     common = {"kernel": kname, "family": name, "launches": k["launches"],
               "traffic_source": tsrc,
               "avg_launch_ms": k["ms"] / max(k["launches"], 1),
-              "flops_per_launch": k["flops"] / max(k["launches"], 1),
+              "flops_per_launch": share * k["flops"] / max(k["launches"], 1), "executed_share": share,
               "bytes_per_launch": k["bytes"] / max(k["launches"], 1), "share_of_step": k["ms"] / total_ms}
     if name in ("gather", "upward", "l2l"):
         achieved = k["bytes"] / (k["ms"] * 1e-3) / 1e9
         return {"bound": "hbm", "achieved": achieved, "peak": PEAK["hbm"], "unit": "GB/s",
                 "frac": achieved / PEAK["hbm"], "traffic": traffic, **common}
-    tf = k["flops"] / (k["ms"] * 1e-3) / 1e12 if k["ms"] > 0 else 0.0
+    tf = share * k["flops"] / (k["ms"] * 1e-3) / 1e12 if k["ms"] > 0 else 0.0
     fp = "fp32" if name.endswith("f32") else "fp64"
     if name in MFMA_FAMILIES:
         peak = PEAK[f"{fp}_mfma"]
@@ -482,8 +478,6 @@ def main():
     ap.add_argument("--no-fp64", action="store_true", help="skip the FP64-form run")
     ap.add_argument("--cpu-seconds", type=float, default=20.0)
     ap.add_argument("--no-autotune", action="store_true", help="keep the default tap splits")
-    ap.add_argument("--m2p-shape", type=int, default=0,
-                    help="M2P tile shape of the plans when the autotuner is off (afmm_options.m2p_shape)")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run a 256 MiB device copy (reference for the FETCH_SIZE/WRITE_SIZE counters)")
     args = ap.parse_args()
@@ -510,17 +504,17 @@ def main():
     mass_t = torch.from_numpy(m).cuda()
     print(f"[bench] workload {w.name}: {h.nleaves()} leaves", file=sys.stderr, flush=True)
 
-    r32, phi32, acc32 = time_form(h, mass_t, w.p, "fp32", args.steps, args.warmup, autotune=not args.no_autotune, m2p_shape=args.m2p_shape)
+    r32, phi32, acc32 = time_form(h, mass_t, w.p, "fp32", args.steps, args.warmup, autotune=not args.no_autotune)
     print(f"[bench] fp32 form: {r32['ms_per_step']:.3f} ms/step", file=sys.stderr, flush=True)
     r32s = None
     if args.overlap:
-        r32s, _, _ = time_form(h, mass_t, w.p, "fp32", args.steps, 1, overlap=True, autotune=not args.no_autotune, m2p_shape=args.m2p_shape)
+        r32s, _, _ = time_form(h, mass_t, w.p, "fp32", args.steps, 1, overlap=True, autotune=not args.no_autotune)
         print(f"[bench] fp32 form, two streams: {r32s['ms_per_step']:.3f} ms/step", file=sys.stderr, flush=True)
     outputs = {"fp32": (phi32, acc32)}
     r32g = None
     if not args.no_graph:
         r32g, phi32g, acc32g = time_form(h, mass_t, w.p, "fp32", args.steps, args.warmup, graph=True,
-                                         autotune=not args.no_autotune, m2p_shape=args.m2p_shape)
+                                         autotune=not args.no_autotune)
         print(f"[bench] fp32 form, graph replay: {r32g['ms_per_step']:.3f} ms/step", file=sys.stderr, flush=True)
         # identical bits to the eager solves when the tuner chose the same splits
         same = (r32g["autotune"] or {}).get("m2l_split") == (r32["autotune"] or {}).get("m2l_split") and \
@@ -529,7 +523,7 @@ def main():
     r64 = None
     if not args.no_fp64:
         r64, phi64, acc64 = time_form(h, mass_t, w.p, "fp64", max(args.steps // 2, 1), 1,
-                                      autotune=not args.no_autotune, m2p_shape=args.m2p_shape)
+                                      autotune=not args.no_autotune)
         outputs["fp64"] = (phi64, acc64)
         print(f"[bench] fp64 form: {r64['ms_per_step']:.3f} ms/step", file=sys.stderr, flush=True)
 
@@ -560,7 +554,7 @@ def main():
         # this order, the host's level-2 far-operator table
         try:
             rp, _, _ = time_form(h, mass_t, w.p, "fp32", max(args.steps // 2, 2), 1,
-                                 autotune=not args.no_autotune, m2p_shape=args.m2p_shape, periodic=True)
+                                 autotune=not args.no_autotune, periodic=True)
             periodic = {"ms_per_step": rp["ms_per_step"], "value": rp["value"], "unit": "cells/s",
                         "over_isolated": rp["ms_per_step"] / r32["ms_per_step"],
                         "plan_create_ms": rp["plan_create_ms"], "autotune": rp["autotune"],

@@ -105,22 +105,14 @@ typedef struct afmm_options {
   uint32_t flags;            /* AFMM_CHECK_INPUT | AFMM_SERIAL | AFMM_OVERLAP | AFMM_GRAPH |
                                 AFMM_PAPER_QUAD_CAP | AFMM_SELF_POTENTIAL | AFMM_PERIODIC */
   int32_t fp64_levels;       /* mixed form: FMM levels <= this stay FP64 (default 3) */
-  int32_t tap_split;         /* M2L and M2P blocks per tile: the 189 source offsets of a tile are
+  int32_t tap_split;         /* M2L and M2P blocks per tile: the source offsets of a tile are
                                 split over this many blocks and their partial sums reduced in a
                                 fixed order; 0 = automatic (enough blocks to fill the GPU), else
                                 1..21.  Results depend on it only through FP rounding order. */
   size_t max_device_bytes;   /* cap on the plan's device memory; 0 = no cap */
-  int32_t m2p_shape;         /* tile shape of the intermediate-field (M2P) launch: 0 = one
-                                16-group tile per wave with each lane loading its own B
-                                fragments (default), 1 = the same tile with the source rows
-                                loaded row by row and staged through LDS, 2 = as 1 with two
-                                16-group tiles of one parity class per wave (p <= 5), 3 = as 0
-                                with the source rows loaded row by row and each lane's
-                                fragments taken from other lanes over the cross-lane crossbar
-                                (no LDS staging).  FP64 launches run shapes 0 and 3 (3 up to p = 7); a shape
-                                the order or precision does not support falls back to 0.  The
-                                autotuner chooses it by timing.  Results do not depend on it:
-                                every shape runs the same products in the same order. */
+  int32_t m2p_shape;         /* 0..3, the tile shapes of earlier intermediate-field (M2P) launches.
+                                Results never depended on it; every value now runs the one kernel
+                                that is left. */
 } afmm_options;
 
 /* Defaults: p = 4, FP64, G = 1, boxlen = 1, no flags, fp64_levels = 3, tap_split = 0 (automatic),
@@ -360,10 +352,8 @@ afmm_status afmm_batch_get_profile(afmm_batch* batch, afmm_stage_time* out, int3
  * depends on the hierarchy's shape.  afmm_plan_autotune times candidate splits
  * (per-launch events, serial launches; each candidate's time is the minimum
  * over 5 full solves of the caller's data after one warm-up) and keeps, per
- * precision, the fastest M2L split and the fastest M2P (tile shape, split)
- * pair (the shapes of afmm_options.m2p_shape that the order and precision
- * support); it leaves phi/acc holding a full solve and counts as one
- * (AFMM_ALL_LEVELS).
+ * precision, the fastest M2L split and the fastest M2P split; it leaves phi/acc
+ * holding a full solve and counts as one (AFMM_ALL_LEVELS).
  * afmm_batch_autotune does the same on a batch and re-captures its graph.
  * Results of later solves change only through FP rounding order.  Takes a few
  * dozen solves; no host-visible allocation beyond the partial-sum buffers.
@@ -374,7 +364,7 @@ typedef struct afmm_tune_result {
   double ms_before;       /* summed launch time of one solve before / after */
   double ms_after;
   int32_t candidates;     /* candidate configurations timed */
-  int32_t m2p_shape[2];   /* chosen M2P tile shapes (see afmm_options.m2p_shape) */
+  int32_t m2p_shape[2];   /* 0 (see afmm_options.m2p_shape) */
 } afmm_tune_result;
 afmm_status afmm_plan_autotune(afmm_plan* plan, const double* d_mass, double* d_phi, double* d_acc,
                                void* hip_stream, afmm_tune_result* out);

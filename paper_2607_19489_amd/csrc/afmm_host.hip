@@ -588,7 +588,10 @@ struct HostTables {
   std::vector<int16_t> up;      // [K][3]
   std::vector<double> Dil, Dsame, cfac2, cfacn, l2lw, l2p, binom;
   std::vector<int32_t> taps;        // [8][189]
-  std::vector<int16_t> m2p_off;     // [steps][64]
+  std::vector<int8_t> symtaps;      // [8][56][8]
+  std::vector<double> symE;         // [orbit][8][K] D~ over the 8 child offsets as characters
+  std::vector<double> symA64;       // M2P operators (TablesDev::symA), one per element type
+  std::vector<float> symA32;
   std::vector<int16_t> m2l_off;     // [steps][64]
   std::vector<int32_t> m2m_start, m2m_list;
   std::vector<double> m2m_w;
@@ -805,7 +808,7 @@ static void build_tables(int p, HostTables& H) {
         H.tapsT.push_back(e | (oF << 5) | (di << 8));
       }
   // MFMA A-operand offsets into the staged D~ rows (sD[o][g], row stride KS, zero slot 8 KS)
-  const int KS = dstage_ks(p), ZERO = 8 * KS, K1 = nmi(p - 1), KH = nh(p), KH1 = nh(p - 1);
+  const int KS = dstage_ks(p), ZERO = 8 * KS, K1 = nmi(p - 1), KH = nh(p);
   auto deg = [&](int idx) { return H.mi[4 * idx + 3]; };
   // Folds of the source coefficients: z^(k+2m) stands for (-1)^m (x^2 + y^2)^m z^k in
   // every sum with harmonic derivatives, so coefficient (i - 2r, j - 2(m - r), k + 2m)
@@ -823,17 +826,32 @@ static void build_tables(int p, HostTables& H) {
       }
     H.fold_start.push_back((int32_t)H.fold_list.size());
   }
-  H.m2p_off.clear();
-  for (int rt = 0; rt < 2; ++rt) {
-    const int steps = ((rt == 0 ? KH : KH1) + 3) / 4;
-    for (int kb = 0; kb < steps; ++kb)
-      for (int lane = 0; lane < 64; ++lane) {
-        const int i = lane & 15, k = 4 * kb + (lane >> 4);
-        const int c = 2 * rt + (i >> 3), o = i & 7;  // c: 0 phi, 1..3 a_x..a_z
-        int v = ZERO;
-        if (c == 0 && k < KH) v = o * KS + h_full(k);
-        if (c > 0 && k < KH1) v = o * KS + H.up[3 * h_full(k) + (c - 1)];
-        H.m2p_off.push_back((int16_t)v);
+  // Orbits of the interaction list (afmm_internal.h): the sources of each, per
+  // parity class, and the characters of its D~ rows over the child offsets,
+  //   E_chi[g] = 1/8 sum_o chi(o) D~_g(-2 d + o - 1/2),  chi(o) = (-1)^popcount(chi & ~o),
+  // for the representative d >= 0
+  H.symtaps.assign((size_t)8 * kSymOrbits * 8, 0);
+  H.symE.assign((size_t)kSymOrbits * 8 * K, 0.0);
+  for (int w = 0; w < kSymOrbits; ++w) {
+    const int m = w / 7, pt = sym_axes(sym_set(m, w % 7));
+    int t[3];
+    for (int i = 0; i < 3; ++i) t[i] = (pt >> i & 1) ? ((m >> i & 1) ? 1 : 2) : ((m >> i & 1) ? 3 : 0);
+    for (int oF = 0; oF < 8; ++oF)
+      for (int sg = 0; sg < 1 << sym_bits(pt); ++sg) {
+        int e = 0, bit = 0;
+        const int pw[3] = {1, 3, 9};
+        for (int i = 0; i < 3; ++i) {
+          const int d = (pt >> i & 1) ? ((sg >> bit++ & 1) ? -t[i] : t[i]) : ((oF >> i & 1) ? -t[i] : t[i]);
+          e += (((oF >> i & 1) + d + 4) / 2 - 1) * pw[i];  // father offset e_i = floor((oF + d) / 2), plus 1
+        }
+        H.symtaps[((size_t)oF * kSymOrbits + w) * 8 + sg] = (int8_t)e;
+      }
+    const int di = (t[0] + 3) + 7 * (t[1] + 3) + 49 * (t[2] + 3);
+    for (int chi = 0; chi < 8; ++chi)
+      for (int g = 0; g < K; ++g) {
+        double v = 0.0;
+        for (int o = 0; o < 8; ++o) v += (__builtin_popcount(chi & ~o) & 1 ? -1.0 : 1.0) * H.Dil[((size_t)di * 8 + o) * K + g];
+        H.symE[((size_t)w * 8 + chi) * K + g] = 0.125 * v;
       }
   }
   // adjoint: transposed L2L pairs (b <= c componentwise, g = c - b) per c
@@ -908,6 +926,40 @@ static void build_tables(int p, HostTables& H) {
   }
 }
 
+// M2P operator of an orbit: lane (block q, row i) of character chi holds, for the
+// coefficients a of block q, E_chi[a] (i = 0, potential) or E_(chi ^ e_i)[a + e_i]
+// (acceleration i).
+template <typename T, int P>
+static void sym_operator(const HostTables& H, std::vector<T>& v) {
+  using SL = SymLayout<P, (int)sizeof(T)>;
+  constexpr SL sl{};
+  v.assign((size_t)kSymOrbits * SL::NP * 8 * 64 * SL::CP, T(0));
+  size_t at = 0;
+  for (int ws = 0; ws < kSymOrbits * SL::NP; ++ws) {  // (m, pass, j)
+    const int s = ws / 7 % SL::NP, w = ws / (7 * SL::NP) * 7 + ws % 7;
+    for (int chi = 0; chi < 8; ++chi)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int e = 0; e < SL::CP; ++e, ++at) {
+          const int h = sl.coef[(s * kSymBlocks + (lane >> 2)) * SL::CP + e], i = lane & 3;
+          if (h < 0 || (i > 0 && h_deg(h) == P)) continue;
+          const int x = i > 0 ? chi ^ (1 << (i - 1)) : chi, g = i > 0 ? H.up[3 * h_full(h) + i - 1] : h_full(h);
+          v[at] = (T)H.symE[((size_t)w * 8 + x) * H.K + g];
+        }
+  }
+}
+
+static void build_sym(int p, HostTables& H) {
+  switch (p) {
+#define X(PP)                              \
+  case PP:                                 \
+    sym_operator<double, PP>(H, H.symA64); \
+    sym_operator<float, PP>(H, H.symA32);  \
+    break;
+    X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8)
+#undef X
+  }
+}
+
 // The translation tables depend on the order only: built once per order and
 // shared (read only) by every plan of the process.
 static std::shared_ptr<const HostTables> tables_for(int p) {
@@ -917,6 +969,7 @@ static std::shared_ptr<const HostTables> tables_for(int p) {
   if (!cache[p]) {
     auto t = std::make_shared<HostTables>();
     build_tables(p, *t);
+    build_sym(p, *t);
     cache[p] = t;
   }
   return cache[p];
@@ -987,9 +1040,6 @@ struct afmm_plan {
   // MFMA tile records of every level, one array per precision (0 FP64, 1 FP32);
   // range[l] = {precision, first tile, count}
   MfmaTiles m2p_all[2], m2l_all[2];
-  MfmaTiles m2p_all2[2];            // M2P tiles of 32 groups (tile shape 2), same level ranges as below
-  int m2p_range2[kMaxLevel][3] = {};
-  int m2p_shape[2] = {0, 0};        // M2P tile shape per precision (afmm_options.m2p_shape)
   // Level solves (ATS, Alg. 2): the M2L / L2L work restricted to the FMM cells
   // that are ancestors of the leaves of target level l (per target level l)
   struct AtsChain {
@@ -1418,6 +1468,51 @@ static int append_tiles(const Topology& T, int target, const std::vector<int32_t
   return n;
 }
 
+// M2P tiles of one level: up to nc groups of one parity class whose sources have
+// at most nf distinct refined fathers (neighbours of the groups' fathers G), tiles
+// of the 8 classes interleaved.  Returns the number of tiles appended.
+static int append_m2p_tiles(const Topology& T, int target, const std::vector<int32_t>& grp, int nc, int nf,
+                            std::vector<int32_t>& out) {
+  const HostLevel &L1 = T.lv[target - 1], &L2 = T.lv[target - 2];
+  std::vector<int32_t> cls[8], end[8];  // groups per class, and where each tile ends
+  for (int32_t F : grp) cls[L1.refcell[F] & 7].push_back(F);
+  parallel_ranges(8, grp.size() > 256 ? 8 : 1, [&](int64_t b, int64_t e, int) {
+    for (int64_t c = b; c < e; ++c) {
+      std::vector<int32_t> seen(L2.nref(), -1);  // last tile with this father
+      int cols = 0, fathers = 0, tile = 0;
+      for (size_t i = 0; i < cls[c].size();) {
+        const int32_t* nb = &L2.nbr[(size_t)(L1.refcell[cls[c][i]] >> 3) * 27];
+        int add = 0;
+        for (int k = 0; k < 27; ++k) add += nb[k] >= 0 && L2.rank[nb[k]] >= 0 && seen[L2.rank[nb[k]]] != tile;
+        if (cols == nc || fathers + add > nf) {
+          end[c].push_back((int32_t)i);
+          cols = fathers = 0;
+          ++tile;
+          continue;
+        }
+        for (int k = 0; k < 27; ++k)
+          if (nb[k] >= 0 && L2.rank[nb[k]] >= 0) seen[L2.rank[nb[k]]] = tile;
+        ++cols;
+        fathers += add;
+        ++i;
+      }
+      if (cols) end[c].push_back((int32_t)cls[c].size());
+    }
+  });
+  size_t maxt = 0;
+  for (auto& e : end) maxt = std::max(maxt, e.size());
+  int n = 0;
+  for (size_t t = 0; t < maxt; ++t)
+    for (int c = 0; c < 8; ++c) {
+      if (t >= end[c].size()) continue;
+      out.push_back(target);
+      const int32_t b = t ? end[c][t - 1] : 0;
+      for (int j = 0; j < nc; ++j) out.push_back(b + j < end[c][t] ? cls[c][b + j] : -1);
+      ++n;
+    }
+  return n;
+}
+
 static void dev_free(afmm_plan* P, void* ptr, size_t bytes) {
   if (!ptr) return;
   for (size_t i = 0; i < P->allocs.size(); ++i)
@@ -1568,21 +1663,21 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     // source copies: FP32 where an FP32 kernel reads this level (M2L of f = l+1 or
     // M2P of l+1 when l >= f64; near-field M2P of l when l > f64+1), FP64 where an
     // FP64 kernel does (l <= f64 + 1)
-    // Each copy has one extra row of zeros after the nref rows: the MFMA tap
-    // loops read it for a missing or leaf source, so that their loads need no
-    // branch.
+    // Each copy has one extra row of zeros after the nref rows: the tap loops
+    // read it for a missing or leaf source, so that their loads need no branch.
+    auto source_copy = [&](int bytes, void** out) -> afmm_status {
+      const size_t row = (size_t)src_row(P->opt.p, bytes) * bytes;
+      afmm_status r = dev_alloc(P, out, (size_t)(D.nref + 1) * row);
+      if (!r && hipMemsetAsync((char*)*out + (size_t)D.nref * row, 0, row, st) != hipSuccess)
+        r = fail(AFMM_E_DEVICE, "zero row of the source copy");
+      return r;
+    };
     if (mixed && l >= f64) {
-      const size_t row = (size_t)src_row(P->opt.p, 4) * sizeof(float);
-      if ((s = dev_alloc(P, &p, (size_t)(D.nref + 1) * row))) return s;
-      if (hipMemsetAsync((char*)p + (size_t)D.nref * row, 0, row, st) != hipSuccess)
-        return fail(AFMM_E_DEVICE, "zero row of the source copy");
+      if ((s = source_copy(4, &p))) return s;
       D.S32 = (float*)p;
     }
     if (!mixed || l <= f64 + 1) {
-      const size_t row = (size_t)src_row(P->opt.p, 8) * sizeof(double);
-      if ((s = dev_alloc(P, &p, (size_t)(D.nref + 1) * row))) return s;
-      if (hipMemsetAsync((char*)p + (size_t)D.nref * row, 0, row, st) != hipSuccess)
-        return fail(AFMM_E_DEVICE, "zero row of the source copy");
+      if ((s = source_copy(8, &p))) return s;
       D.Sc64 = (double*)p;
     }
     if (l <= f64) {
@@ -1612,12 +1707,13 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
   {
     std::vector<int8_t> mi8(H.mi.begin(), H.mi.end());
     int8_t* d_mi;
-    int16_t *d_sum, *d_up, *d_m2p_off, *d_m2l_off;
+    int16_t *d_sum, *d_up, *d_m2l_off;
     double* d_binom;
     int32_t *d_taps, *d_tinfo;
+    int8_t* d_stap;
     if ((s = upload(P, mi8, &d_mi, st)) || (s = upload(P, H.sumidx, &d_sum, st)) || (s = upload(P, H.up, &d_up, st)) ||
         (s = upload(P, H.binom, &d_binom, st)) || (s = upload(P, H.taps, &d_taps, st)) ||
-        (s = upload(P, H.m2p_off, &d_m2p_off, st)) || (s = upload(P, H.m2l_off, &d_m2l_off, st)) ||
+        (s = upload(P, H.symtaps, &d_stap, st)) || (s = upload(P, H.m2l_off, &d_m2l_off, st)) ||
         (s = upload(P, H.m2l_tinfo, &d_tinfo, st)))
       return s;
     P->cm.mi = d_mi;
@@ -1686,7 +1782,7 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     P->cm.l2lT_list = d_ltl;
     P->cm.l2lT_w = d_ltw;
     P->mt.taps = d_taps;
-    P->mt.m2p_off = d_m2p_off;
+    P->mt.symtaps = d_stap;
     P->mt.m2l_off = d_m2l_off;
     P->mt.m2l_tinfo = d_tinfo;
   }
@@ -1745,24 +1841,15 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
   // parity-class tiles of the MFMA kernels (all levels of one precision in one
   // array) and the intermediate-field partials
   {
-    std::vector<int32_t> m2p_rec[2], m2l_rec[2], m2p_rec2[2];
-    int m2p_nc[2] = {m2p_columns(P->opt.p, false), m2p_columns(P->opt.p, true)};
-    // 32-group tiles for tile shape 2, where the order and precision allow it
-    const bool two[2] = {m2p_shape_ok(P->opt.p, false, 2), m2p_shape_ok(P->opt.p, true, 2)};
+    std::vector<int32_t> m2p_rec[2], m2l_rec[2];
+    const int m2p_nc[2] = {m2p_cols(P->opt.p, 8), m2p_cols(P->opt.p, 4)};
     for (int l = 3; l <= T.lmax; ++l) {
       const int pr = (mixed && (l - 1) > f64) ? 1 : 0;
       const int n0 = (int)(m2p_rec[pr].size() / (m2p_nc[pr] + 1));
-      const int n = append_tiles(T, l, T.leafgrp[l], m2p_nc[pr], m2p_rec[pr]);
+      const int n = append_m2p_tiles(T, l, T.leafgrp[l], m2p_nc[pr], m2p_fathers(P->opt.p, pr ? 4 : 8), m2p_rec[pr]);
       P->m2p_range[l][0] = pr;
       P->m2p_range[l][1] = n0;
       P->m2p_range[l][2] = n;
-      if (two[pr]) {
-        const int c = m2p_shape_columns(2);
-        const int q0 = (int)(m2p_rec2[pr].size() / (c + 1));
-        P->m2p_range2[l][0] = pr;
-        P->m2p_range2[l][1] = q0;
-        P->m2p_range2[l][2] = append_tiles(T, l, T.leafgrp[l], c, m2p_rec2[pr]);
-      }
       const int pm = (mixed && l > f64) ? 1 : 0;
       if (l <= T.lmax - 1) {
         const int m0 = (int)(m2l_rec[pm].size() / 17);
@@ -1785,28 +1872,34 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
                          : nt > 0              ? std::max(1, std::min(21, (2 * ncu + nt - 1) / nt))
                                                : 1;
     }
-    // M2P likewise, aiming at 12 waves per CU; each tap range writes its own
-    // partial set, summed in order by the leaf kernel
+    // M2P likewise; each range of orbits writes its own partial set, summed in
+    // order by the leaf kernel.  Powers of two, whose ranges are whole phases of 7
+    // orbits (each restages its rows), up to one block per CU: the next larger
+    // split runs slower (32^3 at p = 4: 75, 45, 35, 38 us at 1, 2, 4, 8, and the
+    // leaf kernel 3 us more per step).  Two ranges up to four blocks per CU, where
+    // the last round of whole tiles leaves most CUs idle (780 tiles at p = 6, FP64:
+    // 406, 374, 368 us at 1, 2, 4; 4096 tiles at p = 4: 741, 820 us at 1, 2).
     for (int pr = 0; pr < 2; ++pr) {
       const int nt = (int)(m2p_rec[pr].size() / (m2p_nc[pr] + 1));
-      P->m2p_split[pr] = P->opt.tap_split > 0 ? P->opt.tap_split
-                         : nt > 0              ? std::max(1, std::min(8, (12 * ncu + nt - 1) / nt))
-                                               : 1;
+      int sp = nt < 4 * ncu ? 2 : 1;
+      while (sp < 8 && nt * sp < ncu) sp *= 2;
+      P->m2p_split[pr] = P->opt.tap_split > 0 ? P->opt.tap_split : nt > 0 ? sp : 1;
     }
     if ((s = alloc_split_buffers(P))) return s;
     for (int pr = 0; pr < 2; ++pr) {
       int32_t* d = nullptr;
       if ((s = upload(P, m2p_rec[pr], &d, st))) return s;
       P->m2p_all[pr] = {d, (int)(m2p_rec[pr].size() / (m2p_nc[pr] + 1)), m2p_nc[pr]};
-      if (two[pr] && !m2p_rec2[pr].empty()) {
-        if ((s = upload(P, m2p_rec2[pr], &d, st))) return s;
-        const int c = m2p_shape_columns(2);
-        P->m2p_all2[pr] = {d, (int)(m2p_rec2[pr].size() / (c + 1)), c};
-      }
-      P->m2p_shape[pr] = m2p_shape_ok(P->opt.p, pr == 1, P->opt.m2p_shape) ? P->opt.m2p_shape : 0;
       if ((s = upload(P, m2l_rec[pr], &d, st))) return s;
       P->m2l_all[pr] = {d, (int)(m2l_rec[pr].size() / 17), 16};
     }
+    float* a32 = nullptr;
+    double* a64 = nullptr;
+    if ((!m2p_rec[0].empty() && (s = upload(P, H.symA64, &a64, st))) ||
+        (!m2p_rec[1].empty() && (s = upload(P, H.symA32, &a32, st))))
+      return s;
+    P->t64.symA = a64;
+    P->t32.symA = a32;
     // ATS chains: walking up from the groups of target level l, the needed
     // cells of FMM level f are the refined ancestors of level-l leaves; the
     // M2L group of f-1 is needed when one of its children is
@@ -2092,8 +2185,7 @@ static afmm_status run_solve(afmm_plan* P, const double* msrc, int fmax, int lo,
     return s;
   // intermediate field (M2P) of the leaf levels lo..hi: one launch per precision
   for (int pr = 0; pr < 2; ++pr) {
-    const int shape = P->m2p_shape[pr];
-    const int(*range)[3] = shape == 2 ? P->m2p_range2 : P->m2p_range;
+    const int(*range)[3] = P->m2p_range;
     int t0 = -1, n = 0;
     for (int l = std::max(lo, 3); l <= hi; ++l)
       if (P->m2p_range[l][0] == pr && range[l][2] > 0) {
@@ -2102,8 +2194,7 @@ static afmm_status run_solve(afmm_plan* P, const double* msrc, int fmax, int lo,
       }
     if (n <= 0) continue;
     hipEvent_t a = prof_begin(P, sm);
-    if ((s = dev_check(P, launch_m2p(p, pr == 1, shape == 2 ? P->m2p_all2[pr] : P->m2p_all[pr], t0, n,
-                                     P->m2p_split[pr], shape, P->mt, P->d_lvs, P->t32, P->t64, sm), "m2p")))
+    if ((s = dev_check(P, launch_m2p(p, pr == 1, P->m2p_all[pr], t0, n, P->m2p_split[pr], P->mt, P->d_lvs, P->t32, P->t64, sm), "m2p")))
       return s;
     for (int l = std::max(lo, 3); l <= hi; ++l)
       if (P->m2p_range[l][0] == pr) {
@@ -2543,52 +2634,13 @@ afmm_status autotune_core(afmm_plan* P, SolveFn solve, hipStream_t st, afmm_tune
       if ((s = trial(P->m2l_split, pr, c, best, arg, pr ? kM2L32 : kM2L64, kL2L))) return s;
     P->m2l_split[pr] = arg;
   }
-  constexpr int kShapes = 4;
   for (int pr = 1; pr >= 0; --pr) {
     if (P->m2p_all[pr].ntiles == 0) continue;
-    const int ka = pr ? kM2P32 : kM2P64, kb = pr ? kLeaf32 : kLeaf64;
-    double sbest[kShapes];
-    int ssplit[kShapes];
-    for (int shape = 0; shape < kShapes; ++shape) {
-      sbest[shape] = 1e300;
-      ssplit[shape] = P->m2p_split[pr];
-      if (!m2p_shape_ok(P->opt.p, pr == 1, shape) || (shape == 2 && P->m2p_all2[pr].ntiles == 0)) continue;
-      P->m2p_shape[pr] = shape;
-      for (int c : cand_m2p)
-        if ((s = trial(P->m2p_split, pr, c, sbest[shape], ssplit[shape], ka, kb))) return s;
-    }
-    // the two fastest shapes at their best splits, timed again in turn three
-    // times each: a sweep takes seconds, over which the clocks drift enough
-    // to decide a close call between shapes timed early and late
-    int sa = -1, sb = -1;
-    for (int shape = 0; shape < kShapes; ++shape) {
-      if (sbest[shape] >= 1e300) continue;
-      if (sa < 0 || sbest[shape] < sbest[sa]) sb = sa, sa = shape;
-      else if (sb < 0 || sbest[shape] < sbest[sb]) sb = shape;
-    }
-    if (sa < 0) continue;
-    if (sb >= 0) {
-      double tot[2] = {0, 0};
-      bool ok = true;  // a refused allocation keeps the sweep's choice
-      for (int r = 0; r < 3 && ok; ++r)
-        for (int j = 0; j < 2 && ok; ++j) {
-          const int shape = j ? sb : sa;
-          P->m2p_shape[pr] = shape;
-          P->m2p_split[pr] = ssplit[shape];
-          const afmm_status q = realloc();
-          if (q == AFMM_E_OUT_OF_MEMORY && !P->dead) {
-            ok = false;
-            break;
-          }
-          if (q) return q;
-          double km[kNumKinds];
-          if ((s = measure(km))) return s;
-          tot[j] += km[ka] + km[kb];
-        }
-      if (ok && tot[1] < tot[0]) sa = sb;
-    }
-    P->m2p_shape[pr] = sa;
-    P->m2p_split[pr] = ssplit[sa];
+    double best = 1e300;
+    int arg = P->m2p_split[pr];
+    for (int c : cand_m2p)
+      if ((s = trial(P->m2p_split, pr, c, best, arg, pr ? kM2P32 : kM2P64, pr ? kLeaf32 : kLeaf64))) return s;
+    P->m2p_split[pr] = arg;
   }
   // the chosen splits were timed, so they fitted then; a refusal now leaves
   // the last timed candidate's splits and buffers (consistent, just not the best)
@@ -2601,7 +2653,7 @@ afmm_status autotune_core(afmm_plan* P, SolveFn solve, hipStream_t st, afmm_tune
     for (int pr = 0; pr < 2; ++pr) {
       out->m2l_split[pr] = P->m2l_split[pr];
       out->m2p_split[pr] = P->m2p_split[pr];
-      out->m2p_shape[pr] = P->m2p_shape[pr];
+      out->m2p_shape[pr] = 0;
     }
     out->ms_before = before;
     out->ms_after = after;

@@ -82,29 +82,87 @@ __host__ __device__ constexpr int h_full(int h) {
   return mi_index(n - b - c, b, c);
 }
 
-// Layout of the scaled source copies (S32 / Sc64), KH = nh(p) folded
-// coefficients a row.  The MFMA kernels read the
-// B operand straight into registers: lane group g (lane >> 4) of a 16x16x4
-// step kb holds coefficient k = 4 kb + g.  A lane group needs STP steps
-// (STP = ceil(KH/4) rounded up to whole 16-byte vectors of VW = 16/bytes
-// values); its vector j holds steps VW j .. VW j + VW - 1.  The row stores the
-// vectors j-major: vector j of lane group g at (4 j + g) VW, so one 16-byte
-// load per lane (vector j for all 4 lane groups of a source) reads 64
+// Layout of the scaled source copies (S32 / Sc64): the KH = nh(p) folded
+// coefficients in NP passes of 16 blocks of CP values, [pass][block][CP], every
+// block holding coefficients of one parity class (the parities of a, b, c), so
+// that the reflections of a block's values are one sign per lane (M2P, M2L).
+// Lane q of 16 loads block q of a row as one vector of CP values (at most 16
+// bytes); unused slots are 0.  The eight classes need no more than 16 blocks
+// with 1, 1, 1, 2, 3, 4, 6, 6 values for p = 1..8 (49 of 64 slots hold a
+// coefficient at p = 6).  Behind the nref rows comes one row of zeros, read for
+// a missing or leaf source.
+constexpr int kSymBlocks = 16;
+__host__ __device__ constexpr int sym_cpl(int p) { return p <= 3 ? 1 : p <= 6 ? p - 2 : 6; }
+__host__ __device__ constexpr int sym_cp(int p, int bytes) {
+  return bytes == 4 ? (sym_cpl(p) <= 4 ? sym_cpl(p) : 3) : (sym_cpl(p) == 1 ? 1 : 2);
+}
+__host__ __device__ constexpr int sym_np(int p, int bytes) { return (sym_cpl(p) + sym_cp(p, bytes) - 1) / sym_cp(p, bytes); }
+__host__ __device__ constexpr int src_row(int p, int bytes) { return sym_np(p, bytes) * kSymBlocks * sym_cp(p, bytes); }
+
+template <int P, int BYTES>
+struct SymLayout {
+  static constexpr int CP = sym_cp(P, BYTES), NP = sym_np(P, BYTES), ROW = src_row(P, BYTES);
+  int pos[nh(P)];             // slot of folded coefficient h
+  int coef[ROW];              // coefficient of a slot, or -1
+  int par[kSymBlocks];        // parity class of a block (bit i: axis i odd)
+  constexpr SymLayout() : pos(), coef(), par() {
+    for (int i = 0; i < ROW; ++i) coef[i] = -1;
+    int blk = 0;
+    for (int c = 0; c < 8; ++c) {
+      int j = 0;
+      for (int n = 0; n <= P; ++n)
+        for (int z = 0; z <= (n > 0 ? 1 : 0); ++z)
+          for (int b = 0; b <= n - z; ++b) {
+            const int a = n - b - z;
+            if (((a & 1) | (b & 1) << 1 | (z & 1) << 2) != c) continue;
+            const int q = blk + j / (NP * CP), e = j % (NP * CP);
+            const int at = (e / CP * kSymBlocks + q) * CP + e % CP;
+            pos[h_index(a, b, z)] = at;
+            coef[at] = h_index(a, b, z);
+            par[q] = c;
+            ++j;
+          }
+      blk += (j + NP * CP - 1) / (NP * CP);
+    }
+  }
+};
+
+// Rows of the adjoint's local-expansion bars: all K coefficients in the order in
+// which its kernel reads the B operand straight into registers.  Lane group g
+// (lane >> 4) of a 16x16x4 step kb holds coefficient k = 4 kb + g.  A lane group
+// needs STP steps (STP = ceil(K/4) rounded up to whole 16-byte vectors of VW =
+// 16/bytes values); its vector j holds steps VW j .. VW j + VW - 1.  The row
+// stores the vectors j-major: vector j of lane group g at (4 j + g) VW, so one
+// 16-byte load per lane (vector j for all 4 lane groups of a source) reads 64
 // contiguous bytes of each source row.  Coefficient k therefore sits at
 // ((k >> 2) / VW) 4 VW + (k & 3) VW + (k >> 2) % VW; unused slots are 0.
-__host__ __device__ constexpr int row_stp(int k, int bytes) {
-  return (((k + 3) / 4) + (16 / bytes) - 1) / (16 / bytes) * (16 / bytes);
+__host__ __device__ constexpr int full_stp(int p, int bytes) {
+  return (((nmi(p) + 3) / 4) + (16 / bytes) - 1) / (16 / bytes) * (16 / bytes);
 }
-__host__ __device__ constexpr int src_stp(int p, int bytes) { return row_stp(nh(p), bytes); }
-__host__ __device__ constexpr int src_row(int p, int bytes) { return 4 * src_stp(p, bytes); }
-// rows of all K coefficients in the same layout (the adjoint's local-expansion bars)
-__host__ __device__ constexpr int full_stp(int p, int bytes) { return row_stp(nmi(p), bytes); }
 __host__ __device__ constexpr int full_row(int p, int bytes) { return 4 * full_stp(p, bytes); }
 __host__ __device__ constexpr int src_pos(int k, int bytes) {
   return ((k >> 2) / (16 / bytes)) * 4 * (16 / bytes) + (k & 3) * (16 / bytes) + (k >> 2) % (16 / bytes);
 }
-// element offset of vector j of lane group g in a source row
+// element offset of vector j of lane group g in such a row
 __host__ __device__ constexpr int src_vec(int j, int g, int bytes) { return (4 * j + g) * (16 / bytes); }
+
+// The 189 source offsets of a group (d in [-2, 3] on each axis, mirrored where the
+// group's octant bit is set, less the 27 near ones) as 56 orbits under the
+// reflections of the axes: on each axis the offsets are {0}, {-1, 1}, {-2, 2} and
+// {3}.  All sources of an orbit are in one octant of their fathers: the group's,
+// with the bits of m flipped, m the axes with an odd offset.  Per m there is one
+// orbit for every set PT of reflected axes but PT = m (the near offsets): offset
+// 1 or 2 on a reflected axis, 3 or 0 on the others as m is set or not.  Orbit
+// w = 7 m + j takes the j-th set of sym_axes(0..7) without m; bit b of a source's
+// index is set where its offset on the b-th axis of PT is negative.
+constexpr int kSymOrbits = 56;
+__host__ __device__ constexpr int sym_axes(int t) { return (0x01243567 >> (4 * t)) & 7; }
+__host__ __device__ constexpr int sym_bits(int pt) { return (pt & 1) + ((pt >> 1) & 1) + ((pt >> 2) & 1); }
+// position t of orbit (m, j)'s set
+__host__ __device__ constexpr int sym_set(int m, int j) {
+  const int t = sym_axes(m);  // the order is its own inverse: m's position in it
+  return j < t ? j : j + 1;
+}
 
 // D~ rows of one source offset in the layout the MFMA kernels stage in LDS:
 // row o (child octant) at o * dstage_ks(p), coefficients g < K then zeros up
@@ -167,7 +225,7 @@ struct LevelDev {
   double* mass = nullptr;            // [n] leaf masses of this solve (0 for refined cells)
   double* S64 = nullptr;             // [nref][K] multipoles (FP64), used by the upward pass
   float* S32 = nullptr;              // [nref][src_row(p, 4)] source copy (-1)^|a|/a! 2^|a| S~_a, folded, FP32
-                                     // (mixed form), in the lane-group layout above
+                                     // (mixed form), in the layout above
   double* Sc64 = nullptr;            // [nref][src_row(p, 8)] same source copy in FP64
   double* L64 = nullptr;             // [nref][K] local expansions (FP64 levels)
   float* L32 = nullptr;              // [nref][K] local expansions (FP32 levels)
@@ -195,6 +253,7 @@ struct TablesDev {
   const T* l2lw = nullptr;    // [8][p+1][K] L2L weights 2^(-1-|b|) u^g/g! per child octant and |b|
   const T* l2p = nullptr;     // [8][4][K] L2P weights (phi, ax, ay, az) per child octant
   const T* nearA = nullptr;   // [2][near_ksteps / VW][64][VW] near-field operator, MFMA A layout
+  const T* symA = nullptr;    // [8 m][NP][7][8][64][CP] M2P operator per orbit, pass and character (SymLayout)
   const T* adjNearA = nullptr;  // [216][64] transposed same-level near field (adjoint), MFMA A layout
 };
 
@@ -232,7 +291,7 @@ struct MfmaTiles {
 
 struct MfmaTables {
   const int32_t* taps = nullptr;      // [8][189] per parity class: e | o' << 5 | d_index << 8
-  const int16_t* m2p_off = nullptr;   // [steps][64] sD offsets of the M2P A operand
+  const int8_t* symtaps = nullptr;    // [8][56][8] per parity class and orbit: its sources' fathers (neighbour e)
   const int16_t* m2l_off = nullptr;   // [steps][64] sD offsets of the M2L A operand
   const int32_t* m2l_tinfo = nullptr; // [NT][2] k-steps and first step of each M2L row tile
 };
@@ -306,9 +365,15 @@ hipError_t launch_adj_out(int p, const LevelDev& lv1, const LevelDev& lv0, int h
 // (list leaf, P2M only) and the others (list mix, M2M of refined children).
 hipError_t launch_upward(int p, const int32_t* leaf, int nleaf, const int32_t* mix, int nmix, const LevelDev& lv,
                          const LevelDev& lvc, const CommonDev& cm, hipStream_t st);
-int m2p_columns(int p, bool fp32);
-bool m2p_shape_ok(int p, bool fp32, int shape);
-int m2p_shape_columns(int shape);
+// M2P tiles: quads of groups per wave (4 waves), groups per tile, and the most
+// distinct fathers of sources of one tile.  Two blocks share a CU's LDS, which
+// holds one octant's rows of those fathers in vectors of 4 values (of 8 bytes or
+// less for the low orders): 200 fathers cover 48 groups of a filled region, 240
+// 64 groups.
+__host__ __device__ constexpr int m2p_vec(int p, int bytes) { return sym_cp(p, bytes) == 3 ? 4 : sym_cp(p, bytes); }
+__host__ __device__ constexpr int m2p_quads(int p, int bytes) { return m2p_vec(p, bytes) * bytes == 16 ? 3 : 4; }
+__host__ __device__ constexpr int m2p_cols(int p, int bytes) { return 16 * m2p_quads(p, bytes); }
+__host__ __device__ constexpr int m2p_fathers(int p, int bytes) { return m2p_quads(p, bytes) == 3 ? 200 : 240; }
 // MFMA launches over a contiguous range [t0, t0 + n) of tile records; each
 // record is (target level, NC groups).  lvs is the device array of LevelDev.
 hipError_t launch_m2l_taps(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
@@ -317,7 +382,7 @@ hipError_t launch_m2l_taps(int p, bool fp32, const MfmaTiles& mt, int t0, int n,
 hipError_t launch_l2l(int p, bool fp32, bool parent_fp32, bool has_parent, int nsplit, const int32_t* grp, int ngrp,
                       const LevelDev& lv1, const LevelDev& lv0, const TablesDev<float>& t32,
                       const TablesDev<double>& t64, const CommonDev& cm, hipStream_t st);
-hipError_t launch_m2p(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, int shape,
+hipError_t launch_m2p(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit,
                       const MfmaTables& tabs, const LevelDev* lvs, const TablesDev<float>& t32,
                       const TablesDev<double>& t64, hipStream_t st);
 // cself: the self-potential constant (AFMM_SELF_POTENTIAL), 0 when off.

@@ -78,17 +78,18 @@ __device__ inline void m2p_row(const T* __restrict__ D, const T* __restrict__ S,
   constexpr int K = nh(P);
   constexpr int K1 = nh(P - 1);
   constexpr HTab<P> mt{};
+  constexpr SymLayout<P, (int)sizeof(T)> sl{};
   T phi = 0, ax = 0, ay = 0, az = 0;
 #pragma unroll
   for (int a = 0; a < K1; ++a) {
-    const T w = (T)(1.0 / (double)(1 << mt.deg[a])) * S[src_pos(a, (int)sizeof(T))];
+    const T w = (T)(1.0 / (double)(1 << mt.deg[a])) * S[sl.pos[a]];
     phi += w * D[mt.full[a]];
     ax += w * D[mt.up[a][0]];
     ay += w * D[mt.up[a][1]];
     az += w * D[mt.up[a][2]];
   }
 #pragma unroll
-  for (int a = K1; a < K; ++a) phi += (T)(1.0 / (double)(1 << mt.deg[a])) * S[src_pos(a, (int)sizeof(T))] * D[mt.full[a]];
+  for (int a = K1; a < K; ++a) phi += (T)(1.0 / (double)(1 << mt.deg[a])) * S[sl.pos[a]] * D[mt.full[a]];
   out[0] += phi;
   out[1] -= ax;
   out[2] -= ay;
@@ -116,29 +117,25 @@ hipError_t launch_gather_mass(const LevelDev& lv, const double* m_src, double* s
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
 // Folded source copies of the nc cells of a block (256 threads): cell c's row
 // index by rank(c), its folded coefficient h by coef(c, h); written slot by slot
 // in row order, so consecutive threads store consecutive addresses (0 in the
 // padding slots).
 template <int P, typename Rank, typename Coef>
 __device__ inline void store_copies(int nc, const LevelDev& lv, Rank rank, Coef coef) {
-  constexpr int KH = nh(P), R32 = src_row(P, 4), R64 = src_row(P, 8);
-  // coefficient of slot s of a lane-group-layout row (inverse of src_pos), or
-  // KH for a padding slot
-  auto slot_coef = [](int s, int vw) {
-    const int j = s / (4 * vw), g = (s % (4 * vw)) / vw, e = s % vw;
-    const int k = 4 * (vw * j + e) + g;
-    return k < KH ? k : KH;
-  };
+  constexpr int R32 = src_row(P, 4), R64 = src_row(P, 8);
+  static constexpr SymLayout<P, 4> l32{};
+  static constexpr SymLayout<P, 8> l64{};
   if (lv.S32)
     for (int i = threadIdx.x; i < nc * R32; i += 256) {
-      const int c = i / R32, sl = i - c * R32, h = slot_coef(sl, 4);
-      lv.S32[(size_t)rank(c) * R32 + sl] = h < KH ? (float)coef(c, h) : 0.f;
+      const int c = i / R32, sl = i - c * R32, h = l32.coef[sl];
+      lv.S32[(size_t)rank(c) * R32 + sl] = h >= 0 ? (float)coef(c, h) : 0.f;
     }
   if (lv.Sc64)
     for (int i = threadIdx.x; i < nc * R64; i += 256) {
-      const int c = i / R64, sl = i - c * R64, h = slot_coef(sl, 2);
-      lv.Sc64[(size_t)rank(c) * R64 + sl] = h < KH ? coef(c, h) : 0.0;
+      const int c = i / R64, sl = i - c * R64, h = l64.coef[sl];
+      lv.Sc64[(size_t)rank(c) * R64 + sl] = h >= 0 ? coef(c, h) : 0.0;
     }
 }
 
@@ -155,10 +152,11 @@ __device__ inline void store_copies(int nc, const LevelDev& lv, Rank rank, Coef 
 // children's ranks and masses, forms the 8 signed child sums Y of each cell in
 // LDS and sums the entries of each coefficient.
 // The coefficients then go to LDS, from where the folded source copies are
-// formed slot by slot of the lane-group layout (0 in the padding slots).  Runs
+// formed slot by slot of their layout (0 in the padding slots).  Runs
 // over a list of the level's refined ranks (those with a refined child;
 // k_p2m_leaf takes the others).
-// (at most 32, one child per thread in the loads).
+// Cells per chunk: as many as fit the block, at most 32 (one child per thread in
+// the loads).
 __host__ __device__ constexpr int upward_cells(int p) { return 256 / nmi(p) < 32 ? 256 / nmi(p) : 32; }
 
 template <int P>
@@ -269,7 +267,7 @@ __global__ __launch_bounds__(256) void k_upward(const int32_t* __restrict__ list
 // parity, a fixed weight times one such sum.  A block takes kP2mCells cells of
 // the list: their masses and the 8 signed sums go to LDS, and the three copies
 // (S64 in coefficient order, the scaled FP32 and FP64 copies in their
-// lane-group layouts) are written slot by slot in row order.
+// layouts) are written slot by slot in row order.
 constexpr int kP2mCells = 8;
 
 template <int P>
@@ -490,41 +488,32 @@ __global__ __launch_bounds__(kBlock) void k_l2l(const int32_t* __restrict__ grp,
 }
 
 // ---------------------------------------------------------------------------
-// Shared tap pipeline of the MFMA kernels.  A block owns 16 groups of one
-// parity class at one level.  For each of the 189 taps:
-//   B[k][n] = c_k 2^|k| S~_k of the tap's source of group n (monopole for a
-//             leaf source, 0 when there is none) is loaded by lane (n, g)
-//             straight into registers: its STP coefficients k = 4 kb + g are
-//             runs of the source copy (lane-group layout: 16-byte vector j of
-//             the 4 lane groups adjacent, so a load reads 64 B of each row);
+// Tap pipeline of M2L.  A block owns 16 groups of one parity class at one
+// level.  For each of the 189 taps:
+//   sB[k][n] = folded coefficient k of the tap's source of group n (its mass for
+//             a leaf source, 0 when there is none): thread (n, q) loads block q
+//             of the source row and stores its values by coefficient;
 //   sD[o][g] = D~_g at the tap's child offset o (8 rows, then one zero slot)
 //             is staged in LDS while the MFMAs of the previous tap run.
 // A fragments are read from sD through per-lane offsets that do not depend on
 // the tap (kept in registers).
 // The first k-step (monopole and dipole terms, by far the largest) and the
-// others sum into separate accumulators in M2P and in the lowest rows of M2L:
-// folded, the terms of orders >= 2 no longer come as large values of opposite
-// sign, and many are below half a unit in the last place of the running sum; in
-// one FP32 accumulator they were rounded away on one side (the potential's mean
-// error rose from 0.4e-7 to 7e-7 at p = 6).  Apart, the FP32 form's rel. L2
-// error against the FP64 form is 2.6e-7 in phi and 4.3e-7 in acc (two-level
-// 64^3, p = 6), below the 5.3e-7 and 6.0e-7 of the unfolded sums.
-// Measured: the folded products take the 8.0M-leaf p = 6 FP32 solve from 16.31
-// to 12.33 ms and the two-level one (288k leaves) from 811 to 646 us, 1289 to
-// 934 us in FP64.
+// others sum into separate accumulators in the lowest rows: folded, the terms
+// of orders >= 2 no longer come as large values of opposite sign, and many are
+// below half a unit in the last place of the running sum; in one FP32
+// accumulator they were rounded away on one side (the potential's mean error
+// rose from 0.4e-7 to 7e-7 at p = 6).
 template <typename T, int P>
 struct TapStage {
   static constexpr int K = nh(P);            // folded coefficients
   static constexpr int KP = (K + 3) & ~3;    // coefficients covered by the k-steps
   static constexpr int KS = dstage_ks(P);    // sD row stride
   static constexpr int VW = 16 / (int)sizeof(T);
-  static constexpr int STP = src_stp(P, (int)sizeof(T));  // per-lane run of the source copy
-  static constexpr int ROW = 4 * STP;        // source-copy row length
-  static constexpr int NVB = STP / VW;       // 16-byte vectors per lane and tap
+  static constexpr int ROW = src_row(P, (int)sizeof(T));  // source-copy row length
   static constexpr int SD = 8 * KS + 1;      // sD size (8 rows + zero slot)
   static constexpr int SDP = dstage_len(P, (int)sizeof(T));  // staged length (16-byte padded)
   static constexpr int NDV = SDP / VW;       // 16-byte vectors of one stage
-  static_assert(KS == dstage_ks(P), "stage stride");
+  static constexpr int SB = 16 * KP + 16;    // sB size (k-steps, then a row for the unused slots)
 };
 
 // scaled source copies c_a 2^|a| S~_a of a level
@@ -593,75 +582,6 @@ __device__ inline int tap_src(int code, int n, const int* __restrict__ sCB, gptr
   return rs >= 0 ? rs : -2 - s;
 }
 
-// B fragments of one tap for lane (n = lane & 15, g = lane >> 4): the lane's
-// run of steps (16-byte vector j holds steps VW j .. VW j + VW - 1), without a
-// branch: a missing or leaf source reads the zero row zrow after the level's
-// nref rows, and every lane loads a mass (cell 0 when the source is no leaf),
-// put into the monopole slot when the tap is used (bfrag_m0).  Only the NS
-// steps used are loaded (a partial last vector element by element): an
-// element loaded but never read would leave a register that the compiler
-// reuses while the load is still in flight.
-template <typename T, int P, int NS>
-__device__ inline void load_bfrag_nb(int sr, int zrow, gptr<double> mass1, gptr<T> S1,
-                                     typename Vec16<T>::type* vb, double& vm) {
-  using TS = TapStage<T, P>;
-  using V = typename Vec16<T>::type;
-  constexpr int NF = NS / TS::VW, R = NS % TS::VW;
-  gptr<T> src = S1 + (size_t)(sr >= 0 ? sr : zrow) * TS::ROW;
-  const int g = (threadIdx.x & 63) >> 4;
-#pragma unroll
-  for (int j = 0; j < NF; ++j) vb[j] = *(gptr<V>)(src + src_vec(j, g, (int)sizeof(T)));
-#pragma unroll
-  for (int r = 0; r < R; ++r) vb[NF][r] = src[src_vec(NF, g, (int)sizeof(T)) + r];
-  vm = mass1[sr <= -2 ? -2 - sr : 0];
-}
-template <typename T>
-__device__ inline T bfrag_m0(int sr, double vm, T b0) {
-  return (sr <= -2 && ((threadIdx.x & 63) >> 4) == 0) ? (T)vm : b0;
-}
-
-// The same run of steps loaded row by row: lane 4 r + q takes vector j of lane
-// group q of row r, so the 4 lanes of every quad read one contiguous 64-byte
-// piece of one row (one cache-line lookup per quad instead of four), and step
-// kb of column n, group g is then found in lane 4 n + g (xb_take).
-template <typename T, int P, int NS>
-__device__ inline void load_brows_xb(int rr, int zrow, gptr<T> S1, typename Vec16<T>::type* vb) {
-  using TS = TapStage<T, P>;
-  using V = typename Vec16<T>::type;
-  constexpr int NF = NS / TS::VW, R = NS % TS::VW;
-  gptr<T> src = S1 + (size_t)(rr >= 0 ? rr : zrow) * TS::ROW;
-  const int q = threadIdx.x & 3;
-#pragma unroll
-  for (int j = 0; j < NF; ++j) vb[j] = *(gptr<V>)(src + src_vec(j, q, (int)sizeof(T)));
-#pragma unroll
-  for (int r = 0; r < R; ++r) vb[NF][r] = src[src_vec(NF, q, (int)sizeof(T)) + r];
-}
-// B fragment value of this lane from the lane whose byte address is xa (the
-// cross-lane crossbar; no LDS memory is touched)
-__device__ inline float xb_take(int xa, float v) {
-  return __int_as_float(__builtin_amdgcn_ds_bpermute(xa, __float_as_int(v)));
-}
-__device__ inline double xb_take(int xa, double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_ds_bpermute(xa, (int)(b & 0xffffffffll));
-  const int hi = __builtin_amdgcn_ds_bpermute(xa, (int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-// D~ stage of tap `code` (rows already in the LDS layout): NTH threads copy
-// its NDV 16-byte vectors, thread t taking vectors t, t + NTH, ...
-template <typename T, int P, int NTH>
-__device__ inline void load_dstage(int code, const T* __restrict__ Dst, typename Vec16<T>::type* vD) {
-  using TS = TapStage<T, P>;
-  using V = typename Vec16<T>::type;
-  constexpr int NJ = (TS::NDV + NTH - 1) / NTH;
-  const int t = threadIdx.x;
-  const V* src = (const V*)(Dst + (size_t)(code >> 8) * TS::SDP);
-#pragma unroll
-  for (int j = 0; j < NJ; ++j)
-    if (TS::NDV % NTH == 0 || t + NTH * j < TS::NDV) vD[j] = src[t + NTH * j];
-}
-
 template <typename T, int P, int NTH>
 __device__ inline void store_dstage(T* sD, const typename Vec16<T>::type* vD) {
   using TS = TapStage<T, P>;
@@ -698,507 +618,425 @@ __device__ inline void tile_setup(const int32_t* __restrict__ rec, int NC, const
 
 
 // ---------------------------------------------------------------------------
-// Intermediate-field M2P at the leaves (Alg. 4 / Sec. 3.2): rows = 8 children
-// x (phi, ax, ay, az) in two 16-row tiles (the acceleration rows only need
-// multipoles of order < p), columns = 16 groups of one parity class,
-// K = multipole coefficients.  One wave per block: B comes straight from the
-// source copies into registers (the next tap's while the current tap's MFMAs
-// run), only the D~ rows go through LDS.  Output: part[F][c*8+o]
-// (accelerations already negated), in target-level units.  One launch covers
-// the tiles of every level of one precision.  One block takes one of `nsplit`
-// contiguous tap ranges of its tile and writes its own partial set
-// part[chunk][F][...], summed in order by the leaf kernel.
-// For FP32 from p = 6 on the launcher sizes the LDS source table for 2 waves
-// per SIMD (the best measured there); the same bound lets the compiler use the
-// registers of that occupancy.
-// XB (tile shape 3): the B rows are loaded row by row (load_brows_xb) and each
-// step's fragment is taken from its lane over the crossbar, which cuts the L1
-// tag lookups of the B loads by 4x; the MFMAs, operands and order are those of
-// the direct form, so the results are identical.
-template <typename T, int P, bool XB>
-constexpr int m2p_max_waves() { return sizeof(T) == 4 && P >= 6 ? (XB ? 4 : 2) : 8; }
+// Intermediate-field M2P at the leaves (Alg. 4 / Sec. 3.2), by the reflections of
+// the axes.  Reflecting an axis maps a source offset d onto another, the child
+// offsets onto each other, and D~_g onto (-1)^(g_i) D~_g; so over an orbit of
+// offsets (afmm_internal.h) the map from the sources' coefficients to the
+// children's values splits by the 8 characters chi of the reflections:
+//   U_chi[a]  = sum over the orbit's sources of chi(sigma) sigma^a S_sigma[a]
+//   V_chi,i   = sum_a A_chi,i[a] U_chi[a]      i = phi, ax, ay, az
+//   value_i(o) = tau_i sum_chi chi(tau) V_chi,i,   tau = the signs of child o
+// with A_chi,i[a] = E_(chi ^ e_i)[a + e_i], E the characters of the D~ rows.  An
+// orbit of 1, 2, 4 or 8 sources costs 8 x 4 x KH products, as much as one source
+// in the direct form: 56 orbits instead of 189 taps.
+//
+// A block takes up to 48 or 64 groups of one parity class (12 or 16 per wave) and
+// a range of the orbits.  The sources of the 7 orbits of one m sit in one octant of
+// their fathers, so the rows of that octant of all fathers of the tile (their
+// number is bounded by the tile) are staged in LDS once and read from there about
+// six times; read from memory for each use, 50 GB at 8M leaves, they held the
+// kernel at the L2's 10 TB/s.  The distinct fathers are found through a hash table
+// in LDS.
+// 4x4 blocks of MFMA: lane (q = lane >> 2, j = lane & 3) holds the coefficients of
+// block q (SymLayout) of group j of a quad; all coefficients of a block have one
+// parity, so sigma^a is one sign per lane and axis, and the sources' vectors turn
+// into the U_chi by butterflies in registers.  One MFMA takes element e of every
+// block for one chi (FP32: 16 blocks of 4 x 4 x 1, the blocks summed at the end;
+// FP64: 4 blocks of 4 x 4 x 4).  The A operand of an orbit (32 values a lane and
+// pass) comes through a ring of three steps in LDS, shared by the block, and stays
+// in registers for the wave's quads.  Output: part[F][i * 8 + o] (accelerations
+// negated), one partial set per orbit range.
+// Matrix and vector instructions of one SIMD do not overlap here (32 of each
+// interleaved take their sum), and at two waves per SIMD the butterflies, the LDS
+// reads behind them and the MFMAs share the time about evenly.  8.08M leaves
+// (128^3 + 4 levels) at p = 6 FP32: 8.7 ms summed tap by tap over all K
+// coefficients, 6.4 on the folded ones, 4.95 by orbits; 287,680 leaves FP64: 703,
+// 501, 368 us; 64^3 and 128^3 batches at p = 4 and 8 FP32: 1494 to 866, 1903 to 986.
+template <typename T> struct M2PAcc { typedef f32x4 type; };
+template <> struct M2PAcc<double> { typedef double type; };
+__device__ inline f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0); }
+__device__ inline double mfma4(double a, double b, double c) { return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0); }
 
-template <typename T, int P, bool XB>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(XB && sizeof(T) == 4 && P == 6 ? 4 : 1, m2p_max_waves<T, P, XB>()))) void k_m2p(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
-                                            const int32_t* __restrict__ taps, const int16_t* __restrict__ aoff,
-                                            const LevelDev* __restrict__ lvs, const T* __restrict__ Dst) {
-  using TS = TapStage<T, P>;
-  using V = typename Vec16<T>::type;
-  constexpr int K1 = nh(P - 1);
-  constexpr int ST0 = TS::KP / 4, ST1 = ((K1 + 3) & ~3) / 4;
-  constexpr int NV = (ST0 + TS::VW - 1) / TS::VW;
-  constexpr int ND = (TS::NDV + 63) / 64;
-  __shared__ __align__(16) T sD[2][TS::SDP];
-  __shared__ int sF[16];
-  __shared__ int sCB[16 * 27];
-  extern __shared__ int sSrcT[];  // [taps of the longest range][16], sized by the launcher
+template <typename T, int P>
+struct M2P {
+  using SL = SymLayout<P, (int)sizeof(T)>;
+  static constexpr int CP = SL::CP, NP = SL::NP, ROW = SL::ROW;
+  static constexpr int NQ = m2p_quads(P, (int)sizeof(T)), COLS = m2p_cols(P, (int)sizeof(T));
+  static constexpr int NF = m2p_fathers(P, (int)sizeof(T)), LV = m2p_vec(P, (int)sizeof(T));
+  static constexpr int AL = 8 * 64 * CP;    // A values of one orbit and pass
+  static constexpr int NH = 512;            // hash slots
+  static_assert(NF <= kBlock && 2 * NF <= NH, "one father per thread, table half full");
+  typedef typename VecN<T, CP>::type V;
+  typedef typename M2PAcc<T>::type Acc;
+  struct Hash {
+    int key[NH];
+    uint16_t slot[NH];
+  };
+  struct Lds {
+    union {
+      T rows[(NF + 1) * kSymBlocks * LV];   // the octant's rows (block q of row u at place q ^ (u & 15)), then zeros
+      Hash h;
+    };
+    T a[3][AL];                             // ring over steps (m, pass, orbit)
+    int src[2][NF];                         // sources of the octant (and of the next one): rank, or -2 - cell
+    int base[NF];                           // children of the distinct fathers
+    uint16_t tab[27 * COLS];                // row of neighbour e of column n's father, as the byte place of its block 0
+    int F[COLS];
+    int wsum[4];
+    int nf;
+  };
+  Lds& l;
+  const T* __restrict__ symA;
+  const uint64_t* __restrict__ taps;        // fathers of the class's orbits, a byte each
+  gptr<int32_t> rank1;
+  gptr<double> mass1;
+  gptr<T> S;                                // the level's source copy
+  int zrow, nf, C, par;
+  int g0, g1;                               // steps (m, pass, j) of this block: [g0, g1) of 56 NP
+  int af;                                   // axes on which the operand being loaded has its far offset on the other side
+  int ra, wa;                               // ring places: operand of the next step, of the one after
+  T sg[3];                                  // sigma^a sign of this lane's block on each axis
+  Acc acc[NQ][8];
+  V a[8], an[2];
+
+  static constexpr int axis(int pt, int b) {  // b-th axis of the set
+    int i = 0;
+    for (; i < 3; ++i)
+      if (pt >> i & 1 && b-- == 0) break;
+    return i;
+  }
+  static constexpr int sub(int pt, int chi) {  // chi restricted to the set, as an index over its axes
+    int r = 0, b = 0;
+    for (int i = 0; i < 3; ++i)
+      if (pt >> i & 1) r |= (chi >> i & 1) << b++;
+    return r;
+  }
+  // The lane, opaque: the addresses that follow from it are formed where they are
+  // used; hoisted out of the step loop, dozens of them went to scratch, and their
+  // reloads waited for every load in flight.
+  static __device__ inline int lane_id() {
+    int x = threadIdx.x & 63;
+    asm volatile("" : "+v"(x));
+    return x;
+  }
+  static __device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6); }
+
+  // byte place in LDS of block q of row u; block q of the row at place p is at p ^ place(0, q)
+  static constexpr int VB = LV * (int)sizeof(T);
+  static_assert((NF + 1) * kSymBlocks * VB <= 65536, "places fit 16 bits");
+  static __device__ inline int place(int u, int q) { return (u * kSymBlocks + (q ^ (u & 15))) * VB; }
+
+  // The distinct refined fathers among the neighbours of the columns' fathers:
+  // every (column, neighbour) enters its rank into the table, the occupied slots
+  // are numbered, and tab takes the numbers (NF, the zero row, for none).
+  __device__ inline void find_fathers(gptr<int32_t> refcell1, gptr<int32_t> nbr2, gptr<int32_t> rank2) {
+    const int t = threadIdx.x;
+    constexpr int NE = (27 * COLS + kBlock - 1) / kBlock;
+    int key[NE], at[NE];
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      const int i = t + kBlock * k, e = i / COLS, F = i < 27 * COLS ? l.F[i - e * COLS] : -1;
+      const int Q = F >= 0 ? nbr2[(size_t)(refcell1[F] >> 3) * 27 + e] : -1;
+      key[k] = Q >= 0 ? rank2[Q] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      at[k] = -1;
+      if (key[k] < 0) continue;
+      uint32_t h = ((uint32_t)key[k] * 2654435761u) >> 23;  // top 9 bits
+      for (int tries = 0; tries < NH; ++tries, h = (h + 1) & (NH - 1)) {
+        const int old = atomicCAS(&l.h.key[h], -1, key[k]);
+        if (old == -1 || old == key[k]) {
+          at[k] = (int)h;
+          break;
+        }
+      }
+    }
+    __syncthreads();
+    const int k0 = l.h.key[2 * t], k1 = l.h.key[2 * t + 1], lane = t & 63;
+    const uint64_t m0 = __ballot(k0 >= 0), m1 = __ballot(k1 >= 0), below = (1ull << lane) - 1ull;
+    if (lane == 0) l.wsum[t >> 6] = __popcll(m0) + __popcll(m1);
+    __syncthreads();
+    int b = __popcll(m0 & below) + __popcll(m1 & below);
+    for (int v = 0; v < (t >> 6); ++v) b += l.wsum[v];
+    if (k0 >= 0 && b < NF) {
+      l.h.slot[2 * t] = (uint16_t)b;
+      l.base[b++] = 8 * k0;
+    }
+    if (k1 >= 0 && b < NF) {
+      l.h.slot[2 * t + 1] = (uint16_t)b;
+      l.base[b++] = 8 * k1;
+    }
+    if (t == kBlock - 1) l.nf = min(b, NF);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NE; ++k)
+      if (t + kBlock * k < 27 * COLS) l.tab[t + kBlock * k] = (uint16_t)place(at[k] >= 0 ? l.h.slot[at[k]] : NF, 0);
+    __syncthreads();
+  }
+
+  // source of father t in the octant of m
+  __device__ inline int source_cell(int m) const {
+    return (int)threadIdx.x < nf ? l.base[threadIdx.x] + (C ^ m) : 0;
+  }
+  __device__ inline void put_source(int m, int cell, int rk) {
+    if ((int)threadIdx.x < nf) l.src[m & 1][threadIdx.x] = rk >= 0 ? rk : -2 - cell;
+  }
+  // rows of the octant of m, pass s; on the last pass, the sources of m + 1
+  __device__ inline void stage(int m, int s) {
+    const int t = threadIdx.x, q = t & 15;
+    const int cell = source_cell(min(m + 1, 7));
+    const int rk = rank1[cell];
+    constexpr int U = 4;
+    for (int u0 = t >> 4; u0 < nf; u0 += 16 * U) {
+      V v[U];
+      double mm[U];
+      int code[U];
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int u = min(u0 + 16 * k, nf - 1);
+        code[k] = l.src[m & 1][u];
+        v[k] = load_vec<T, CP>(S + (size_t)(code[k] >= 0 ? code[k] : zrow) * ROW + (s * kSymBlocks + q) * CP);
+        mm[k] = mass1[code[k] <= -2 ? -2 - code[k] : 0];
+      }
+#pragma unroll
+      for (int k = 0; k < U; ++k) {
+        const int u = min(u0 + 16 * k, nf - 1);
+        if (s == 0 && q == 0 && code[k] <= -2) v[k][0] = (T)mm[k];  // a leaf: its mass
+        store_vec<T, CP>((T*)((char*)l.rows + place(u, q)), v[k]);
+      }
+    }
+    if (s == NP - 1 && m + 1 < 8) put_source(m + 1, cell, rk);
+    __syncthreads();
+  }
+  // the block's share of the A operand of step g (the last one past the end):
+  // characters wave, wave + 4; put into the ring with the sign of this class: the
+  // operator's representative offsets are positive, mirrored on the axes on which
+  // the class has its far offset on the other side
+  __device__ inline void load_a(int g) {
+    const int lane = lane_id(), wv = wave_id();
+    g = min(g, g1 - 1);
+    const int ms = g / 7, m = ms / NP;
+    af = C & m & ~sym_axes(sym_set(m, g - 7 * ms));
+    gptr<T> src = as_global(symA + ((size_t)g * AL + wv * 64 * CP)) + lane * CP;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) an[r] = load_vec<T, CP>(src + 4 * 64 * CP * r);
+  }
+  __device__ inline void put_a(int place) {
+    const int lane = lane_id(), wv = wave_id();
+    if (af) {
+#pragma unroll
+      for (int r = 0; r < 2; ++r) an[r] *= __popc((par ^ (wv + 4 * r)) & af) & 1 ? (T)-1 : (T)1;
+    }
+    T* ring = l.a[place] + (wv * 64 + lane) * CP;
+#pragma unroll
+    for (int r = 0; r < 2; ++r) store_vec<T, CP>(ring + 4 * 64 * CP * r, an[r]);
+  }
+  __device__ inline void read_a(int c, int lane, int place) {
+    a[c] = load_vec<T, CP>((const T*)l.a[place] + (c * 64 + lane) * CP);
+  }
+  template <int PT>
+  __device__ inline void transform(V* v) const {
+    constexpr int NB = sym_bits(PT);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const T s = sg[axis(PT, b)];
+#pragma unroll
+      for (int i = 0; i < 1 << NB; ++i)
+        if (!(i >> b & 1)) {
+          const V p = v[i], m = v[i | 1 << b];
+#pragma unroll
+          for (int e = 0; e < CP; ++e) {
+            v[i][e] = p[e] + s * m[e];
+            v[i | 1 << b][e] = p[e] - s * m[e];
+          }
+        }
+    }
+  }
+  // one orbit and pass, its sources' fathers in code: the wave's quads
+  template <int PT>
+  __device__ inline void orbit(uint64_t code) {
+    constexpr int NS = 1 << sym_bits(PT);
+    const int lane = lane_id(), wv = wave_id(), q = lane >> 2, j = lane & 3;
+    int off[NS];
+#pragma unroll
+    for (int i = 0; i < NS; ++i) off[i] = (int)(code >> (8 * i) & 31) * COLS;
+    const uint16_t* tab = l.tab + wv * NQ * 4 + j;
+    auto read_rows = [&](int qd, V* v) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i) v[i] = load_vec<T, CP>((const T*)((const char*)l.rows + (tab[off[i] + 4 * qd] ^ q * VB)));
+    };
+    V v[2][NS];
+    read_rows(0, v[0]);
+#pragma unroll
+    for (int qd = 0; qd < NQ; ++qd) {
+      if (qd + 1 < NQ) read_rows(qd + 1, v[(qd + 1) & 1]);
+      transform<PT>(v[qd & 1]);
+      // butterflies and products apart: these MFMAs and the VALU share the units,
+      // and every change between them costs some cycles (32 of each: 541 cycles
+      // interleaved, 421 one after the other, two waves)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int e = 0; e < CP; ++e)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[qd][c] = mfma4(a[c][e], v[qd & 1][sub(PT, c)][e], acc[qd][c]);
+      if (qd == NQ - 1)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) read_a(c, lane, ra);
+      __builtin_amdgcn_sched_barrier(0);  // one quad's reads ahead, no more (registers)
+    }
+  }
+  __device__ inline uint64_t sources_of(int g) const {
+    g = min(g, g1 - 1);
+    return taps[g / (7 * NP) * 7 + g % 7];
+  }
+  // the steps of one phase, h the step of the TY-th set: one after the other
+  // (behind a switch the accumulators were copied)
+  template <int TY>
+  __device__ inline void sets(int m, int h, int& g, uint64_t& code) {
+    const bool on = sym_axes(TY) != m;
+    if (on && h == g && g < g1) {
+      const uint64_t c = code;
+      code = sources_of(g + 1);
+      put_a(wa);
+      load_a(g + 3);
+      orbit<sym_axes(TY)>(c);
+      const int x = 3 - ra - wa;  // the place of the operand just used
+      ra = wa;
+      wa = x;
+      ++g;
+      __syncthreads();
+    }
+    if constexpr (TY < 7) sets<TY + 1>(m, on ? h + 1 : h, g, code);
+  }
+  __device__ inline void run() {
+    int g = g0;
+    uint64_t code = sources_of(g);
+    while (g < g1) {
+      const int ms = g / 7, m = ms / NP;
+      stage(m, ms - m * NP);
+      sets<0>(m, 7 * ms, g, code);
+    }
+  }
+};
+
+template <typename T, int P>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
+void k_m2p(const int32_t* __restrict__ tiles, int ntiles, int nsplit, const int8_t* __restrict__ taps,
+           const LevelDev* __restrict__ lvs, const T* __restrict__ symA) {
+  using MP = M2P<T, P>;
+  using SL = typename MP::SL;
+  static constexpr SL sl{};
+  __shared__ __align__(16) typename MP::Lds lds;
   const int item = xcd_tile(ntiles * nsplit);
   if (item >= ntiles * nsplit) return;
   const int tile = item / nsplit, chunk = item - tile * nsplit;
-  int tb, te;
-  tap_range(chunk, nsplit, tb, te);
-  const int lane = threadIdx.x;
-  const int n = lane & 15;
-  const int32_t* rec = tiles + (size_t)tile * 17;
-  const int l = rec[0];
-  const LevelDev lv1 = lvs[l - 1];
-  const LevelDev lv2 = lvs[l - 2];
-  gptr<int32_t> rank1 = as_global(lv1.rank);
-  gptr<double> mass1 = as_global(lv1.mass);
-  gptr<T> S1 = as_global(level_S<T>(lv1));
-  gmut<T> part = as_global_mut((T*)lv1.part) + (size_t)chunk * lv1.nref * 32;
-  if (lane < 16) sF[lane] = rec[1 + lane];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, q = lane >> 2, j = lane & 3;
+  const int32_t* rec = tiles + (size_t)tile * (MP::COLS + 1);
+  const LevelDev lv1 = lvs[rec[0] - 1];
+  const LevelDev lv2 = lvs[rec[0] - 2];
+  if (t < MP::COLS) lds.F[t] = rec[1 + t];
+  lds.h.key[t] = lds.h.key[t + kBlock] = -1;
+  static_assert(MP::NH == 2 * kBlock, "two hash slots per thread");
   __syncthreads();
   gptr<int32_t> refcell1 = as_global(lv1.refcell);
-  gptr<int32_t> nbr2 = as_global(lv2.nbr);
-  gptr<int32_t> rank2 = as_global(lv2.rank);
-  for (int i = lane; i < 16 * 27; i += 64) {
-    const int c = i / 27, e = i - c * 27;
-    const int F = sF[c];
-    int v = -1;
-    if (F >= 0) {
-      const int Q = nbr2[(size_t)(refcell1[F] >> 3) * 27 + e];
-      if (Q >= 0) {
-        const int rQ = rank2[Q];
-        if (rQ >= 0) v = 8 * rQ;
-      }
-    }
-    sCB[i] = v;
+  MP m{lds, symA};
+  m.C = __builtin_amdgcn_readfirstlane(refcell1[lds.F[0]] & 7);
+  m.taps = (const uint64_t*)taps + m.C * kSymOrbits;
+  m.g0 = chunk * (kSymOrbits * MP::NP) / nsplit;
+  m.g1 = (chunk + 1) * (kSymOrbits * MP::NP) / nsplit;
+  m.S = as_global(level_S<T>(lv1));
+  m.rank1 = as_global(lv1.rank);
+  m.mass1 = as_global(lv1.mass);
+  m.zrow = lv1.nref;
+  m.par = sl.par[q];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) m.sg[i] = m.par >> i & 1 ? (T)-1 : (T)1;
+#pragma unroll
+  for (int d = 0; d < MP::NQ; ++d)
+#pragma unroll
+    for (int c = 0; c < 8; ++c) m.acc[d][c] = typename MP::Acc{};
+  m.find_fathers(refcell1, as_global(lv2.nbr), as_global(lv2.rank));
+  m.nf = lds.nf;
+  // the A operand of the first two steps into the ring, the third on its way; the
+  // first octant's sources; the zero row
+  {
+    const int mf = m.g0 / (7 * MP::NP), cell = m.source_cell(mf);
+    m.put_source(mf, cell, m.rank1[cell]);
   }
-  const int oF = refcell1[sF[0]] & 7;
-  const int32_t* tpg = taps + oF * kTaps + tb;
-  int off0[ST0], off1[ST1];
-#pragma unroll
-  for (int kb = 0; kb < ST0; ++kb) off0[kb] = aoff[kb * 64 + lane];
-#pragma unroll
-  for (int kb = 0; kb < ST1; ++kb) off1[kb] = aoff[(ST0 + kb) * 64 + lane];
+  if (t < kSymBlocks * MP::LV) lds.rows[MP::NF * kSymBlocks * MP::LV + t] = 0;
+  m.load_a(m.g0);
+  m.put_a(0);
+  m.load_a(m.g0 + 1);
+  m.put_a(1);
+  m.load_a(m.g0 + 2);
+  m.ra = 1;
+  m.wa = 2;
   __syncthreads();
-  // sources of every tap of the range
-  const int nt = te - tb;
-  const int32_t* tp = tpg;
-  if constexpr (!XB) {
-    for (int i = lane; i < nt * 16; i += 64) sSrcT[i] = tap_src(tp[i >> 4], i & 15, sCB, rank1);
-    __syncthreads();
-  }
-  const int zrow = lv1.nref;
-  V vD[ND];
-  typename Acc4<T>::type acc0 = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0}, hi0 = {0, 0, 0, 0}, hi1 = {0, 0, 0, 0};
-  // Taps run in pairs; an odd range ends with one empty tap (no source, so B
-  // is zero; the D~ stage repeats the last tap's finite rows), so that both
-  // halves of a pair and every load run unconditionally.
-  const int nt2 = (nt + 1) & ~1;
-  if constexpr (XB && P >= 6) {
-    // One set of source rows in flight (tap k + 1, loaded row by row) and one
-    // set of fragments in use (tap k): after tap k's MFMAs the rows of tap
-    // k + 1, loaded a whole tap earlier, pass over the crossbar into the
-    // fragments, so no MFMA waits on the crossbar.  No source table: each
-    // lane resolves the two sources it needs (column xrow for its row loads,
-    // column n for the monopole slot) two taps ahead, the rank lookup being
-    // a load that lands while a tap runs; the block's LDS is then small
-    // enough for 4 waves per SIMD.
-    const int xrow = lane >> 2, xa = 4 * (4 * n + (lane >> 4));
-    V braw[NV];
-    T frag[ST0];
-    auto cell_of = [&](int code, int col) {
-      const int cb = sCB[col * 27 + (code & 31)];
-      return cb < 0 ? -1 : cb + ((code >> 5) & 7);
-    };
-    // source code of a column (as tap_src) from its cell and rank, or -1
-    // past the range
-    auto fin = [](bool valid, int c, int rk) { return !valid || c < 0 ? -1 : (rk >= 0 ? rk : -2 - c); };
-    // tap k + 1: cells and rank loads in flight; tap k + 2 likewise
-    int cR1, cC1, kR1, kC1, cR2, cC2, kR2, kC2;
-    auto resolve = [&](int k, int& cR, int& cC, int& kR, int& kC) {
-      const int code = tp[k < nt ? k : nt - 1];
-      cR = cell_of(code, xrow);
-      cC = cell_of(code, n);
-      kR = rank1[cR >= 0 ? cR : 0];
-      kC = rank1[cC >= 0 ? cC : 0];
-    };
-    auto load_rows = [&](int srow, int scol, double& vm) {
-      load_brows_xb<T, P, ST0>(srow, zrow, S1, braw);
-      vm = mass1[scol <= -2 ? -2 - scol : 0];  // unconditional (a select on it would wait)
-    };
-    auto take = [&](int sr, double vm) {
 #pragma unroll
-      for (int kb = 0; kb < ST0; ++kb) frag[kb] = xb_take(xa, braw[kb / TS::VW][kb % TS::VW]);
-      frag[0] = bfrag_m0<T>(sr, vm, frag[0]);
-    };
-    {
-      int cR0, cC0, kR0, kC0;
-      resolve(0, cR0, cC0, kR0, kC0);
-      const int sc0 = fin(true, cC0, kC0);
-      double vm0;
-      load_rows(fin(true, cR0, kR0), sc0, vm0);
-      load_dstage<T, P, 64>(tp[0], Dst, vD);
-      resolve(1, cR1, cC1, kR1, kC1);
-      store_dstage<T, P, 64>(sD[0], vD);
-      take(sc0, vm0);
-    }
-    __syncthreads();
-    auto step = [&](int k, int b) {
-      const bool v1 = k + 1 < nt;
-      const int srn = fin(v1, cC1, kC1);
-      const int srr = fin(v1, cR1, kR1);
-      load_dstage<T, P, 64>(tp[v1 ? k + 1 : nt - 1], Dst, vD);
-      double vmn;
-      load_rows(srr, srn, vmn);
-      resolve(k + 2, cR2, cC2, kR2, kC2);
-      __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the MFMAs
-      const T* D = sD[b];
-#pragma unroll
-      for (int kb = 0; kb < ST0; ++kb) {
-        auto& s0 = kb == 0 ? acc0 : hi0;
-        auto& s1 = kb == 0 ? acc1 : hi1;
-        s0 = mfma16(D[off0[kb]], frag[kb], s0);
-        if (kb < ST1) s1 = mfma16(D[off1[kb]], frag[kb], s1);
-      }
-      __builtin_amdgcn_sched_barrier(0);  // the next fragments after the MFMAs
-      take(srn, vmn);
-      store_dstage<T, P, 64>(sD[b ^ 1], vD);
-      cR1 = cR2, cC1 = cC2, kR1 = kR2, kC1 = kC2;
-      __syncthreads();
-    };
-    for (int k = 0; k < nt2; k += 2) {
-      step(k, 0);
-      step(k + 1, 1);
-    }
-  } else if constexpr (XB) {
-    // Short taps (p <= 5): the same crossbar form with source rows and D~
-    // stages loaded two taps ahead (set k & 1 holds tap k's) and the sources
-    // resolved three taps ahead, so that a load has two taps of MFMAs to land.
-    const int xrow = lane >> 2, xa = 4 * (4 * n + (lane >> 4));
-    V braw[2][NV];
-    V vD2[2][ND];
-    T frag[ST0];
-    double vm[2];
-    int sc[2];
-    auto cell_of = [&](int code, int col) {
-      const int cb = sCB[col * 27 + (code & 31)];
-      return cb < 0 ? -1 : cb + ((code >> 5) & 7);
-    };
-    auto fin = [](bool valid, int c, int rk) { return !valid || c < 0 ? -1 : (rk >= 0 ? rk : -2 - c); };
-    int cR, cC, kR, kC;  // the next tap to load: cells and rank loads in flight
-    auto resolve = [&](int k) {
-      const int code = tp[k < nt ? k : nt - 1];
-      cR = cell_of(code, xrow);
-      cC = cell_of(code, n);
-      kR = rank1[cR >= 0 ? cR : 0];
-      kC = rank1[cC >= 0 ? cC : 0];
-    };
-    // tap k into set q (sources from the pending resolution), then resolve k + 1
-    auto prefetch = [&](int k, int q) {
-      const bool v = k < nt;
-      const int srr = fin(v, cR, kR);
-      sc[q] = fin(v, cC, kC);
-      load_dstage<T, P, 64>(tp[v ? k : nt - 1], Dst, vD2[q]);
-      load_brows_xb<T, P, ST0>(srr, zrow, S1, braw[q]);
-      vm[q] = mass1[sc[q] <= -2 ? -2 - sc[q] : 0];  // unconditional (a select on it would wait)
-      resolve(k + 1);
-    };
-    auto take = [&](int q) {
-#pragma unroll
-      for (int kb = 0; kb < ST0; ++kb) frag[kb] = xb_take(xa, braw[q][kb / TS::VW][kb % TS::VW]);
-      frag[0] = bfrag_m0<T>(sc[q], vm[q], frag[0]);
-    };
-    resolve(0);
-    prefetch(0, 0);
-    prefetch(1, 1);
-    store_dstage<T, P, 64>(sD[0], vD2[0]);
-    take(0);
-    __syncthreads();
-    // tap k (stage sD[b], set b): prefetch tap k + 2 into set b, MFMAs of tap
-    // k, then tap k + 1 (set b ^ 1) into the fragments and the other stage
-    auto step = [&](int k, int b) {
-      prefetch(k + 2, b);
-      __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the MFMAs
-      const T* D = sD[b];
-#pragma unroll
-      for (int kb = 0; kb < ST0; ++kb) {
-        auto& s0 = kb == 0 ? acc0 : hi0;
-        auto& s1 = kb == 0 ? acc1 : hi1;
-        s0 = mfma16(D[off0[kb]], frag[kb], s0);
-        if (kb < ST1) s1 = mfma16(D[off1[kb]], frag[kb], s1);
-      }
-      __builtin_amdgcn_sched_barrier(0);  // the next fragments after the MFMAs
-      take(b ^ 1);
-      store_dstage<T, P, 64>(sD[b ^ 1], vD2[b ^ 1]);
-      __syncthreads();
-    };
-    for (int k = 0; k < nt2; k += 2) {
-      step(k, 0);
-      step(k + 1, 1);
-    }
-  } else {
-    V bA[NV], bB[NV];
-    double vmA = 0, vmB = 0;
-    int srA = sSrcT[n], srB = -1;
-    load_bfrag_nb<T, P, ST0>(srA, zrow, mass1, S1, bA, vmA);
-    load_dstage<T, P, 64>(tp[0], Dst, vD);
-    store_dstage<T, P, 64>(sD[0], vD);
-    __syncthreads();
-    // one tap: prefetch tap k + 1 (D~ rows into vD, B into bn), MFMAs of tap k
-    // from bc and the LDS stage sD[b]
-    auto step = [&](int k, int b, const V* bc, int src, double vmc, V* bn, int& srn, double& vmn) {
-      const int k1 = k + 1 < nt ? k + 1 : nt - 1;
-      load_dstage<T, P, 64>(tp[k1], Dst, vD);
-      srn = k + 1 < nt ? sSrcT[k1 * 16 + n] : -1;
-      load_bfrag_nb<T, P, ST0>(srn, zrow, mass1, S1, bn, vmn);
-      __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the MFMAs
-      const T* D = sD[b];
-#pragma unroll
-      for (int kb = 0; kb < ST0; ++kb) {
-        const T bv = kb == 0 ? bfrag_m0<T>(src, vmc, bc[0][0]) : bc[kb / TS::VW][kb % TS::VW];
-        auto& s0 = kb == 0 ? acc0 : hi0;
-        auto& s1 = kb == 0 ? acc1 : hi1;
-        s0 = mfma16(D[off0[kb]], bv, s0);
-        if (kb < ST1) s1 = mfma16(D[off1[kb]], bv, s1);
-      }
-      store_dstage<T, P, 64>(sD[b ^ 1], vD);
-      __syncthreads();
-    };
-    for (int k = 0; k < nt2; k += 2) {
-      step(k, 0, bA, srA, vmA, bB, srB, vmB);
-      step(k + 1, 1, bB, srB, vmB, bA, srA, vmA);
-    }
-  }
-  acc0 += hi0;
-  acc1 += hi1;
-  const int F = sF[n];
-  if (F >= 0) {
-    gmut<T> out = part + (size_t)F * 32;
-    const int krow = lane >> 4;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = acc_row<T>(krow, r);
-      out[i] = i < 8 ? acc0[r] : -acc0[r];
-      out[16 + i] = -acc1[r];
-    }
-  }
-}
-
-// M2P with the source rows staged through LDS, for NT 16-column tiles per wave
-// (tile shapes 1 and 2 of the launcher; the kernel above is shape 0).  In the
-// direct form each lane's B fragments come from one of 16 source rows, so a
-// 16-byte load of the wave touches 64 cache lines and the texture addresser
-// and L1 tag lookups bound the kernel when a tap carries few MFMAs (low p).
-// Here consecutive lanes load consecutive 16-byte pieces of a row (piece
-// v = 64 j + lane is piece v % NVR of row v / NVR of the tap's 16 NT rows),
-// two taps ahead; halfway through a tap's MFMAs the rows of the next tap go
-// to an LDS row stage (padded by one vector per row: conflict-free fragment
-// reads) and come back as MFMA fragments.  With NT = 2 one wave runs two
-// tiles of the same parity class: each A fragment read from LDS feeds two
-// MFMAs and one D~ stage serves 32 groups.  The block is one wave, whose LDS
-// accesses complete in issue order, so the stages need no barrier.  The
-// sources are resolved in chunks of CH taps; the code and sources of a tap
-// are read from LDS one step before the loads that use them.
-template <int NT>
-constexpr int m2p_chunk() { return NT == 1 ? 64 : 32; }
-
-template <typename T, int P, int NT>
-__global__ __launch_bounds__(64) void k_m2p_s(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
-                                              const int32_t* __restrict__ taps, const int16_t* __restrict__ aoff,
-                                              const LevelDev* __restrict__ lvs, const T* __restrict__ Dst) {
-  using TS = TapStage<T, P>;
-  using V = typename Vec16<T>::type;
-  constexpr int K1 = nh(P - 1);
-  constexpr int ST0 = TS::KP / 4, ST1 = ((K1 + 3) & ~3) / 4;
-  constexpr int NV = (ST0 + TS::VW - 1) / TS::VW;  // B vectors per lane and tile (MFMA layout)
-  constexpr int ND = (TS::NDV + 63) / 64;
-  constexpr int NC = 16 * NT;                      // groups (columns) of the block
-  constexpr int NVR = TS::ROW / TS::VW;             // 16-byte pieces of a source row
-  constexpr int RP = TS::ROW + TS::VW;              // LDS row stride
-  constexpr int NG = (NC * NVR + 63) / 64;          // row pieces per lane and tap
-  constexpr int CH = m2p_chunk<NT>();
-  constexpr int KMID = ST0 / 2;
-  static_assert(4 * NV <= NVR, "fragments inside the row");
-  __shared__ __align__(16) T sD[2][TS::SDP];
-  __shared__ __align__(16) T sB[NC * RP];
-  __shared__ int sF[NC];
-  __shared__ int sCB[NC * 27];
-  __shared__ int sCode[kTaps];
-  __shared__ int sSrc[CH * NC];
-  const int item = xcd_tile(ntiles * nsplit);
-  if (item >= ntiles * nsplit) return;
-  const int tile = item / nsplit, chunk = item - tile * nsplit;
-  int tb, te;
-  tap_range(chunk, nsplit, tb, te);
-  const int lane = threadIdx.x;
-  const int n = lane & 15, g = lane >> 4;
-  const int32_t* rec = tiles + (size_t)tile * (NC + 1);
-  const int l = rec[0];
-  const LevelDev lv1 = lvs[l - 1];
-  const LevelDev lv2 = lvs[l - 2];
-  gptr<int32_t> rank1 = as_global(lv1.rank);
-  gptr<double> mass1 = as_global(lv1.mass);
-  gptr<T> S1 = as_global(level_S<T>(lv1));
+  for (int c = 0; c < 8; ++c) m.read_a(c, lane, 0);
+  m.run();
+  // characters -> children (index y = ~o), in registers; then the sum over the
+  // blocks of coefficients: halves exchanged until each lane holds two values
   gmut<T> part = as_global_mut((T*)lv1.part) + (size_t)chunk * lv1.nref * 32;
-  if (lane < NC) sF[lane] = rec[1 + lane];
-  __syncthreads();
-  gptr<int32_t> refcell1 = as_global(lv1.refcell);
-  gptr<int32_t> nbr2 = as_global(lv2.nbr);
-  gptr<int32_t> rank2 = as_global(lv2.rank);
-  for (int i = lane; i < NC * 27; i += 64) {
-    const int c = i / 27, e = i - c * 27;
-    const int F = sF[c];
-    int v = -1;
-    if (F >= 0) {
-      const int Q = nbr2[(size_t)(refcell1[F] >> 3) * 27 + e];
-      if (Q >= 0) {
-        const int rQ = rank2[Q];
-        if (rQ >= 0) v = 8 * rQ;
-      }
-    }
-    sCB[i] = v;
-  }
-  const int oF = refcell1[sF[0]] & 7;
-  const int32_t* tpg = taps + oF * kTaps + tb;
-  const int nt = te - tb;
-  for (int i = lane; i < nt; i += 64) sCode[i] = tpg[i];
-  int off0[ST0], off1[ST1];
 #pragma unroll
-  for (int kb = 0; kb < ST0; ++kb) off0[kb] = aoff[kb * 64 + lane];
+  for (int d = 0; d < MP::NQ; ++d) {
 #pragma unroll
-  for (int kb = 0; kb < ST1; ++kb) off1[kb] = aoff[(ST0 + kb) * 64 + lane];
-  const int zrow = lv1.nref;
-  // the row (0 .. NC-1) and piece of each of this lane's row pieces; pieces
-  // past the last row re-read the last piece and are not stored
-  int prow[NG], pchk[NG];
+    for (int bit = 1; bit < 8; bit <<= 1)
 #pragma unroll
-  for (int j = 0; j < NG; ++j) {
-    const int v = min(64 * j + lane, NC * NVR - 1);
-    prow[j] = v / NVR;
-    pchk[j] = v - prow[j] * NVR;
-  }
-  typename Acc4<T>::type acc0[NT], acc1[NT], hi0[NT], hi1[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) acc0[t] = acc1[t] = hi0[t] = hi1[t] = {0, 0, 0, 0};
-  // fragments (per tile) of the current and the next tap, row pieces of the
-  // next two taps, and each tile's column source and mass for the monopole slot
-  V bA[NT][NV], bB[NT][NV];
-  V gX[NG], gY[NG];
-  V vD[ND];
-  double vmA[NT], vmB[NT], vmX[NT], vmY[NT];
-  int srA[NT], srB[NT], srX[NT], srY[NT];
-  int cN = 0, sN[NT], rN[NG];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) vmA[t] = vmB[t] = vmX[t] = vmY[t] = 0, srA[t] = srB[t] = srX[t] = srY[t] = sN[t] = -1;
-  auto load_rows = [&](const int* rs, V* gb) {
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {
-      const int row = rs[j] >= 0 ? rs[j] : zrow;
-      gb[j] = *(gptr<V>)(S1 + (size_t)row * TS::ROW + pchk[j] * TS::VW);
-    }
-  };
-  auto store_rows = [&](const V* gb) {
-#pragma unroll
-    for (int j = 0; j < NG; ++j)
-      if (64 * j + lane < NC * NVR) *(V*)(sB + prow[j] * RP + pchk[j] * TS::VW) = gb[j];
-  };
-  auto read_frags = [&](V (*b)[NV]) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int j = 0; j < NV; ++j) b[t][j] = *(const V*)(sB + (16 * t + n) * RP + (4 * j + g) * TS::VW);
-  };
-  // the mass of a leaf source for lane group 0 (the only lanes that use it)
-  auto load_mass = [&](const int* sr, double* vm) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      double v = 0;
-      if (g == 0 && sr[t] <= -2) v = mass1[-2 - sr[t]];
-      vm[t] = v;
-    }
-  };
-  // sources of chunk tap k (none past the chunk): columns of this lane, rows of its pieces
-  auto read_srcs = [&](int k, int cn) {
-#pragma unroll
-    for (int t = 0; t < NT; ++t) sN[t] = k < cn ? sSrc[k * NC + 16 * t + n] : -1;
-#pragma unroll
-    for (int j = 0; j < NG; ++j) rN[j] = k < cn ? sSrc[k * NC + prow[j]] : -1;
-  };
-  for (int c0 = 0; c0 < nt; c0 += CH) {
-    const int cn = min(CH, nt - c0);
-    __syncthreads();
-    for (int i = lane; i < cn * NC; i += 64) sSrc[i] = tap_src(sCode[c0 + i / NC], i % NC, sCB, rank1);
-    __syncthreads();
-    {
-      // tap 0 into the stages and bA; tap 1's rows in flight (set X); tap 2's sources read
-      read_srcs(0, cn);
-      load_rows(rN, gY);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) srA[t] = sN[t];
-      load_mass(srA, vmA);
-      load_dstage<T, P, 64>(sCode[c0], Dst, vD);
-      store_dstage<T, P, 64>(sD[0], vD);
-      store_rows(gY);
-      read_frags(bA);
-      read_srcs(1, cn);
-      load_rows(rN, gX);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) srX[t] = sN[t];
-      load_mass(srX, vmX);
-      cN = sCode[c0 + (cn > 1 ? 1 : 0)];
-      read_srcs(2, cn);
-    }
-    __builtin_amdgcn_wave_barrier();
-    // step k: rows of tap k + 2 into gn (sources read one step ago) and the D~
-    // stage of tap k + 1 into vD; the MFMAs of tap k, halfway through them the
-    // rows of tap k + 1 (gc) through the LDS row stage into bn; then the D~
-    // stage of tap k + 1 into LDS.  Taps run in pairs; an odd chunk ends with
-    // one empty tap (zero rows; its D~ stage repeats the last tap's rows).
-    auto step = [&](int k, int b, V (*bc)[NV], const int* srcc, const double* vmc, V (*bn)[NV], int* srn,
-                    double* vmn, const V* gc, const int* src1, const double* vm1, V* gn, int* sr2, double* vm2) {
-      load_dstage<T, P, 64>(cN, Dst, vD);
-      load_rows(rN, gn);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) sr2[t] = sN[t];
-      load_mass(sr2, vm2);
-      cN = sCode[c0 + (k + 2 < cn ? k + 2 : cn - 1)];
-      read_srcs(k + 3, cn);
-      __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the MFMAs
-      const T* D = sD[b];
-#pragma unroll
-      for (int kb = 0; kb < ST0; ++kb) {
-        const T a0 = D[off0[kb]];
-        const T a1 = kb < ST1 ? D[off1[kb]] : (T)0;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const T bv = kb == 0 ? bfrag_m0<T>(srcc[t], vmc[t], bc[t][0][0]) : bc[t][kb / TS::VW][kb % TS::VW];
-          auto& s0 = kb == 0 ? acc0[t] : hi0[t];
-          auto& s1 = kb == 0 ? acc1[t] : hi1[t];
-          s0 = mfma16(a0, bv, s0);
-          if (kb < ST1) s1 = mfma16(a1, bv, s1);
+      for (int c = 0; c < 8; ++c)
+        if (!(c & bit)) {
+          const auto x = m.acc[d][c], y = m.acc[d][c | bit];
+          m.acc[d][c] = x + y;
+          m.acc[d][c | bit] = x - y;
         }
-        if (kb == KMID) {
-          store_rows(gc);
-          read_frags(bn);
+    const int F = lds.F[(wv * MP::NQ + d) * 4 + j];
+    if constexpr (sizeof(T) == 4) {
+      T v[32];  // i * 8 + o
 #pragma unroll
-          for (int t = 0; t < NT; ++t) srn[t] = src1[t], vmn[t] = vm1[t];
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+          const T x = m.acc[d][7 - o][i];
+          v[i * 8 + o] = i > 0 && (o >> (i > 0 ? i - 1 : 0) & 1) ? -x : x;
+        }
+#pragma unroll
+      for (int n = 16, lb = 32; n >= 2; n >>= 1, lb >>= 1) {
+        const bool up = lane & lb;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+          const T keep = up ? v[n + k] : v[k], give = up ? v[k] : v[n + k];
+          v[k] = keep + __shfl_xor(give, lb, 64);
         }
       }
-      store_dstage<T, P, 64>(sD[b ^ 1], vD);
-      __builtin_amdgcn_wave_barrier();
-    };
-    const int cn2 = (cn + 1) & ~1;
-    for (int k = 0; k < cn2; k += 2) {
-      step(k, 0, bA, srA, vmA, bB, srB, vmB, gX, srX, vmX, gY, srY, vmY);
-      step(k + 1, 1, bB, srB, vmB, bA, srA, vmA, gY, srY, vmY, gX, srX, vmX);
-    }
-  }
-  const int krow = lane >> 4;
+      if (F >= 0) {
+        gmut<T> out = part + (size_t)F * 32 + 2 * q;
+        out[0] = v[0];
+        out[1] = v[1];
+      }
+    } else {
+      // lane (i = lane >> 4, block = (lane >> 2) & 3, group j)
+      const int i = lane >> 4;
+      T v[8];
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    acc0[t] += hi0[t];
-    acc1[t] += hi1[t];
-    const int F = sF[16 * t + n];
-    if (F < 0) continue;
-    gmut<T> out = part + (size_t)F * 32;
+      for (int o = 0; o < 8; ++o) {
+        const T x = m.acc[d][7 - o];
+        v[o] = i > 0 && (o >> (i - 1) & 1) ? -x : x;
+      }
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = acc_row<T>(krow, r);
-      out[i] = i < 8 ? acc0[t][r] : -acc0[t][r];
-      out[16 + i] = -acc1[t][r];
+      for (int n = 4, lb = 8; n >= 2; n >>= 1, lb >>= 1) {
+        const bool up = lane & lb;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+          const T keep = up ? v[n + k] : v[k], give = up ? v[k] : v[n + k];
+          v[k] = keep + __shfl_xor(give, lb, 64);
+        }
+      }
+      if (F >= 0) {
+        gmut<T> out = part + (size_t)F * 32 + i * 8 + 2 * (q & 3);
+        out[0] = v[0];
+        out[1] = v[1];
+      }
     }
   }
 }
@@ -1244,49 +1082,51 @@ constexpr M2LPlan<P> make_m2l_plan() {
   return pl;
 }
 
-// B of one M2L tap in LDS, fragment order sB[kb][lane]: wave w loads vectors
-// j in [w NVW, (w+1) NVW) of every lane's run (16-byte loads) and writes
-// element e of vector j to sB[(VW j + e) * 64 + lane] (consecutive lanes,
-// consecutive banks).
+// B of one M2L tap in LDS, sB[k][n] (fragment order of the k-steps): thread (n =
+// t & 15, q = t >> 4) loads the vectors of block q of column n's source row and
+// stores each value at its coefficient.  Branch-free: a missing or leaf source
+// reads the zero row, and every thread loads a mass (cell 0 when the source is
+// no leaf), which the threads of block 0 store for a leaf source.
 template <typename T, int P>
-struct M2LStage {
-  static constexpr int NVB = TapStage<T, P>::STP / TapStage<T, P>::VW;  // vectors per lane run
-  static constexpr int NVW = (NVB + 3) / 4;                            // per wave
-};
-
-// Wave w's share of the B stage of a tap (vectors j in [w NVW, (w+1) NVW) of
-// every lane's run).  Branch-free: a missing or leaf source reads the zero
-// row zrow of the source copy, and wave 0 also loads a mass (cell 0 when the
-// source is no leaf) that store_bshare puts into the monopole slot.
-template <typename T, int P, int W>
-__device__ inline void load_bshare(int sr, int zrow, int lane, gptr<double> mass1, gptr<T> S1,
-                                   typename Vec16<T>::type* vb, double& vm) {
-  using TS = TapStage<T, P>;
-  using MS = M2LStage<T, P>;
-  using V = typename Vec16<T>::type;
-  gptr<T> src = S1 + (size_t)(sr >= 0 ? sr : zrow) * TS::ROW;
+struct BStage {
+  using SL = SymLayout<P, (int)sizeof(T)>;
+  static constexpr int CP = SL::CP, NP = SL::NP;
+  typedef typename VecN<T, CP>::type V;
+  struct Regs {
+    V v[NP];
+    double m;
+    bool leaf;
+  };
+  gptr<T> base;
+  gptr<double> mass;
+  int zrow;
+  bool first;
+  int at[NP * CP];  // sB slots of the thread's values
+  __device__ inline void init(const LevelDev& lv) {
+    static constexpr SL sl{};
+    const int t = threadIdx.x, n = t & 15, q = t >> 4;
+    zrow = lv.nref;
+    first = q == 0;
+    base = as_global(level_S<T>(lv)) + q * CP;
+    mass = as_global(lv.mass);
 #pragma unroll
-  for (int i = 0; i < MS::NVW; ++i) {
-    constexpr int j0 = W * MS::NVW;
-    if (j0 + i < MS::NVB) vb[i] = *(gptr<V>)(src + src_vec(j0 + i, lane >> 4, (int)sizeof(T)));
-  }
-  if (W == 0) vm = mass1[sr <= -2 ? -2 - sr : 0];
-}
-
-template <typename T, int P, int W>
-__device__ inline void store_bshare(T* sB, int sr, int lane, typename Vec16<T>::type* vb, double vm) {
-  using TS = TapStage<T, P>;
-  using MS = M2LStage<T, P>;
-  if (W == 0 && sr <= -2 && (lane >> 4) == 0) vb[0][0] = (T)vm;
-#pragma unroll
-  for (int i = 0; i < MS::NVW; ++i) {
-    const int j = W * MS::NVW + i;
-    if (j < MS::NVB) {
-#pragma unroll
-      for (int e = 0; e < TS::VW; ++e) sB[(j * TS::VW + e) * 64 + lane] = vb[i][e];
+    for (int i = 0; i < NP * CP; ++i) {
+      const int h = sl.coef[(i / CP * kSymBlocks + q) * CP + i % CP];
+      at[i] = (h >= 0 ? h : TapStage<T, P>::KP) * 16 + n;
     }
   }
-}
+  __device__ inline void load(int sr, Regs& r) const {
+    gptr<T> src = base + (size_t)(sr >= 0 ? sr : zrow) * SL::ROW;
+#pragma unroll
+    for (int s = 0; s < NP; ++s) r.v[s] = load_vec<T, CP>(src + s * kSymBlocks * CP);
+    r.m = mass[sr <= -2 ? -2 - sr : 0];
+    r.leaf = sr <= -2;
+  }
+  __device__ inline void store(T* sB, const Regs& r) const {
+#pragma unroll
+    for (int i = 0; i < NP * CP; ++i) sB[at[i]] = i == 0 && first && r.leaf ? (T)r.m : r.v[i / CP][i % CP];
+  }
+};
 
 // D~ stage copy without a branch around the loads: thread t loads vectors
 // t, t + NTH, ... clamped to the last one (stores skip the extra ones).
@@ -1309,11 +1149,11 @@ __device__ inline void load_dstage_nb(int code, const T* __restrict__ Dst, typen
 // (sSrcT) before the loop.
 template <typename T, int P, int H>
 __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const int16_t* __restrict__ aoff,
-                                const int* sF, const int* sSrcT, T (*sB)[TapStage<T, P>::STP * 64],
-                                T (*sD)[TapStage<T, P>::SDP], int zrow, gptr<double> mass1,
-                                const T* __restrict__ Dst, gptr<T> S1, gptr<int32_t> rank0, gmut<T> Lout, int ldl) {
+                                const int* sF, const int* sSrcT, T (*sB)[TapStage<T, P>::SB],
+                                T (*sD)[TapStage<T, P>::SDP], const BStage<T, P>& bs,
+                                const T* __restrict__ Dst, gptr<int32_t> rank0, gmut<T> Lout, int ldl) {
   using TS = TapStage<T, P>;
-  using MS = M2LStage<T, P>;
+  using BV = typename BStage<T, P>::Regs;
   using V = typename Vec16<T>::type;
   constexpr int K = TS::K;
   constexpr M2LPlan<P> PL = make_m2l_plan<P>();
@@ -1334,26 +1174,23 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
 #pragma unroll
   for (int i = 0; i < NTH; ++i) acc[i] = {0, 0, 0, 0};
   // register sets X (odd taps ahead) and Y; tap 1 goes to X first
-  V vDX[ND], vDY[ND], vBX[MS::NVW], vBY[MS::NVW];
-  double vmX = 0, vmY = 0;
-  int srX = -1, srY = -1;
+  V vDX[ND], vDY[ND];
+  BV vBX, vBY;
   // Taps run in pairs; an odd range ends with one empty tap (no source, so B
   // is zero; its D~ stage repeats the last tap's finite rows), so that both
   // steps of a pair and every load run unconditionally.
   const int nt2 = (nt + 1) & ~1;
   {
     const int k1 = nt > 1 ? 1 : 0;
-    srX = nt > 1 ? sSrcT[16 + n] : -1;
     load_dstage_nb<T, P, kBlock>(tp[k1], Dst, vDX);
-    load_bshare<T, P, H>(srX, zrow, lane, mass1, S1, vBX, vmX);
+    bs.load(nt > 1 ? sSrcT[16 + n] : -1, vBX);
   }
   // one tap: load tap k + 2 into (vDn, vBn), MFMAs of tap k from LDS buffer
   // b, store tap k + 1 from (vDc, vBc) into buffer b ^ 1
-  auto step = [&](int k, int b, V* vDc, V* vBc, double vmc, int src, V* vDn, V* vBn, double& vmn, int& srn) {
+  auto step = [&](int k, int b, V* vDc, const BV& vBc, V* vDn, BV& vBn) {
     const int k2 = k + 2 < nt ? k + 2 : nt - 1;
-    srn = k + 2 < nt ? sSrcT[k2 * 16 + n] : -1;
     load_dstage_nb<T, P, kBlock>(tp[k2], Dst, vDn);
-    load_bshare<T, P, H>(srn, zrow, lane, mass1, S1, vBn, vmn);
+    bs.load(k + 2 < nt ? sSrcT[k2 * 16 + n] : -1, vBn);
     __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the MFMAs
     const T* B = sB[b] + lane;
     const T* D = sD[b];
@@ -1371,13 +1208,13 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
       }
     if (k + 1 < nt2) {
       store_dstage<T, P, kBlock>(sD[b ^ 1], vDc);
-      store_bshare<T, P, H>(sB[b ^ 1], src, lane, vBc, vmc);
+      bs.store(sB[b ^ 1], vBc);
     }
     __syncthreads();
   };
   for (int k = 0; k < nt2; k += 2) {
-    step(k, 0, vDX, vBX, vmX, srX, vDY, vBY, vmY, srY);
-    step(k + 1, 1, vDY, vBY, vmY, srY, vDX, vBX, vmX, srX);
+    step(k, 0, vDX, vBX, vDY, vBY);
+    step(k + 1, 1, vDY, vBY, vDX, vBX);
   }
   if (NTH > 0 && PL.tile[H][0] == 0) acc[0] += hi;
   const int F = sF[lane & 15];
@@ -1416,9 +1253,9 @@ void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
                                                      const int16_t* __restrict__ aoff,
                                                      const LevelDev* __restrict__ lvs, const T* __restrict__ Dst) {
   using TS = TapStage<T, P>;
-  using MS = M2LStage<T, P>;
+  using BS = BStage<T, P>;
   constexpr int ND = (TS::NDV + kBlock - 1) / kBlock;
-  __shared__ T sB[2][TS::STP * 64];
+  __shared__ T sB[2][TS::SB];
   __shared__ __align__(16) T sD[2][TS::SDP];
   __shared__ int sF[16];
   __shared__ int sCB[16 * 27];
@@ -1439,9 +1276,9 @@ void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
   __syncthreads();
   const int oF = as_global(lv1.refcell)[sF[0]] & 7;
   const int32_t* tpg = taps + oF * kTaps + tb;
-  gptr<T> S1 = as_global(level_S<T>(lv1));
   gptr<int32_t> rank1 = as_global(lv1.rank);
-  gptr<double> mass1 = as_global(lv1.mass);
+  // coefficients past the last one, covered by the last k-step, stay 0
+  for (int i = TS::K * 16 + t; i < TS::KP * 16; i += kBlock) sB[0][i] = sB[1][i] = 0;
   // sources of every tap of the range, then the taps with a source (wave 0)
   for (int i = t; i < (te - tb) * 16; i += kBlock) sSrcT[i] = tap_src(tpg[i >> 4], i & 15, sCB, rank1);
   __syncthreads();
@@ -1452,19 +1289,14 @@ void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
   __syncthreads();
   const int nt = sNt;
   const int* tp = sCode;
-  const int zrow = lv1.nref;
+  BS bs;
+  bs.init(lv1);
   {
     typename Vec16<T>::type vD[ND];
-    typename Vec16<T>::type vB[MS::NVW];
-    double vm = 0;
-    const int sr = sSrcT[lane & 15];
+    typename BS::Regs vB;
     load_dstage_nb<T, P, kBlock>(tp[0], Dst, vD);
-    switch (w) {
-      case 0: load_bshare<T, P, 0>(sr, zrow, lane, mass1, S1, vB, vm); store_bshare<T, P, 0>(sB[0], sr, lane, vB, vm); break;
-      case 1: load_bshare<T, P, 1>(sr, zrow, lane, mass1, S1, vB, vm); store_bshare<T, P, 1>(sB[0], sr, lane, vB, vm); break;
-      case 2: load_bshare<T, P, 2>(sr, zrow, lane, mass1, S1, vB, vm); store_bshare<T, P, 2>(sB[0], sr, lane, vB, vm); break;
-      default: load_bshare<T, P, 3>(sr, zrow, lane, mass1, S1, vB, vm); store_bshare<T, P, 3>(sB[0], sr, lane, vB, vm); break;
-    }
+    bs.load(sSrcT[lane & 15], vB);
+    bs.store(sB[0], vB);
     store_dstage<T, P, kBlock>(sD[0], vD);
   }
   __syncthreads();
@@ -1473,10 +1305,10 @@ void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
   gptr<int32_t> rank0 = as_global(lv0.rank);
   // every wave runs the same number of barriers (one per tap)
   switch (w) {
-    case 0: m2l_part<T, P, 0>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout, ldl); break;
-    case 1: m2l_part<T, P, 1>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout, ldl); break;
-    case 2: m2l_part<T, P, 2>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout, ldl); break;
-    default: m2l_part<T, P, 3>(tp, nt, aoff, sF, sSrcT, sB, sD, zrow, mass1, Dst, S1, rank0, Lout, ldl); break;
+    case 0: m2l_part<T, P, 0>(tp, nt, aoff, sF, sSrcT, sB, sD, bs, Dst, rank0, Lout, ldl); break;
+    case 1: m2l_part<T, P, 1>(tp, nt, aoff, sF, sSrcT, sB, sD, bs, Dst, rank0, Lout, ldl); break;
+    case 2: m2l_part<T, P, 2>(tp, nt, aoff, sF, sSrcT, sB, sD, bs, Dst, rank0, Lout, ldl); break;
+    default: m2l_part<T, P, 3>(tp, nt, aoff, sF, sSrcT, sB, sD, bs, Dst, rank0, Lout, ldl); break;
   }
 }
 
@@ -1740,88 +1572,30 @@ hipError_t launch_drift(const DriftLevels& d, const double* m, const double* rat
 
 template <typename T>
 static hipError_t m2p_dispatch(int p, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
-                               const LevelDev* lvs, const T* Dst, int shape, hipStream_t st) {
+                               const LevelDev* lvs, const T* symA, hipStream_t st) {
   const int items = n * nsplit;
-  const dim3 grid(8 * ((items + 7) / 8)), block(64);
+  const dim3 grid(8 * ((items + 7) / 8)), block(kBlock);
+  if (mt.nc != m2p_cols(p, (int)sizeof(T)) || nsplit < 1 || nsplit > kSymOrbits) return hipErrorInvalidValue;
   const int32_t* tl = mt.tiles + (size_t)t0 * (mt.nc + 1);
-  if (!m2p_shape_ok(p, sizeof(T) == 4, shape) || mt.nc != m2p_shape_columns(shape)) return hipErrorInvalidValue;
-  if (shape == 1 || shape == 2) {
-    if constexpr (sizeof(T) == 4) {
-      switch (p * 4 + shape) {
-#define AFMM_M2PS(PP, SH)                                                                                      \
-  case PP * 4 + SH:                                                                                           \
-    hipLaunchKernelGGL((k_m2p_s<T, PP, SH>), grid, block, 0, st, tl, n, nsplit, tabs.taps, tabs.m2p_off, lvs, Dst); \
+  switch (p) {
+#define AFMM_M2P(PP)                                                                                \
+  case PP:                                                                                          \
+    hipLaunchKernelGGL((k_m2p<T, PP>), grid, block, 0, st, tl, n, nsplit, tabs.symtaps, lvs, symA); \
     break;
-        AFMM_M2PS(1, 1) AFMM_M2PS(2, 1) AFMM_M2PS(3, 1) AFMM_M2PS(4, 1) AFMM_M2PS(5, 1) AFMM_M2PS(6, 1)
-        AFMM_M2PS(7, 1) AFMM_M2PS(8, 1) AFMM_M2PS(1, 2) AFMM_M2PS(2, 2) AFMM_M2PS(3, 2) AFMM_M2PS(4, 2)
-        AFMM_M2PS(5, 2)
-#undef AFMM_M2PS
-        default: return hipErrorInvalidValue;
-      }
-      return hipGetLastError();
-    }
-    return hipErrorInvalidValue;
-  }
-  // LDS source table of k_m2p: the longest tap range of the split, except
-  // for FP32 from p = 6 on, where the table keeps all 189 taps so that the
-  // block's LDS (about 20 KB) holds the kernel at 2 waves per SIMD.  Measured:
-  // FP32 at p = 6, 2 waves per SIMD beat 3 and 4 (the 16 source rows each wave
-  // streams thrash L1 when more waves share it); FP32 at p = 4 (a short tap of
-  // 14 MFMAs leaves the waits exposed) and FP64 at p = 6 ran 7-9% faster with
-  // the smaller table at a split of 3.
-  int ntmax = 0;
-  for (int c = 0; c < nsplit; ++c) {
-    int tb, te;
-    tap_range(c, nsplit, tb, te);
-    ntmax = std::max(ntmax, te - tb);
-  }
-  const size_t lds = shape == 3 ? 0 : (size_t)(sizeof(T) == 4 && p >= 6 ? kTaps : ntmax) * 16 * sizeof(int);
-  switch (p * 2 + (shape == 3)) {
-#define AFMM_M2P(PP, XB)                                                                                         \
-  case PP * 2 + XB:                                                                                              \
-    hipLaunchKernelGGL((k_m2p<T, PP, XB>), grid, block, lds, st, tl, n, nsplit, tabs.taps, tabs.m2p_off, lvs, Dst); \
-    break;
-    AFMM_M2P(1, 0) AFMM_M2P(2, 0) AFMM_M2P(3, 0) AFMM_M2P(4, 0) AFMM_M2P(5, 0) AFMM_M2P(6, 0) AFMM_M2P(7, 0)
-    AFMM_M2P(8, 0) AFMM_M2P(1, 1) AFMM_M2P(2, 1) AFMM_M2P(3, 1) AFMM_M2P(4, 1) AFMM_M2P(5, 1) AFMM_M2P(6, 1)
-    AFMM_M2P(7, 1)
+    AFMM_M2P(1) AFMM_M2P(2) AFMM_M2P(3) AFMM_M2P(4) AFMM_M2P(5) AFMM_M2P(6) AFMM_M2P(7) AFMM_M2P(8)
 #undef AFMM_M2P
-    case 8 * 2 + 1:
-      if constexpr (sizeof(T) == 4) {
-        hipLaunchKernelGGL((k_m2p<T, 8, true>), grid, block, lds, st, tl, n, nsplit, tabs.taps, tabs.m2p_off, lvs, Dst);
-        break;
-      }
-      return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_m2p(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, int shape,
-                      const MfmaTables& tabs, const LevelDev* lvs, const TablesDev<float>& t32,
-                      const TablesDev<double>& t64, hipStream_t st) {
+hipError_t launch_m2p(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
+                      const LevelDev* lvs, const TablesDev<float>& t32, const TablesDev<double>& t64,
+                      hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  if (fp32) return m2p_dispatch<float>(p, mt, t0, n, nsplit, tabs, lvs, t32.Dstage, shape, st);
-  return m2p_dispatch<double>(p, mt, t0, n, nsplit, tabs, lvs, t64.Dstage, shape, st);
+  if (fp32) return m2p_dispatch<float>(p, mt, t0, n, nsplit, tabs, lvs, t32.symA, st);
+  return m2p_dispatch<double>(p, mt, t0, n, nsplit, tabs, lvs, t64.symA, st);
 }
-
-int m2p_columns(int p, bool fp32) {
-  (void)p;
-  (void)fp32;
-  return 16;
-}
-
-// Tile shapes of the M2P launch: 0 the direct form (16 groups per wave), 1 the
-// row-staged form (16 groups), 2 the row-staged form with two tiles of one
-// parity class per wave (32 groups; up to p = 5, where its registers fit),
-// 3 the direct form with row-wise B loads passed over the crossbar (16
-// groups).  The staged forms are instantiated for the FP32 kernels only.
-bool m2p_shape_ok(int p, bool fp32, int shape) {
-  if (shape == 0) return true;
-  if (shape == 3) return fp32 || p <= 7;  // FP64 at p = 8 would spill
-  if (!fp32) return false;
-  return shape == 1 || (shape == 2 && p <= 5);
-}
-int m2p_shape_columns(int shape) { return shape == 2 ? 32 : 16; }
 
 template <typename T>
 static hipError_t m2l_dispatch(int p, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,

@@ -43,6 +43,36 @@ template <typename T> struct Vec16;
 template <> struct Vec16<float> { typedef float type __attribute__((ext_vector_type(4))); };
 template <> struct Vec16<double> { typedef double type __attribute__((ext_vector_type(2))); };
 
+// N consecutive values as one vector (registers).  A 3-vector has the size of
+// four values in memory, so those are moved value by value (the compiler joins
+// the accesses); the others as one access of the pointer's alignment.
+template <typename T, int N> struct VecN { typedef T type __attribute__((ext_vector_type(N))); };
+template <typename T, int N, typename Ptr>
+__device__ inline typename VecN<T, N>::type load_vec(Ptr p) {
+  using V = typename VecN<T, N>::type;
+  V v;
+  if constexpr (N == 1 || N == 3) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = p[i];
+  } else {
+    static_assert(sizeof(V) == N * sizeof(T), "vector without padding");
+    if constexpr (__is_same(Ptr, gptr<T>)) v = *(gptr<V>)p;
+    else v = *(const V*)p;
+  }
+  return v;
+}
+template <typename T, int N>
+__device__ inline void store_vec(T* p, typename VecN<T, N>::type v) {
+  using V = typename VecN<T, N>::type;
+  if constexpr (N == 1 || N == 3) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) p[i] = v[i];
+  } else {
+    static_assert(sizeof(V) == N * sizeof(T), "vector without padding");
+    *(V*)p = v;
+  }
+}
+
 // XCD-aware tile order: consecutive blocks land on different XCDs, so block b
 // takes tile (b % 8) * ceil(n/8) + b / 8 and each XCD sweeps one contiguous
 // (spatially compact) range of tiles.
