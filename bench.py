@@ -32,7 +32,7 @@ sys.path.insert(0, ROOT)
 METRIC = "cells/sec full FMM solve (φ+accel) at rel. force err ≤1e-4, FP32 vs FP64"
 PEAK = {"fp32_mfma": 157.3, "fp64_mfma": 78.6, "fp32_vector": 157.3, "fp64_vector": 78.6, "hbm": 8000.0}
 KERNEL_NAMES = {"near_f32": "k_near<float, P>", "near_f64": "k_near<double, P>",
-                "m2l_f32": "k_m2l_mfma<float, P>", "m2l_f64": "k_m2l_mfma<double, P>",
+                "m2l_f32": "k_m2l<float, P> (k_m2l_taps to p = 4)", "m2l_f64": "k_m2l<double, P> (k_m2l_taps to p = 4)",
                 "m2p_f32": "k_m2p<float, P>", "m2p_f64": "k_m2p<double, P>",
                 "l2l": "k_l2l<T, TL, P>", "upward": "k_upward<P>", "gather": "k_gather_mass",
                 "adj_near": "k_adj_near_leaf + k_adj_near_m2p<P>", "adj_m2p": "k_adj_m2p<P>",
@@ -292,7 +292,7 @@ def time_form(h, mass_t, p, precision, steps, warmup, overlap=False, autotune=Tr
 
 
 SYMBOLS = {"m2p_f32": "k_m2p<float, {p}>", "m2p_f64": "k_m2p<double, {p}>",
-           "m2l_f32": "k_m2l_mfma<float, {p}>", "m2l_f64": "k_m2l_mfma<double, {p}>",
+           "m2l_f32": "k_m2l<float, {p}>", "m2l_f64": "k_m2l<double, {p}>",
            "near_f32": "k_near<float, {p}>", "near_f64": "k_near<double, {p}>", "upward": "k_upward<{p}>"}
 
 
@@ -300,7 +300,8 @@ def executed_share(family, p):
     """Share of a family's profiled operations that its kernel executes.  The profile
     counts the Cartesian translation of every (target, source) pair: (p+1)(p+2)(p+3)/6
     coefficients, 189 sources per group.  The kernels work on the (p+1)^2 independent
-    coefficients, and M2P on 56 orbits of sources that share an operator."""
+    coefficients, and M2P and (from p = 5) M2L on 56 orbits of sources that share an
+    operator."""
     def n_full(q):
         return (q + 1) * (q + 2) * (q + 3) // 6
 
@@ -311,7 +312,8 @@ def executed_share(family, p):
     if family.startswith("m2l_"):  # pairs with |a| + |b| <= p
         def pairs(inc):
             return sum(inc(d) * sum(inc(e) for e in range(p - d + 1)) for d in range(p + 1))
-        return pairs(lambda d: 2 * d + 1) / pairs(lambda d: (d + 1) * (d + 2) // 2)
+        share = pairs(lambda d: 2 * d + 1) / pairs(lambda d: (d + 1) * (d + 2) // 2)
+        return share if p <= 4 else share * 56 / 189
     return 1.0
 
 

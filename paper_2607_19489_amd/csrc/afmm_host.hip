@@ -590,14 +590,18 @@ struct HostTables {
   std::vector<int32_t> taps;        // [8][189]
   std::vector<int8_t> symtaps;      // [8][56][8]
   std::vector<double> symE;         // [orbit][8][K] D~ over the 8 child offsets as characters
+  std::vector<int> symvar;          // [8][56] variant of an orbit for each class
+  std::vector<double> symE64;       // E rows of the variants (TablesDev::symE), one per element type
+  std::vector<float> symE32;
+  std::vector<double> dstage64;     // TablesDev::Dstage, one per element type
+  std::vector<float> dstage32;
   std::vector<double> symA64;       // M2P operators (TablesDev::symA), one per element type
   std::vector<float> symA32;
-  std::vector<int16_t> m2l_off;     // [steps][64]
+  std::vector<int16_t> m2l_off;     // [8][steps][64]
   std::vector<int32_t> m2m_start, m2m_list;
   std::vector<double> m2m_w;
   std::vector<int32_t> m2mT_start, m2mT_list, tapsT;
   std::vector<double> m2mT_w;
-  std::vector<int32_t> m2l_tinfo;   // [NT][2]
   std::vector<int16_t> adj_m2p_off, adj_m2l_off;
   std::vector<int32_t> l2lT_start, l2lT_list;
   std::vector<double> l2lT_w;
@@ -903,27 +907,38 @@ static void build_tables(int p, HostTables& H) {
         }
     }
   }
-  const int NT = (8 * KH + 15) / 16;
-  H.m2l_tinfo.assign(2 * NT, 0);
+  // M2L's A operand.  By taps: row tile t (rows R = 8 b + o from 16 t), k-step kb
   H.m2l_off.clear();
-  int step = 0;
-  for (int T = 0; T < NT; ++T) {
-    const int ks = (nh(p - h_deg(2 * T)) + 3) / 4;
-    H.m2l_tinfo[2 * T] = ks;
-    H.m2l_tinfo[2 * T + 1] = step;
-    step += ks;
-    for (int kb = 0; kb < ks; ++kb)
-      for (int lane = 0; lane < 64; ++lane) {
-        const int R = 16 * T + (lane & 15), k = 4 * kb + (lane >> 4);
-        const int b = R >> 3, o = R & 7;
-        int v = ZERO;
-        if (b < KH && k < KH && h_deg(k) + h_deg(b) <= p) {
-          const int *kk = &H.mi[4 * h_full(k)], *bb = &H.mi[4 * h_full(b)];
-          v = o * KS + mi_index(kk[0] + bb[0], kk[1] + bb[1], kk[2] + bb[2]);
+  if (m2l_by_taps(p)) {
+    for (int t = 0; 16 * t < 8 * KH; ++t)
+      for (int kb = 0; kb < (nh(p - h_deg(2 * t)) + 3) / 4; ++kb)
+        for (int lane = 0; lane < 64; ++lane) {
+          const int R = 16 * t + (lane & 15), k = 4 * kb + (lane >> 4), b = R >> 3, o = R & 7;
+          int v = ZERO;
+          if (b < KH && k < KH && h_deg(k) + h_deg(b) <= p) {
+            const int *kk = &H.mi[4 * h_full(k)], *bb = &H.mi[4 * h_full(b)];
+            v = o * KS + mi_index(kk[0] + bb[0], kk[1] + bb[1], kk[2] + bb[2]);
+          }
+          H.m2l_off.push_back((int16_t)v);
         }
-        H.m2l_off.push_back((int16_t)v);
-      }
+    return;
   }
+  // by orbits: character chi, row tile r (b = 16 r + (lane & 15)), k-step kb
+  // (a = 4 kb + (lane >> 4)) takes E_(chi ^ par b)[a + b]; k-steps outermost
+  for (int chi = 0; chi < 8; ++chi)
+    for (int kb = 0; kb < (KH + 3) / 4; ++kb)
+      for (int r = 0; 16 * r < KH; ++r) {
+        if (kb >= (nh(p - h_deg(16 * r)) + 3) / 4) continue;
+        for (int lane = 0; lane < 64; ++lane) {
+          const int b = 16 * r + (lane & 15), a = 4 * kb + (lane >> 4);
+          int v = 8 * sym_es(p);
+          if (b < KH && a < KH && h_deg(a) + h_deg(b) <= p) {
+            const int *aa = &H.mi[4 * h_full(a)], *bb = &H.mi[4 * h_full(b)];
+            v = (chi ^ h_parity(b)) * sym_es(p) + mi_index(aa[0] + bb[0], aa[1] + bb[1], aa[2] + bb[2]);
+          }
+          H.m2l_off.push_back((int16_t)v);
+        }
+      }
 }
 
 // M2P operator of an orbit: lane (block q, row i) of character chi holds, for the
@@ -948,7 +963,58 @@ static void sym_operator(const HostTables& H, std::vector<T>& v) {
   }
 }
 
-static void build_sym(int p, HostTables& H) {
+// E rows of the variants (M2L): E_x[g] with the sign (-1)^popcount((x ^ par g) & far),
+// far the variant's axes
+template <typename T>
+static void sym_variants(const HostTables& H, std::vector<T>& v) {
+  const int p = H.p, len = sym_elen(p, (int)sizeof(T));
+  v.assign((size_t)kSymVariants * len, T(0));
+  T* out = v.data();
+  for (int w = 0; w < kSymOrbits; ++w) {
+    const int free = (w / 7) & ~sym_axes(sym_set(w / 7, w % 7));
+    for (int far = 0; far < 8; ++far) {
+      if (far & ~free) continue;
+      for (int x = 0; x < 8; ++x)
+        for (int g = 0; g < H.K; ++g) {
+          const int par = (H.mi[4 * g] & 1) | (H.mi[4 * g + 1] & 1) << 1 | (H.mi[4 * g + 2] & 1) << 2;
+          const double e = H.symE[((size_t)w * 8 + x) * H.K + g];
+          out[x * sym_es(p) + g] = (T)(__builtin_popcount((x ^ par) & far) & 1 ? -e : e);
+        }
+      out += len;
+    }
+  }
+}
+
+// D~ rows in the LDS stage layout of the MFMA kernels (per element type:
+// the padding is to whole 16-byte vectors)
+template <typename T>
+static void build_dstage(const HostTables& H, std::vector<T>& v) {
+  const int ks = dstage_ks(H.p), len = dstage_len(H.p, (int)sizeof(T));
+  v.assign((size_t)kNumD * len, T(0));
+  for (int di = 0; di < kNumD; ++di)
+    for (int o = 0; o < 8; ++o)
+      for (int g = 0; g < H.K; ++g) v[(size_t)di * len + o * ks + g] = (T)H.Dil[((size_t)di * 8 + o) * H.K + g];
+}
+
+static void build_device_tables(int p, HostTables& H) {
+  H.symvar.assign(8 * kSymOrbits, 0);
+  for (int oF = 0; oF < 8; ++oF) {
+    int base = 0;
+    for (int w = 0; w < kSymOrbits; ++w) {
+      const int free = (w / 7) & ~sym_axes(sym_set(w / 7, w % 7));
+      for (int far = 0; far < 8; ++far) {
+        if (far & ~free) continue;
+        if (far == (oF & free)) H.symvar[oF * kSymOrbits + w] = base;
+        ++base;
+      }
+    }
+  }
+  if (!m2l_by_taps(p)) {
+    sym_variants(H, H.symE64);
+    sym_variants(H, H.symE32);
+  }
+  build_dstage(H, H.dstage64);
+  build_dstage(H, H.dstage32);
   switch (p) {
 #define X(PP)                              \
   case PP:                                 \
@@ -969,7 +1035,7 @@ static std::shared_ptr<const HostTables> tables_for(int p) {
   if (!cache[p]) {
     auto t = std::make_shared<HostTables>();
     build_tables(p, *t);
-    build_sym(p, *t);
+    build_device_tables(p, *t);
     cache[p] = t;
   }
   return cache[p];
@@ -1278,15 +1344,15 @@ afmm_status dev_alloc(afmm_plan* P, void** ptr, size_t bytes) {
 }
 
 template <typename V>
-afmm_status upload(afmm_plan* P, const std::vector<V>& v, V** out, hipStream_t st) {
+afmm_status upload(afmm_plan* P, const std::vector<V>& v, V** out, hipStream_t st, bool temporary = true) {
   *out = nullptr;
   if (v.empty()) return AFMM_OK;
   void* p = nullptr;
   afmm_status s = dev_alloc(P, &p, v.size() * sizeof(V));
   if (s) return s;
-  // the source is often a temporary: wait for the copy before it can go away
+  // a temporary source: wait for the copy before it can go away
   if (hipMemcpyAsync(p, v.data(), v.size() * sizeof(V), hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess)
+      (temporary && hipStreamSynchronize(st) != hipSuccess))
     return fail(AFMM_E_DEVICE, "upload failed");
   *out = (V*)p;
   return AFMM_OK;
@@ -1478,20 +1544,30 @@ static int append_m2p_tiles(const Topology& T, int target, const std::vector<int
   for (int32_t F : grp) cls[L1.refcell[F] & 7].push_back(F);
   parallel_ranges(8, grp.size() > 256 ? 8 : 1, [&](int64_t b, int64_t e, int) {
     for (int64_t c = b; c < e; ++c) {
-      std::vector<int32_t> seen(L2.nref(), -1);  // last tile with this father
+      // fathers of the tile: open addressing, at most nf + 27 of 1024 slots taken
+      constexpr uint32_t kSlots = 1024;
+      std::vector<int32_t> key(kSlots), of(kSlots, -1);  // rank, and the tile it belongs to
       int cols = 0, fathers = 0, tile = 0;
       for (size_t i = 0; i < cls[c].size();) {
         const int32_t* nb = &L2.nbr[(size_t)(L1.refcell[cls[c][i]] >> 3) * 27];
+        int32_t rk[27];
         int add = 0;
-        for (int k = 0; k < 27; ++k) add += nb[k] >= 0 && L2.rank[nb[k]] >= 0 && seen[L2.rank[nb[k]]] != tile;
-        if (cols == nc || fathers + add > nf) {
+        for (int k = 0; k < 27; ++k) rk[k] = nb[k] >= 0 ? L2.rank[nb[k]] : -1;
+        for (int k = 0; k < 27; ++k) {
+          if (rk[k] < 0) continue;
+          uint32_t h = ((uint32_t)rk[k] * 2654435761u) >> 22;
+          while (of[h] == tile && key[h] != rk[k]) h = (h + 1) & (kSlots - 1);
+          if (of[h] == tile) continue;
+          of[h] = tile;
+          key[h] = rk[k];
+          ++add;
+        }
+        if (cols == nc || fathers + add > nf) {  // the group begins the next tile
           end[c].push_back((int32_t)i);
           cols = fathers = 0;
           ++tile;
           continue;
         }
-        for (int k = 0; k < 27; ++k)
-          if (nb[k] >= 0 && L2.rank[nb[k]] >= 0) seen[L2.rank[nb[k]]] = tile;
         ++cols;
         fathers += add;
         ++i;
@@ -1630,6 +1706,19 @@ static afmm_status alloc_split_buffers(afmm_plan* P, const int* prev_m2l = nullp
   return s;
 }
 
+// D~ rows: read by the adjoint, and by M2L where it sums tap by tap
+static afmm_status upload_dstage(afmm_plan* P, hipStream_t st) {
+  afmm_status s;
+  double* d64 = nullptr;
+  float* d32 = nullptr;
+  if (P->t64.Dstage) return AFMM_OK;
+  if (P->opt.precision == AFMM_FP32_MIXED && (s = upload(P, P->tabs->dstage32, &d32, st))) return s;
+  if ((s = upload(P, P->tabs->dstage64, &d64, st))) return s;
+  P->t32.Dstage = d32;
+  P->t64.Dstage = d64;
+  return AFMM_OK;
+}
+
 static afmm_status adjoint_topology(afmm_plan* P);
 static bool adjoint_noalloc_may_fit(const afmm_plan* P);
 
@@ -1639,7 +1728,7 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
   const int K = P->K;
   const bool mixed = P->opt.precision == AFMM_FP32_MIXED;
   const int f64 = mixed ? P->opt.fp64_levels : 1 << 20;
-  build_groups(T);
+  build_groups(T);  // the plan keeps its topology and tables: their uploads are waited for once, at the end
   P->tabs = tables_for(P->opt.p);
   afmm_status s;
   for (int l = 0; l <= T.lmax; ++l) {
@@ -1648,8 +1737,8 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     D.n = H.n();
     D.nref = H.nref();
     int32_t *rank, *slot, *refcell, *nbr;
-    if ((s = upload(P, H.rank, &rank, st)) || (s = upload(P, H.slot, &slot, st)) ||
-        (s = upload(P, H.refcell, &refcell, st)) || (s = upload(P, H.nbr, &nbr, st)))
+    if ((s = upload(P, H.rank, &rank, st, false)) || (s = upload(P, H.slot, &slot, st, false)) ||
+        (s = upload(P, H.refcell, &refcell, st, false)) || (s = upload(P, H.nbr, &nbr, st, false)))
       return s;
     D.rank = rank;
     D.slot = slot;
@@ -1689,12 +1778,12 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     }
   }
   for (int l = 0; l <= T.lmax; ++l) {
-    if ((s = upload(P, T.leafgrp[l], &P->d_leafgrp[l], st))) return s;
-    if ((s = upload(P, T.m2lgrp[l], &P->d_m2lgrp[l], st))) return s;
-    if ((s = upload(P, T.nmgrp[l], &P->d_nmgrp[l], st))) return s;
-    if ((s = upload(P, T.adjvgrp[l], &P->d_adjvgrp[l], st))) return s;
-    if ((s = upload(P, T.upleaf[l], &P->d_upleaf[l], st))) return s;
-    if ((s = upload(P, T.upmix[l], &P->d_upmix[l], st))) return s;
+    if ((s = upload(P, T.leafgrp[l], &P->d_leafgrp[l], st, false))) return s;
+    if ((s = upload(P, T.m2lgrp[l], &P->d_m2lgrp[l], st, false))) return s;
+    if ((s = upload(P, T.nmgrp[l], &P->d_nmgrp[l], st, false))) return s;
+    if ((s = upload(P, T.adjvgrp[l], &P->d_adjvgrp[l], st, false))) return s;
+    if ((s = upload(P, T.upleaf[l], &P->d_upleaf[l], st, false))) return s;
+    if ((s = upload(P, T.upmix[l], &P->d_upmix[l], st, false))) return s;
     if (!T.nmgrp[l].empty()) {
       const size_t es = (mixed && (l - 1) > f64) ? sizeof(float) : sizeof(double);
       // groups without refined near candidates are never written: zero once
@@ -1708,13 +1797,13 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     std::vector<int8_t> mi8(H.mi.begin(), H.mi.end());
     int8_t* d_mi;
     int16_t *d_sum, *d_up, *d_m2l_off;
+    int *d_svar, *d_taps;
     double* d_binom;
-    int32_t *d_taps, *d_tinfo;
     int8_t* d_stap;
-    if ((s = upload(P, mi8, &d_mi, st)) || (s = upload(P, H.sumidx, &d_sum, st)) || (s = upload(P, H.up, &d_up, st)) ||
-        (s = upload(P, H.binom, &d_binom, st)) || (s = upload(P, H.taps, &d_taps, st)) ||
-        (s = upload(P, H.symtaps, &d_stap, st)) || (s = upload(P, H.m2l_off, &d_m2l_off, st)) ||
-        (s = upload(P, H.m2l_tinfo, &d_tinfo, st)))
+    if ((s = upload(P, mi8, &d_mi, st)) || (s = upload(P, H.sumidx, &d_sum, st, false)) || (s = upload(P, H.up, &d_up, st, false)) ||
+        (s = upload(P, H.binom, &d_binom, st, false)) || (s = upload(P, H.taps, &d_taps, st, false)) ||
+        (s = upload(P, H.symtaps, &d_stap, st, false)) ||
+        (s = upload(P, H.symvar, &d_svar, st, false)) || (s = upload(P, H.m2l_off, &d_m2l_off, st, false)))
       return s;
     P->cm.mi = d_mi;
     P->cm.sumidx = d_sum;
@@ -1745,7 +1834,7 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     int32_t* d_fs;
     int16_t* d_fl;
     double *d_fw, *d_fp;
-    if ((s = upload(P, H.fold_start, &d_fs, st)) || (s = upload(P, H.fold_list, &d_fl, st)) ||
+    if ((s = upload(P, H.fold_start, &d_fs, st, false)) || (s = upload(P, H.fold_list, &d_fl, st, false)) ||
         (s = upload(P, fw, &d_fw, st)) || (s = upload(P, fp, &d_fp, st)))
       return s;
     P->cm.fold_start = d_fs;
@@ -1754,50 +1843,39 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     P->cm.fold_p2m = d_fp;
     int32_t *d_ms, *d_ml;
     double* d_mw;
-    if ((s = upload(P, H.m2m_start, &d_ms, st)) || (s = upload(P, H.m2m_list, &d_ml, st)) ||
-        (s = upload(P, H.m2m_w, &d_mw, st)))
+    if ((s = upload(P, H.m2m_start, &d_ms, st, false)) || (s = upload(P, H.m2m_list, &d_ml, st, false)) ||
+        (s = upload(P, H.m2m_w, &d_mw, st, false)))
       return s;
     P->cm.m2m_start = d_ms;
     P->cm.m2m_list = d_ml;
     P->cm.m2m_w = d_mw;
     int32_t *d_ts, *d_tl, *d_tt;
     double* d_tw;
-    if ((s = upload(P, H.m2mT_start, &d_ts, st)) || (s = upload(P, H.m2mT_list, &d_tl, st)) ||
-        (s = upload(P, H.m2mT_w, &d_tw, st)) || (s = upload(P, H.tapsT, &d_tt, st)))
+    if ((s = upload(P, H.m2mT_start, &d_ts, st, false)) || (s = upload(P, H.m2mT_list, &d_tl, st, false)) ||
+        (s = upload(P, H.m2mT_w, &d_tw, st, false)) || (s = upload(P, H.tapsT, &d_tt, st, false)))
       return s;
     P->cm.m2mT_start = d_ts;
     P->cm.m2mT_list = d_tl;
     P->cm.m2mT_w = d_tw;
     P->cm.tapsT = d_tt;
     int16_t *d_ap, *d_al;
-    if ((s = upload(P, H.adj_m2p_off, &d_ap, st)) || (s = upload(P, H.adj_m2l_off, &d_al, st))) return s;
+    if ((s = upload(P, H.adj_m2p_off, &d_ap, st, false)) || (s = upload(P, H.adj_m2l_off, &d_al, st, false))) return s;
     P->cm.adj_m2p_off = d_ap;
     P->cm.adj_m2l_off = d_al;
     int32_t *d_lts, *d_ltl;
     double* d_ltw;
-    if ((s = upload(P, H.l2lT_start, &d_lts, st)) || (s = upload(P, H.l2lT_list, &d_ltl, st)) ||
-        (s = upload(P, H.l2lT_w, &d_ltw, st)))
+    if ((s = upload(P, H.l2lT_start, &d_lts, st, false)) || (s = upload(P, H.l2lT_list, &d_ltl, st, false)) ||
+        (s = upload(P, H.l2lT_w, &d_ltw, st, false)))
       return s;
     P->cm.l2lT_start = d_lts;
     P->cm.l2lT_list = d_ltl;
     P->cm.l2lT_w = d_ltw;
     P->mt.taps = d_taps;
     P->mt.symtaps = d_stap;
+    P->mt.symvar = d_svar;
     P->mt.m2l_off = d_m2l_off;
-    P->mt.m2l_tinfo = d_tinfo;
   }
-  // D~ rows in the LDS stage layout of the MFMA kernels (per element type: the
-  // padding is to whole 16-byte vectors)
-  auto dstage = [&](int bytes) {
-    const int p = P->opt.p, ks = dstage_ks(p), len = dstage_len(p, bytes);
-    std::vector<double> v((size_t)kNumD * len, 0.0);
-    for (int di = 0; di < kNumD; ++di)
-      for (int o = 0; o < 8; ++o)
-        for (int g = 0; g < K; ++g) v[(size_t)di * len + o * ks + g] = H.Dil[((size_t)di * 8 + o) * K + g];
-    return v;
-  };
-  if ((s = upload_conv<double>(P, dstage(8), &P->t64.Dstage, st))) return s;
-  if (mixed && (s = upload_conv<float>(P, dstage(4), &P->t32.Dstage, st))) return s;
+  if (m2l_by_taps(P->opt.p) && (s = upload_dstage(P, st))) return s;
   // near-field operator regrouped into 16-byte vectors of consecutive MFMA
   // steps per lane: [t][kb / VW][lane][kb % VW]
   auto near_vec = [&](int bytes) {
@@ -1842,6 +1920,7 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
   // array) and the intermediate-field partials
   {
     std::vector<int32_t> m2p_rec[2], m2l_rec[2];
+    const int m2l_nc[2] = {m2l_cols(P->opt.p, 8), m2l_cols(P->opt.p, 4)};
     const int m2p_nc[2] = {m2p_cols(P->opt.p, 8), m2p_cols(P->opt.p, 4)};
     for (int l = 3; l <= T.lmax; ++l) {
       const int pr = (mixed && (l - 1) > f64) ? 1 : 0;
@@ -1852,25 +1931,37 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
       P->m2p_range[l][2] = n;
       const int pm = (mixed && l > f64) ? 1 : 0;
       if (l <= T.lmax - 1) {
-        const int m0 = (int)(m2l_rec[pm].size() / 17);
-        const int m = append_tiles(T, l, T.m2lgrp[l], 16, m2l_rec[pm]);
+        const int m0 = (int)(m2l_rec[pm].size() / (m2l_nc[pm] + 1));
+        const int m = append_tiles(T, l, T.m2lgrp[l], m2l_nc[pm], m2l_rec[pm]);
         P->m2l_range[l][0] = pm;
         P->m2l_range[l][1] = m0;
         P->m2l_range[l][2] = m;
       }
     }
-    // M2L launches with few tiles split their 189 taps over several blocks
+    // splits of the orbits over several blocks
     int ncu = 256;
     {
       int dev = 0;
       if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
       if (ncu <= 0) ncu = 256;
     }
+    // M2L by orbits: one block runs per CU, and costs its orbits and about 4 more for
+    // its sources' table and the sums' way out; the split with the fewest rounds x
+    // cost (168 tiles at p = 6 FP32: 120, 134, 104, 124 us at 1, 2, 3, 4; 336 tiles
+    // FP64: 244, 200, 187, 219 us).  By taps: two blocks per CU.
     for (int pr = 0; pr < 2; ++pr) {
-      const int nt = (int)(m2l_rec[pr].size() / 17);
-      P->m2l_split[pr] = P->opt.tap_split > 0 ? P->opt.tap_split
-                         : nt > 0              ? std::max(1, std::min(21, (2 * ncu + nt - 1) / nt))
-                                               : 1;
+      const int nt = (int)(m2l_rec[pr].size() / (m2l_nc[pr] + 1));
+      int sp = 1;
+      if (m2l_by_taps(P->opt.p)) {
+        if (nt > 0) sp = std::max(1, std::min(21, (2 * ncu + nt - 1) / nt));
+      } else {
+        auto cost = [&](int n) {
+          return (int64_t)((nt * (int64_t)n + ncu - 1) / ncu) * ((kSymOrbits + n - 1) / n + 4);
+        };
+        for (int n = 2; n <= 21; ++n)
+          if (nt > 0 && 50 * cost(n) < 49 * cost(sp)) sp = n;  // 2%: more sets for k_l2l to add
+      }
+      P->m2l_split[pr] = P->opt.tap_split > 0 ? P->opt.tap_split : sp;
     }
     // M2P likewise; each range of orbits writes its own partial set, summed in
     // order by the leaf kernel.  Powers of two, whose ranges are whole phases of 7
@@ -1891,13 +1982,18 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
       if ((s = upload(P, m2p_rec[pr], &d, st))) return s;
       P->m2p_all[pr] = {d, (int)(m2p_rec[pr].size() / (m2p_nc[pr] + 1)), m2p_nc[pr]};
       if ((s = upload(P, m2l_rec[pr], &d, st))) return s;
-      P->m2l_all[pr] = {d, (int)(m2l_rec[pr].size() / 17), 16};
+      P->m2l_all[pr] = {d, (int)(m2l_rec[pr].size() / (m2l_nc[pr] + 1)), m2l_nc[pr]};
     }
-    float* a32 = nullptr;
-    double* a64 = nullptr;
-    if ((!m2p_rec[0].empty() && (s = upload(P, H.symA64, &a64, st))) ||
-        (!m2p_rec[1].empty() && (s = upload(P, H.symA32, &a32, st))))
+    // the operators of the kernels that the plan runs
+    float *a32 = nullptr, *e32 = nullptr;
+    double *a64 = nullptr, *e64 = nullptr;
+    if ((!m2p_rec[0].empty() && (s = upload(P, H.symA64, &a64, st, false))) ||
+        (!m2p_rec[1].empty() && (s = upload(P, H.symA32, &a32, st, false))) ||
+        (!m2l_rec[0].empty() && (s = upload(P, H.symE64, &e64, st, false))) ||
+        (!m2l_rec[1].empty() && (s = upload(P, H.symE32, &e32, st, false))))
       return s;
+    P->t64.symE = e64;
+    P->t32.symE = e32;
     P->t64.symA = a64;
     P->t32.symA = a32;
     // ATS chains: walking up from the groups of target level l, the needed
@@ -1927,8 +2023,8 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
       std::vector<int32_t> rec[2];
       for (int f = 3; f <= l - 1; ++f) {
         const int pm = P->m2l_range[f][0];
-        const int m0 = (int)(rec[pm].size() / 17);
-        const int m = append_tiles(T, f, grp[f], 16, rec[pm]);
+        const int m0 = (int)(rec[pm].size() / (m2l_nc[pm] + 1));
+        const int m = append_tiles(T, f, grp[f], m2l_nc[pm], rec[pm]);
         A.m2l_range[f][0] = pm;
         A.m2l_range[f][1] = m0;
         A.m2l_range[f][2] = m;
@@ -1938,7 +2034,7 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
       for (int pr = 0; pr < 2; ++pr) {
         int32_t* d = nullptr;
         if ((s = upload(P, rec[pr], &d, st))) return s;
-        A.m2l_all[pr] = {d, (int)(rec[pr].size() / 17), 16};
+        A.m2l_all[pr] = {d, (int)(rec[pr].size() / (m2l_nc[pr] + 1)), m2l_nc[pr]};
       }
       A.on = true;
     }
@@ -2218,7 +2314,7 @@ static afmm_status run_solve(afmm_plan* P, const double* msrc, int fmax, int lo,
       }
     if (n <= 0) continue;
     hipEvent_t a = prof_begin(P, st);
-    if ((s = dev_check(P, launch_m2l_taps(p, pr == 1, m2l_all[pr], t0, n, P->m2l_split[pr], P->mt, P->d_lvs,
+    if ((s = dev_check(P, launch_m2l(p, pr == 1, m2l_all[pr], t0, n, P->m2l_split[pr], P->mt, P->d_lvs,
                                           P->t32, P->t64, st),
                        "m2l")))
       return s;
@@ -2729,6 +2825,7 @@ static afmm_status adjoint_topology(afmm_plan* P) {
   if (P->adj_topo) return AFMM_OK;
   const Topology& T = P->topo;
   afmm_status s;
+  if ((s = upload_dstage(P, nullptr))) return s;
   // source tiles: the level-ls cells read by some group of `grp` (refined ranks
   // at ls), 16 per tile in Morton order, one octant class per tile.  For every
   // tile, the taps (transposed order) whose group has a target child in some

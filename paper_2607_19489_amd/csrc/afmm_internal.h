@@ -82,6 +82,14 @@ __host__ __device__ constexpr int h_full(int h) {
   return mi_index(n - b - c, b, c);
 }
 
+// parities of folded coefficient h (bit i: axis i)
+__host__ __device__ inline int h_parity(int h) {
+  int n = 0;
+  while ((n + 1) * (n + 1) <= h) ++n;
+  const int r = h - n * n, c = r > n ? 1 : 0, b = r - c * (n + 1);
+  return ((n - b - c) & 1) | (b & 1) << 1 | c << 2;
+}
+
 // Layout of the scaled source copies (S32 / Sc64): the KH = nh(p) folded
 // coefficients in NP passes of 16 blocks of CP values, [pass][block][CP], every
 // block holding coefficients of one parity class (the parities of a, b, c), so
@@ -164,12 +172,40 @@ __host__ __device__ constexpr int sym_set(int m, int j) {
   return j < t ? j : j + 1;
 }
 
+// Variants of an orbit's operator (M2L): one per set of the axes, among those of m
+// that it does not reflect, on which the group's class has its offset 3 on the
+// negative side; 1, 2, 4 or 8 per orbit, 117 in all.
+constexpr int kSymVariants = 117;
+// E rows of a variant: character x at x * sym_es(p), coefficients g < K then zeros,
+// one zero slot at 8 * sym_es(p), zeros to whole 16-byte vectors.  The stride is
+// the one with the fewest LDS bank conflicts of the A operand's gathers (counted
+// for 4- and 8-byte values; 2.9 passes of 64 lanes at p = 6, 3.8 without padding).
+__host__ __device__ constexpr int sym_es(int p) {
+  return p <= 5 ? 80 : p == 6 ? 96 : p == 7 ? 144 : 176;
+}
+__host__ __device__ constexpr int sym_elen(int p, int bytes) {
+  return (8 * sym_es(p) + 1 + 16 / bytes - 1) / (16 / bytes) * (16 / bytes);
+}
+// M2L sums tap by tap up to p = 4 and by orbits from p = 5.  An orbit's loads,
+// butterflies and barrier cost the same at any order, its products grow with p^4:
+// 64^3 + 1 level in FP32, taps / orbits 77 / 90 us at p = 4, 105 / 103 at p = 5,
+// 150 / 126 at p = 6, 329 / 211 at p = 8 (FP64: 115 / 131, 167 / 167, 277 / 203).  The
+// line is one of orders alone: a batch and its members' own plans, of other sizes,
+// give the same bits.
+__host__ __device__ constexpr bool m2l_by_taps(int p) { return p <= 4; }
+// Columns of an M2L tile; by orbits, two tiles of 16 per wave share the A operand
+// where both sets of U fit the LDS.
+constexpr int kM2LBlock = 512;
+__host__ __device__ constexpr int m2l_cols(int p, int bytes) {
+  return !m2l_by_taps(p) && bytes == 4 && p <= 6 ? 32 : 16;
+}
+
 // D~ rows of one source offset in the layout the MFMA kernels stage in LDS:
 // row o (child octant) at o * dstage_ks(p), coefficients g < K then zeros up
 // to the stride, one zero slot at 8 * dstage_ks(p), zero padding to whole
 // 16-byte vectors for every lane of a wave.  Copied to LDS as is.  The row
 // stride is chosen per order (at least K rounded up to 4, same padded length)
-// to spread the A-operand gathers of M2P and M2L (8 rows x derivative-shifted
+// to spread the A-operand gathers (8 rows x derivative-shifted
 // coefficient indices per lane) over the LDS banks; chosen by counting bank
 // conflicts of those offset tables for 32- and 64-bank LDS models.
 __host__ __device__ constexpr int dstage_ks(int p) {
@@ -253,6 +289,7 @@ struct TablesDev {
   const T* l2lw = nullptr;    // [8][p+1][K] L2L weights 2^(-1-|b|) u^g/g! per child octant and |b|
   const T* l2p = nullptr;     // [8][4][K] L2P weights (phi, ax, ay, az) per child octant
   const T* nearA = nullptr;   // [2][near_ksteps / VW][64][VW] near-field operator, MFMA A layout
+  const T* symE = nullptr;    // [kSymVariants][sym_elen] E rows of the orbits (M2L)
   const T* symA = nullptr;    // [8 m][NP][7][8][64][CP] M2P operator per orbit, pass and character (SymLayout)
   const T* adjNearA = nullptr;  // [216][64] transposed same-level near field (adjoint), MFMA A layout
 };
@@ -290,10 +327,11 @@ struct MfmaTiles {
 };
 
 struct MfmaTables {
-  const int32_t* taps = nullptr;      // [8][189] per parity class: e | o' << 5 | d_index << 8
   const int8_t* symtaps = nullptr;    // [8][56][8] per parity class and orbit: its sources' fathers (neighbour e)
-  const int16_t* m2l_off = nullptr;   // [steps][64] sD offsets of the M2L A operand
-  const int32_t* m2l_tinfo = nullptr; // [NT][2] k-steps and first step of each M2L row tile
+  const int* symvar = nullptr;        // [8][56] per parity class and orbit: its variant
+  const int32_t* taps = nullptr;      // [8][189] per parity class: e | o' << 5 | d_index << 8
+  const int16_t* m2l_off = nullptr;   // places of M2L's A operand: [steps][64] in D~ rows (taps), or
+                                      // [8][steps][64] in a variant's E rows, per character (orbits)
 };
 
 // Launchers (afmm_kernels.hip).  All return hipGetLastError() of the launch.
@@ -376,7 +414,7 @@ __host__ __device__ constexpr int m2p_cols(int p, int bytes) { return 16 * m2p_q
 __host__ __device__ constexpr int m2p_fathers(int p, int bytes) { return m2p_quads(p, bytes) == 3 ? 200 : 240; }
 // MFMA launches over a contiguous range [t0, t0 + n) of tile records; each
 // record is (target level, NC groups).  lvs is the device array of LevelDev.
-hipError_t launch_m2l_taps(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
+hipError_t launch_m2l(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
                            const LevelDev* lvs, const TablesDev<float>& t32, const TablesDev<double>& t64,
                            hipStream_t st);
 hipError_t launch_l2l(int p, bool fp32, bool parent_fp32, bool has_parent, int nsplit, const int32_t* grp, int ngrp,

@@ -488,7 +488,7 @@ __global__ __launch_bounds__(kBlock) void k_l2l(const int32_t* __restrict__ grp,
 }
 
 // ---------------------------------------------------------------------------
-// Tap pipeline of M2L.  A block owns 16 groups of one parity class at one
+// Tap pipeline of M2L up to p = 4.  A block owns 16 groups of one parity class at one
 // level.  For each of the 189 taps:
 //   sB[k][n] = folded coefficient k of the tap's source of group n (its mass for
 //             a leaf source, 0 when there is none): thread (n, q) loads block q
@@ -1042,7 +1042,7 @@ void k_m2p(const int32_t* __restrict__ tiles, int ntiles, int nsplit, const int8
 }
 
 // ---------------------------------------------------------------------------
-// M2L tap sums at the FMM levels (Alg. 3 without the ShiftLocal term, which
+// M2L tap sums up to p = 4 (Alg. 3 without the ShiftLocal term, which
 // the L2L chain adds afterwards): rows R = 8 b + o (local coefficient b, child
 // octant o; b in degree order, so 16-row tile T starts at coefficient 2T and
 // needs only the first ks(T)*4 multipole coefficients: the triangle
@@ -1084,9 +1084,10 @@ constexpr M2LPlan<P> make_m2l_plan() {
 
 // B of one M2L tap in LDS, sB[k][n] (fragment order of the k-steps): thread (n =
 // t & 15, q = t >> 4) loads the vectors of block q of column n's source row and
-// stores each value at its coefficient.  Branch-free: a missing or leaf source
-// reads the zero row, and every thread loads a mass (cell 0 when the source is
-// no leaf), which the threads of block 0 store for a leaf source.
+// stores each value at its coefficient.  A missing or leaf source reads the zero
+// row; the threads of block 0 store a leaf's mass, which was put into LDS with the
+// source table (loaded in the tap loop by every thread, it took 40% of the kernel
+// at p = 1).
 template <typename T, int P>
 struct BStage {
   using SL = SymLayout<P, (int)sizeof(T)>;
@@ -1094,37 +1095,39 @@ struct BStage {
   typedef typename VecN<T, CP>::type V;
   struct Regs {
     V v[NP];
-    double m;
-    bool leaf;
+    int leaf;  // place of the leaf's mass, or -1
   };
   gptr<T> base;
-  gptr<double> mass;
+  const int* src;    // [tap][column]
+  const T* mass;     // [tap][column]
   int zrow;
-  bool first;
-  int at[NP * CP];  // sB slots of the thread's values
-  __device__ inline void init(const LevelDev& lv) {
+  int at[NP * CP];   // sB slots of the thread's values
+  __device__ inline void init(const LevelDev& lv, const int* s, const T* m) {
     static constexpr SL sl{};
     const int t = threadIdx.x, n = t & 15, q = t >> 4;
     zrow = lv.nref;
-    first = q == 0;
     base = as_global(level_S<T>(lv)) + q * CP;
-    mass = as_global(lv.mass);
+    src = s;
+    mass = m;
 #pragma unroll
     for (int i = 0; i < NP * CP; ++i) {
       const int h = sl.coef[(i / CP * kSymBlocks + q) * CP + i % CP];
       at[i] = (h >= 0 ? h : TapStage<T, P>::KP) * 16 + n;
     }
   }
-  __device__ inline void load(int sr, Regs& r) const {
-    gptr<T> src = base + (size_t)(sr >= 0 ? sr : zrow) * SL::ROW;
+  // tap k, or none (k < 0)
+  __device__ inline void load(int k, Regs& r) const {
+    const int i = k * 16 + ((int)threadIdx.x & 15), sr = k >= 0 ? src[i] : -1;
+    gptr<T> row = base + (size_t)min((uint32_t)sr, (uint32_t)zrow) * SL::ROW;
 #pragma unroll
-    for (int s = 0; s < NP; ++s) r.v[s] = load_vec<T, CP>(src + s * kSymBlocks * CP);
-    r.m = mass[sr <= -2 ? -2 - sr : 0];
-    r.leaf = sr <= -2;
+    for (int s = 0; s < NP; ++s) r.v[s] = load_vec<T, CP>(row + s * kSymBlocks * CP);
+    r.leaf = threadIdx.x < 16 && sr <= -2 ? i : -1;
   }
   __device__ inline void store(T* sB, const Regs& r) const {
+    T v0 = r.v[0][0];
+    if (r.leaf >= 0) v0 = mass[r.leaf];
 #pragma unroll
-    for (int i = 0; i < NP * CP; ++i) sB[at[i]] = i == 0 && first && r.leaf ? (T)r.m : r.v[i / CP][i % CP];
+    for (int i = 0; i < NP * CP; ++i) sB[at[i]] = i == 0 ? v0 : r.v[i / CP][i % CP];
   }
 };
 
@@ -1149,7 +1152,7 @@ __device__ inline void load_dstage_nb(int code, const T* __restrict__ Dst, typen
 // (sSrcT) before the loop.
 template <typename T, int P, int H>
 __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const int16_t* __restrict__ aoff,
-                                const int* sF, const int* sSrcT, T (*sB)[TapStage<T, P>::SB],
+                                const int* sF, T (*sB)[TapStage<T, P>::SB],
                                 T (*sD)[TapStage<T, P>::SDP], const BStage<T, P>& bs,
                                 const T* __restrict__ Dst, gptr<int32_t> rank0, gmut<T> Lout, int ldl) {
   using TS = TapStage<T, P>;
@@ -1161,7 +1164,7 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
   constexpr int NS = PL.steps[H];
   constexpr int KBH = PL.kbmax[H];
   constexpr int ND = (TS::NDV + kBlock - 1) / kBlock;
-  const int t = threadIdx.x, lane = t & 63, krow = lane >> 4, n = lane & 15;
+  const int lane = threadIdx.x & 63, krow = lane >> 4;
   int off[NS > 0 ? NS : 1];
   {
     int s = 0;
@@ -1183,14 +1186,14 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
   {
     const int k1 = nt > 1 ? 1 : 0;
     load_dstage_nb<T, P, kBlock>(tp[k1], Dst, vDX);
-    bs.load(nt > 1 ? sSrcT[16 + n] : -1, vBX);
+    bs.load(nt > 1 ? 1 : -1, vBX);
   }
   // one tap: load tap k + 2 into (vDn, vBn), MFMAs of tap k from LDS buffer
   // b, store tap k + 1 from (vDc, vBc) into buffer b ^ 1
   auto step = [&](int k, int b, V* vDc, const BV& vBc, V* vDn, BV& vBn) {
     const int k2 = k + 2 < nt ? k + 2 : nt - 1;
     load_dstage_nb<T, P, kBlock>(tp[k2], Dst, vDn);
-    bs.load(k + 2 < nt ? sSrcT[k2 * 16 + n] : -1, vBn);
+    bs.load(k + 2 < nt ? k2 : -1, vBn);
     __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the MFMAs
     const T* B = sB[b] + lane;
     const T* D = sD[b];
@@ -1231,24 +1234,20 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
   }
 }
 
-// Occupancy floor of k_m2l_mfma: for FP32 up to p = 6 the kernel fits 128
-// registers without spilling, so its LDS (4 blocks per CU) sets 4 waves per
-// SIMD; left to itself the compiler takes about 176 registers and 2 waves,
-// and the M2L launches ran about 8% slower.  At p = 8 (FP32) a floor of 2
-// waves (256 registers, 20 bytes of spill, against 348 registers and 1 wave)
-// ran 28% faster.  Other instantiations keep the compiler's choice (p = 7
-// already runs 2 waves, and a floor of 3 spills; FP64 spills at any floor that
-// would raise its occupancy).
-template <typename T, int P>
-constexpr int m2l_min_waves() { return sizeof(T) != 4 ? 1 : P <= 6 ? 4 : P == 8 ? 2 : 1; }
+// Occupancy floor of k_m2l_taps: the FP32 kernel fits 128 registers without
+// spilling, so its LDS (4 blocks per CU) sets 4 waves per SIMD; left to itself the
+// compiler takes about 176 registers and 2 waves, and the M2L launches ran about
+// 8% slower.  FP64 keeps the compiler's choice (it spills at a higher floor).
+template <typename T>
+constexpr int m2l_min_waves() { return sizeof(T) == 4 ? 4 : 1; }
 
 // One block = one tile (16 groups) and one of `nsplit` contiguous tap ranges.
 // With nsplit == 1 the sums go to the front of the rows of L; otherwise to the
 // level's partial buffer [nsplit][nref][KH], reduced in fixed order by k_l2l,
 // which also forms the coefficients that follow from these.
 template <typename T, int P>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(m2l_min_waves<T, P>())))
-void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(m2l_min_waves<T>())))
+void k_m2l_taps(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
                                                      const int32_t* __restrict__ taps,
                                                      const int16_t* __restrict__ aoff,
                                                      const LevelDev* __restrict__ lvs, const T* __restrict__ Dst) {
@@ -1258,8 +1257,9 @@ void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
   __shared__ T sB[2][TS::SB];
   __shared__ __align__(16) T sD[2][TS::SDP];
   __shared__ int sF[16];
-  __shared__ int sCB[16 * 27];
   __shared__ int sSrcT[kTaps * 16];
+  __shared__ T sM[kTaps * 16];
+  int* sCB = (int*)sM;  // [16][27], until the sources are known
   __shared__ int sCode[kTaps];
   __shared__ int sNt;
   const int item = xcd_tile(ntiles * nsplit);
@@ -1289,13 +1289,18 @@ void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
   __syncthreads();
   const int nt = sNt;
   const int* tp = sCode;
+  for (int i = t; i < nt * 16; i += kBlock) {
+    const int sr = sSrcT[i];
+    sM[i] = (T)as_global(lv1.mass)[sr <= -2 ? -2 - sr : 0];
+  }
   BS bs;
-  bs.init(lv1);
+  bs.init(lv1, sSrcT, sM);
+  __syncthreads();
   {
     typename Vec16<T>::type vD[ND];
     typename BS::Regs vB;
     load_dstage_nb<T, P, kBlock>(tp[0], Dst, vD);
-    bs.load(sSrcT[lane & 15], vB);
+    bs.load(0, vB);
     bs.store(sB[0], vB);
     store_dstage<T, P, kBlock>(sD[0], vD);
   }
@@ -1305,10 +1310,424 @@ void k_m2l_mfma(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
   gptr<int32_t> rank0 = as_global(lv0.rank);
   // every wave runs the same number of barriers (one per tap)
   switch (w) {
-    case 0: m2l_part<T, P, 0>(tp, nt, aoff, sF, sSrcT, sB, sD, bs, Dst, rank0, Lout, ldl); break;
-    case 1: m2l_part<T, P, 1>(tp, nt, aoff, sF, sSrcT, sB, sD, bs, Dst, rank0, Lout, ldl); break;
-    case 2: m2l_part<T, P, 2>(tp, nt, aoff, sF, sSrcT, sB, sD, bs, Dst, rank0, Lout, ldl); break;
-    default: m2l_part<T, P, 3>(tp, nt, aoff, sF, sSrcT, sB, sD, bs, Dst, rank0, Lout, ldl); break;
+    case 0: m2l_part<T, P, 0>(tp, nt, aoff, sF, sB, sD, bs, Dst, rank0, Lout, ldl); break;
+    case 1: m2l_part<T, P, 1>(tp, nt, aoff, sF, sB, sD, bs, Dst, rank0, Lout, ldl); break;
+    case 2: m2l_part<T, P, 2>(tp, nt, aoff, sF, sB, sD, bs, Dst, rank0, Lout, ldl); break;
+    default: m2l_part<T, P, 3>(tp, nt, aoff, sF, sB, sD, bs, Dst, rank0, Lout, ldl); break;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// M2L sums from p = 5 (Alg. 3 without the ShiftLocal term, which the L2L chain adds
+// afterwards), by the reflections of the axes as in M2P: with
+//   U_chi[a] = sum over an orbit's sources of chi(sigma) sigma^a S_sigma[a]
+// the children's local expansions are
+//   L_o[b] = tau^b sum_chi chi(tau) Lambda_chi[b],
+//   Lambda_chi[b] = sum over orbits and |a| + |b| <= p of E_(chi ^ par b)[a + b] U_chi[a],
+// par b the parities of b.  56 orbits x 8 characters x 532 products per group at
+// p = 6 instead of 189 sources x 8 children x 532.
+//
+// A block takes NC groups of one parity class and a range of the orbits; wave chi
+// forms Lambda_chi of all its columns.  Per orbit, thread (pass, block q, column)
+// holds block q (SymLayout) of the orbit's sources of one column; all coefficients
+// of a block have one parity, so butterflies in registers make the distinct U of
+// the orbit (one per character of its reflected axes), which go to LDS in the
+// order of the products' k-steps.  The loads of the next orbit are in flight
+// during the products of one.  The E rows of an orbit (8 x K values, with the
+// signs of the class) are staged in LDS; a lane gathers its A operand from there
+// through offsets that depend on the character only (registers).
+// Products, FP32: 4 x 4 x 1 blocks (16 per instruction: 4 k x 4 column quads), the
+// row quad picked by the broadcast of A, so that a row quad of degree n runs only
+// the k-steps below degree p - n: 46 x 256 products per character and column tile
+// at p = 6 where 16-row tiles take 18 x 1024.  FP64: 16 x 16 x 4.
+// In FP32 the first k-step (monopole and dipole terms, by far the largest) sums
+// into an accumulator of its own in the lowest rows: the terms of orders >= 2 are
+// many, and below half a unit in the last place of the running sum they were
+// rounded away on one side (mean error of the potential 7e-7 at p = 6, 0.4e-7 apart).
+// Bound by instruction issue: one block of 8 waves per CU, whose butterflies,
+// addresses and LDS traffic cost about as much as the products, and the barrier of
+// every orbit.  A wider tile (or a second block) does not fit the registers (253 at
+// p = 6 FP32); a second orbit's loads in flight changed nothing.  Tap by tap / by
+// orbits: 8.08M leaves p = 6 FP32 2.60 / 2.04 ms, 287,680 leaves p = 6 FP64 272 / 184
+// us, 8 hierarchies p = 8 FP32 720 / 457 us.
+__device__ inline f32x4 mfma4q(int quad, float a, float b, f32x4 c) {
+  switch (quad) {  // constant at every call
+    case 0: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 2, 0, 0);
+    case 1: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 2, 1, 0);
+    case 2: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 2, 2, 0);
+    default: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 2, 3, 0);
+  }
+}
+
+template <typename T, int P>
+struct M2L {
+  using SL = SymLayout<P, (int)sizeof(T)>;
+  using V16 = typename Vec16<T>::type;
+  static constexpr int CP = SL::CP, NP = SL::NP, ROW = SL::ROW;
+  static constexpr int KH = nh(P), KB = (KH + 3) / 4, RT = (KH + 15) / 16;
+  static constexpr int NC = m2l_cols(P, (int)sizeof(T)), CT = NC / 16;
+  static constexpr bool QUADS = sizeof(T) == 4;
+  static constexpr int UT = KB * 64 + 16;             // U of one column tile (the tiles 16 banks apart)
+  static constexpr int UP = CT * UT + 64;             // U of one character, then places for the unused slots
+  static constexpr int ES = sym_es(P), EL = sym_elen(P, (int)sizeof(T));
+  static constexpr int NIT = NP * 16 * NC;            // (pass, block, column)
+  static constexpr int NI = (NIT + kM2LBlock - 1) / kM2LBlock;
+  static constexpr int VW = 16 / (int)sizeof(T), NEV = EL / VW;  // vectors of the E rows
+  static constexpr int NE = (NEV + kM2LBlock - 1) / kM2LBlock;
+  static constexpr int SRC = 216 * NC;
+  // two sets of U and E where they fit the LDS
+  static constexpr int NBUF = 2 * (8 * UP + EL) * (int)sizeof(T) + (SRC + 9 * NC) * 4 <= 160 * 1024 ? 2 : 1;
+  static_assert(NIT % 64 == 0 && kM2LBlock % (16 * NC) == 0, "whole waves, one block q per thread");
+  typedef typename VecN<T, CP>::type V;
+  struct Lds {  // E first: the gathers' places and the buffer's fit the instruction's offset
+    T e[NBUF][EL];
+    int src[SRC];       // [m][neighbour][column]: rank, or -2 - cell of a leaf, or -1
+    int F[NC];
+    int rank0[8 * NC];  // [column][child]
+    T u[NBUF][8 * UP];
+  };
+  static constexpr int LS = NC + 1;  // Lambda's row stride in LDS
+  static_assert(8 * KH * LS <= NBUF * 8 * UP, "Lambda in the place of U");
+  // k-steps of the row quad i of row tile r (0: no rows)
+  static constexpr int ks(int r, int i) { return 16 * r + 4 * i < KH ? (nh(P - h_deg(16 * r + 4 * i)) + 3) / 4 : 0; }
+  static constexpr int steps() {
+    int s = 0;
+    for (int r = 0; r < RT; ++r) s += ks(r, 0);
+    return s;
+  }
+  static constexpr int NS = steps();
+
+  Lds& l;
+  gptr<T> S;
+  gptr<double> mass1;
+  const T* __restrict__ symE;
+  sptr<uint64_t> taps;
+  sptr<int> var;
+  uint64_t code;         // neighbours of the next orbit's sources, a byte each
+  int vr;                // and its variant
+  int zrow, col, q, s0, wave;
+  bool on;               // the thread has a first item
+  T sg[3];
+  int at[NI * CP];       // places in U of the thread's values
+  struct Regs {          // an orbit on its way
+    V v[NI][8];
+    double mm[8];
+    unsigned leaf;
+    V16 e[NE];
+  };
+
+  static __device__ inline int set_of(int g) {
+    const int m = g / 7;
+    return sym_axes(sym_set(m, g - 7 * m));
+  }
+  // sources 2^(NB-1) .. 2^NB - 1 of an orbit (NB = 0: source 0).  The steps of nb
+  // reflections nest, so that a value has one register whatever the orbit: copies
+  // behind a branch would wait for the loads
+  template <int NB>
+  __device__ inline void load_rows(int nb, const int* sc, Regs& r) const {
+    if (nb < NB) return;
+    constexpr int I0 = NB ? 1 << (NB - 1) : 0, I1 = 1 << NB;
+#pragma unroll
+    for (int i = I0; i < I1; ++i) {
+      gptr<T> row = S + (size_t)min((uint32_t)sc[i], (uint32_t)zrow) * ROW;  // no source or a leaf: the zero row
+#pragma unroll
+      for (int k = 0; k < NI; ++k) {
+        const int s = k * (kM2LBlock / (16 * NC));
+        r.v[k][i] = load_vec<T, CP>(row + (k == 0 || s0 + s < NP ? s : 0) * kSymBlocks * CP);
+      }
+    }
+    if (wave == 0) {  // its lanes hold the monopoles
+#pragma unroll
+      for (int i = I0; i < I1; ++i) {
+        r.mm[i] = mass1[sc[i] <= -2 ? -2 - sc[i] : 0];
+        r.leaf |= (unsigned)(sc[i] <= -2) << i;
+      }
+    }
+    if constexpr (NB < 3) load_rows<NB + 1>(nb, sc, r);
+  }
+  // scalars of orbit g, read one orbit ahead of their use
+  __device__ inline void next(int g) {
+    code = taps[g];
+    vr = var[g];
+  }
+  // loads of orbit g
+  __device__ inline void load(int g, Regs& r) const {
+    gptr<V16> e = (gptr<V16>)as_global(symE + (size_t)vr * EL);
+#pragma unroll
+    for (int k = 0; k < NE; ++k) r.e[k] = e[min((int)threadIdx.x + kM2LBlock * k, NEV - 1)];
+    if (on) {
+      r.leaf = 0;
+      const int base = g / 7 * 27 * NC + col;
+      int sc[8];  // all at once (bytes past the orbit's sources are 0)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) sc[i] = l.src[base + ((int)(code >> (8 * i)) & 31) * NC];
+      load_rows<0>(sym_bits(set_of(g)), sc, r);
+    }
+  }
+  template <int B>
+  static __device__ inline void stage(Regs& r, int i0, int n, T s) {  // butterflies of index bit B on values i0 .. i0 + n - 1
+#pragma unroll
+    for (int k = 0; k < NI; ++k)
+#pragma unroll
+      for (int i = i0; i < i0 + n; ++i)
+        if (!(i >> B & 1)) {
+          const V x = r.v[k][i], y = r.v[k][i | 1 << B];
+#pragma unroll
+          for (int e = 0; e < CP; ++e) {
+            r.v[k][i][e] = x[e] + s * y[e];
+            r.v[k][i | 1 << B][e] = x[e] - s * y[e];
+          }
+        }
+  }
+  __device__ inline T axis_sign(int rest) const {  // of the lowest axis of the set
+    const T x0 = sg[0], x1 = sg[1], x2 = sg[2];
+    return rest & 1 ? x0 : rest & 2 ? x1 : x2;
+  }
+  template <int I0, int I1>
+  __device__ inline void put_u(T* u, const Regs& r) const {
+#pragma unroll
+    for (int k = 0; k < NI; ++k)
+      if (k == 0 || s0 + k * (kM2LBlock / (16 * NC)) < NP) {
+#pragma unroll
+        for (int i = I0; i < I1; ++i)
+#pragma unroll
+          for (int e = 0; e < CP; ++e) u[i * UP + at[k * CP + e]] = r.v[k][i][e];
+      }
+  }
+  // the loaded orbit g into LDS
+  __device__ inline void put(int g, int buf, Regs& r) const {
+#pragma unroll
+    for (int k = 0; k < NE; ++k)
+      if ((int)threadIdx.x + kM2LBlock * k < NEV) ((V16*)l.e[buf])[threadIdx.x + kM2LBlock * k] = r.e[k];
+    if (!on) return;
+    T* u = l.u[buf];
+    const int pt = set_of(g), nb = sym_bits(pt);
+    if (wave == 0) {
+      const unsigned lf = (int)threadIdx.x < NC ? r.leaf : 0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (lf >> i & 1) r.v[0][i][0] = (T)r.mm[i];
+    }
+    const T t0 = axis_sign(pt), t1 = axis_sign(pt & (pt - 1)), t2 = sg[2];
+    if (nb >= 1) {
+      stage<0>(r, 0, 2, t0);
+      if (nb >= 2) {
+        stage<0>(r, 2, 2, t0);
+        stage<1>(r, 0, 4, t1);
+        if (nb >= 3) {
+          stage<0>(r, 4, 4, t0);
+          stage<1>(r, 4, 4, t1);
+          stage<2>(r, 0, 8, t2);
+          put_u<4, 8>(u, r);
+        }
+        put_u<2, 4>(u, r);
+      }
+      put_u<1, 2>(u, r);
+    }
+    put_u<0, 1>(u, r);
+  }
+};
+
+// One block = one tile and one of `nsplit` contiguous ranges of the orbits.  With
+// nsplit == 1 the sums go to the front of the rows of L; otherwise to the level's
+// partial buffer [nsplit][nref][KH], reduced in fixed order by k_l2l, which also
+// forms the coefficients that follow from these.
+template <typename T, int P>
+__global__ __launch_bounds__(kM2LBlock)
+void k_m2l(const int32_t* __restrict__ tiles, int ntiles, int nsplit, const int8_t* __restrict__ taps,
+           const int* __restrict__ var, const int16_t* __restrict__ aoff, const LevelDev* __restrict__ lvs,
+           const T* __restrict__ symE) {
+  using ML = M2L<T, P>;
+  using SL = typename ML::SL;
+  static constexpr SL sl{};
+  constexpr int NC = ML::NC, CT = ML::CT, RT = ML::RT, KB = ML::KB, KH = ML::KH;
+  __shared__ __align__(16) typename ML::Lds lds;
+  const int item = xcd_tile(ntiles * nsplit);
+  if (item >= ntiles * nsplit) return;
+  const int tile = item / nsplit, chunk = item - tile * nsplit;
+  const int t = threadIdx.x, lane = t & 63, chi = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int32_t* rec = tiles + (size_t)tile * (NC + 1);
+  const int f = rec[0];
+  const LevelDev lv0 = lvs[f], lv1 = lvs[f - 1], lv2 = lvs[f - 2];
+  if (t < NC) lds.F[t] = rec[1 + t];
+  for (int i = t; i < ML::NBUF * 8 * ML::UP; i += kM2LBlock) (&lds.u[0][0])[i] = 0;  // k-steps past the last coefficient
+  __syncthreads();
+  gptr<int32_t> refcell1 = as_global(lv1.refcell);
+  const int C = __builtin_amdgcn_readfirstlane(refcell1[lds.F[0]] & 7);
+  // sources of the columns: the 8 children of each neighbour of their fathers
+  for (int i = t; i < 27 * NC; i += kM2LBlock) {
+    const int e = i / NC, F = lds.F[i - e * NC];
+    const int Q = F >= 0 ? as_global(lv2.nbr)[(size_t)(refcell1[F] >> 3) * 27 + e] : -1;
+    const int rQ = Q >= 0 ? as_global(lv2.rank)[Q] : -1;
+    typedef int i32x4 __attribute__((ext_vector_type(4)));
+    gptr<i32x4> rk = (gptr<i32x4>)(as_global(lv1.rank) + 8 * max(rQ, 0));
+    const i32x4 lo = rk[0], up = rk[1];
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+      const int r = o < 4 ? lo[o & 3] : up[o & 3];
+      lds.src[(o ^ C) * 27 * NC + i] = rQ < 0 ? -1 : r >= 0 ? r : -2 - (8 * rQ + o);
+    }
+  }
+  for (int i = t; i < 8 * NC; i += kM2LBlock) {
+    const int F = lds.F[i >> 3];
+    lds.rank0[i] = F >= 0 ? as_global(lv0.rank)[8 * F + (i & 7)] : -1;
+  }
+  ML m{lds};
+  m.S = as_global(level_S<T>(lv1)) + (t / (16 * NC) * kSymBlocks + (t / NC & 15)) * ML::CP;
+  m.mass1 = as_global(lv1.mass);
+  m.symE = symE;
+  m.wave = chi;
+  m.taps = (sptr<uint64_t>)taps + C * kSymOrbits;
+  m.var = (sptr<int>)var + C * kSymOrbits;
+  m.zrow = lv1.nref;
+  m.col = t % NC;
+  m.q = t / NC & 15;
+  m.s0 = t / (16 * NC);
+  m.on = 64 * chi < ML::NIT;
+  {
+    const int par = sl.par[m.q];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) m.sg[i] = par >> i & 1 ? (T)-1 : (T)1;
+#pragma unroll
+    for (int k = 0; k < ML::NI; ++k) {
+      const int s = m.s0 + k * (kM2LBlock / (16 * NC));
+#pragma unroll
+      for (int e = 0; e < ML::CP; ++e) {
+        const int h = s < ML::NP ? sl.coef[(s * kSymBlocks + m.q) * ML::CP + e] : -1;
+        m.at[k * ML::CP + e] = h < 0 ? CT * ML::UT + lane : (m.col >> 4) * ML::UT + (h >> 2) * 64 + (h & 3) * 16 + (m.col & 15);
+      }
+    }
+  }
+  int off[ML::NS];
+#pragma unroll
+  for (int i = 0; i < ML::NS; ++i) off[i] = as_global(aoff)[(chi * ML::NS + i) * 64 + lane];
+  typename Acc4<T>::type acc[RT][ML::QUADS ? 4 : 1][CT], hi[CT];
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    hi[c] = {0, 0, 0, 0};
+#pragma unroll
+    for (int r = 0; r < RT; ++r)
+#pragma unroll
+      for (int i = 0; i < (ML::QUADS ? 4 : 1); ++i) acc[r][i][c] = {0, 0, 0, 0};
+  }
+  const int g0 = chunk * kSymOrbits / nsplit, g1 = (chunk + 1) * kSymOrbits / nsplit;
+  m.next(g0);
+  typename ML::Regs rg;
+  rg.leaf = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    rg.mm[i] = 0;
+#pragma unroll
+    for (int k = 0; k < ML::NI; ++k) rg.v[k][i] = typename ML::V{};
+  }
+  __syncthreads();
+  m.load(g0, rg);
+  m.next(min(g0 + 1, g1 - 1));
+  m.put(g0, 0, rg);
+  __syncthreads();
+  auto step = [&](int g, int buf) {
+    if (g + 1 < g1) m.load(g + 1, rg);
+    m.next(min(g + 2, g1 - 1));
+    __builtin_amdgcn_sched_barrier(0);  // keep the loads ahead of the products
+    // the character restricted to the orbit's axes
+    const int pt = ML::set_of(g);
+    int u = 0, bit = 0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (pt >> i & 1) u |= (chi >> i & 1) << bit++;
+    const T* U = lds.u[buf] + u * ML::UP + lane;
+    const T* E = lds.e[buf];
+    int s = 0;
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      if (ML::NI > 1 && kb % 2 == 0) __builtin_amdgcn_sched_barrier(0);  // LDS reads hoisted further spill
+      T b[CT];
+#pragma unroll
+      for (int c = 0; c < CT; ++c) b[c] = U[c * ML::UT + kb * 64];
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        if (kb >= ML::ks(r, 0)) continue;
+        const T a = E[off[s++]];
+        if constexpr (ML::QUADS) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (kb < ML::ks(r, i)) {
+#pragma unroll
+              for (int c = 0; c < CT; ++c) {
+                auto& sum = r == 0 && i == 0 && kb > 0 ? hi[c] : acc[r][i][c];
+                sum = mfma4q(i, a, b[c], sum);
+              }
+            }
+        } else {
+#pragma unroll
+          for (int c = 0; c < CT; ++c) acc[r][0][c] = mfma16(a, b[c], acc[r][0][c]);
+        }
+      }
+    }
+    if (ML::NBUF == 1) __syncthreads();
+    if (g + 1 < g1) m.put(g + 1, ML::NBUF == 2 ? buf ^ 1 : 0, rg);
+    __syncthreads();
+  };
+  for (int g = g0; g < g1; ++g) {
+    step(g, 0);
+    if (ML::NBUF == 2 && ++g < g1) step(g, 1);
+  }
+  // Lambda to LDS, [chi][b][column]
+  T* lam = &lds.u[0][0] + chi * KH * ML::LS;
+  const int kq = lane >> 4;
+#pragma unroll
+  for (int c = 0; c < CT; ++c) {
+    if constexpr (ML::QUADS) {
+      acc[0][0][c] += hi[c];
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          if (ML::ks(r, i) == 0) continue;
+          // sum over the four k of the blocks: lane group kq keeps row kq
+          const auto x = acc[r][i][c];
+          const bool up = kq & 2, odd = kq & 1;
+          T y0 = up ? x[2] : x[0], y1 = up ? x[3] : x[1];
+          y0 += __shfl_xor(up ? x[0] : x[2], 32, 64);
+          y1 += __shfl_xor(up ? x[1] : x[3], 32, 64);
+          const T z = (odd ? y1 : y0) + __shfl_xor(odd ? y0 : y1, 16, 64);
+          const int h = 16 * r + 4 * i + kq;
+          if (h < KH) lam[h * ML::LS + 16 * c + (lane & 15)] = z;
+        }
+    } else {
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int h = 16 * r + acc_row<T>(kq, j);
+          if (h < KH) lam[h * ML::LS + 16 * c + (lane & 15)] = acc[r][0][c][j];
+        }
+    }
+  }
+  __syncthreads();
+  gmut<T> Lout = as_global_mut(nsplit > 1 ? (T*)lv0.Lpart + (size_t)chunk * lv0.nref * KH : level_L<T>(lv0));
+  const int ldl = nsplit > 1 ? KH : nmi(P);
+  for (int i = t; i < KH * NC; i += kM2LBlock) {
+    const int n = i / KH, h = i - n * KH;
+    T x[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) x[c] = (&lds.u[0][0])[(c * KH + h) * ML::LS + n];
+    // characters -> children (index y = ~o)
+#pragma unroll
+    for (int bit = 1; bit < 8; bit <<= 1)
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (!(c & bit)) {
+          const T y = x[c], z = x[c | bit];
+          x[c] = y + z;
+          x[c | bit] = y - z;
+        }
+    const int par = h_parity(h);
+#pragma unroll
+    for (int y = 0; y < 8; ++y) {
+      const int ry = lds.rank0[8 * n + (7 - y)];
+      if (ry >= 0) Lout[(size_t)ry * ldl + h] = __popc(par & y) & 1 ? -x[y] : x[y];
+    }
   }
 }
 
@@ -1599,15 +2018,19 @@ hipError_t launch_m2p(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int 
 
 template <typename T>
 static hipError_t m2l_dispatch(int p, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
-                               const LevelDev* lvs, const T* Dst, hipStream_t st) {
+                               const LevelDev* lvs, const TablesDev<T>& td, hipStream_t st) {
   const int items = n * nsplit;
-  const dim3 grid(8 * ((items + 7) / 8)), block(kBlock);
-  const int32_t* tl = mt.tiles + (size_t)t0 * 17;
+  const dim3 grid(8 * ((items + 7) / 8));
+  const int32_t* tl = mt.tiles + (size_t)t0 * (mt.nc + 1);
   switch (p) {
-#define AFMM_M2L(PP)                                                                                          \
-  case PP:                                                                                                    \
-    hipLaunchKernelGGL((k_m2l_mfma<T, PP>), grid, block, 0, st, tl, n, nsplit, tabs.taps, tabs.m2l_off, lvs, \
-                       Dst);                                                                                  \
+#define AFMM_M2L(PP)                                                                                              \
+  case PP:                                                                                                        \
+    if constexpr (m2l_by_taps(PP))                                                                                \
+      hipLaunchKernelGGL((k_m2l_taps<T, PP>), grid, dim3(kBlock), 0, st, tl, n, nsplit, tabs.taps, tabs.m2l_off, \
+                         lvs, td.Dstage);                                                                         \
+    else                                                                                                          \
+      hipLaunchKernelGGL((k_m2l<T, PP>), grid, dim3(kM2LBlock), 0, st, tl, n, nsplit, tabs.symtaps, tabs.symvar,  \
+                         tabs.m2l_off, lvs, td.symE);                                                             \
     break;
     AFMM_M2L(1) AFMM_M2L(2) AFMM_M2L(3) AFMM_M2L(4) AFMM_M2L(5) AFMM_M2L(6) AFMM_M2L(7) AFMM_M2L(8)
 #undef AFMM_M2L
@@ -1616,12 +2039,11 @@ static hipError_t m2l_dispatch(int p, const MfmaTiles& mt, int t0, int n, int ns
   return hipGetLastError();
 }
 
-hipError_t launch_m2l_taps(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
-                           const LevelDev* lvs, const TablesDev<float>& t32, const TablesDev<double>& t64,
-                           hipStream_t st) {
+hipError_t launch_m2l(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
+                      const LevelDev* lvs, const TablesDev<float>& t32, const TablesDev<double>& t64, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  if (fp32) return m2l_dispatch<float>(p, mt, t0, n, nsplit, tabs, lvs, t32.Dstage, st);
-  return m2l_dispatch<double>(p, mt, t0, n, nsplit, tabs, lvs, t64.Dstage, st);
+  if (fp32) return m2l_dispatch<float>(p, mt, t0, n, nsplit, tabs, lvs, t32, st);
+  return m2l_dispatch<double>(p, mt, t0, n, nsplit, tabs, lvs, t64, st);
 }
 
 template <typename T, typename TL>

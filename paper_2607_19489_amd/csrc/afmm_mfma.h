@@ -26,6 +26,8 @@ __device__ inline int acc_row(int krow, int r) { return sizeof(T) == 4 ? 4 * kro
 // always address global memory; the kernels load and store through these.
 template <typename T> using gptr = const __attribute__((address_space(1))) T*;
 template <typename T> using gmut = __attribute__((address_space(1))) T*;
+// tables that no kernel writes, at wave-uniform places: scalar loads
+template <typename T> using sptr = const __attribute__((address_space(4))) T*;
 template <typename T> __device__ inline gptr<T> as_global(const T* p) { return (gptr<T>)p; }
 template <typename T> __device__ inline gmut<T> as_global_mut(T* p) { return (gmut<T>)p; }
 
