@@ -509,15 +509,34 @@ __global__ void k_adj_tbT(LevelDev lvs, LevelDev lvt, T* __restrict__ tbT) {
   tbT[i] = (T)((j & 3) == 0 ? v : -v);
 }
 
-// Local-expansion bars of level f in T and in the lane-group layout of the
-// source copies (coefficient b at src_pos(b), zero padded).
+// Local-expansion bars of level f, folded onto the independent coefficients (the
+// products D~_(a+b) of the transposed M2L obey the harmonic relation in b), in T
+// and in lane-group layout (coefficient b at src_pos(b), zero padded).
 template <typename T, int P>
-__global__ void k_adj_lbarT(LevelDev lv, T* __restrict__ lT) {
-  constexpr int K = nmi(P), ROW = full_row(P, (int)sizeof(T));
+__global__ void k_adj_lbarT(LevelDev lv, CommonDev cm, T* __restrict__ lT) {
+  constexpr int K = nmi(P), KH = nh(P), ROW = folded_row(P, (int)sizeof(T));
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= lv.nref * ROW) return;
   const int r = i / ROW, b = i - r * ROW;   // b runs over coefficient indices 0 .. ROW-1
-  lT[(size_t)r * ROW + src_pos(b, (int)sizeof(T))] = b < K ? (T)lv.lbar[(size_t)r * K + b] : (T)0;
+  double v = 0.0;
+  if (b < KH)
+    for (int j = cm.fold_start[b]; j < cm.fold_start[b + 1]; ++j) v += cm.fold_u[j] * lv.lbar[(size_t)r * K + cm.fold_list[j]];
+  lT[(size_t)r * ROW + src_pos(b, (int)sizeof(T))] = (T)v;
+}
+
+// Coefficient a of a function that obeys the harmonic relation, from the
+// independent ones h(i): (i, j, k + 2m), k <= 1, is (-1)^m sum_r C(m, r) of
+// (i + 2r, j + 2(m - r), k).
+template <typename Get>
+__device__ inline double harmonic(const int8_t* __restrict__ mi, int a, Get h) {
+  const int n = mi[4 * a + 3], m = mi[4 * a + 2] >> 1;
+  const int i = n * n + (mi[4 * a + 2] & 1) * (n + 1) + mi[4 * a + 1] + 2 * m;
+  double v = h(i);
+  for (int r = 1, c = m; r <= m; ++r) {
+    v += c * h(i - 2 * r);
+    c = c * (m - r) / (r + 1);
+  }
+  return m & 1 ? -v : v;
 }
 
 // Per-block setup shared by both kernels: the 16 source cells, the child base
@@ -584,33 +603,35 @@ __device__ inline int adj_live_taps(int tb, int te, int* sTap, const int* sCB, c
   return cnt;
 }
 
-// Output rows of one 16-row tile: multipole-source bars of refined sources,
-// the monopole row of leaf sources into their mass bars; with a tap split,
-// the rows go to the block's partial set part[(chunk * ntiles + tile) * 16 + n][K]
-// instead, summed in order by k_adj_reduce.
-template <typename T, int K>
-__device__ inline void adj_write(const typename Acc4<T>::type& acc, int rt, int lane, int s, const LevelDev& lvs,
-                                 double* part) {
-  if (s < 0) return;
-  if (part) {
-    const int krow = lane >> 4;
+// Output of a tile, rows a of the independent coefficients: the others follow by
+// the harmonic relation, and the sums go to the multipole-source bars of refined
+// sources and, for leaf sources, the monopole row to their mass bars (the rows
+// change hands in LDS).  With a tap split the rows go to the block's partial set
+// part[(chunk * ntiles + tile) * 16 + n][KH] instead, summed in order by
+// k_adj_reduce.
+template <typename T, int P>
+__device__ inline void adj_write(const typename Acc4<T>::type* acc, int lane, const int* sS, const LevelDev& lvs,
+                                 const int8_t* __restrict__ mi, T* lds, double* part) {
+  constexpr int K = nmi(P), KH = nh(P), RT = (KH + 15) / 16;
+  static_assert(16 * KH <= 2 * dstage_len(P, (int)sizeof(T)), "rows in the place of the D~ stages");
+  const int krow = lane >> 4, n = lane & 15;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int a = 16 * rt + acc_row<T>(krow, r);
-      if (a < K) part[(size_t)(lane & 15) * K + a] = (double)acc[r];
+      if (a >= KH) continue;
+      if (!part) lds[n * KH + a] = acc[rt][r];
+      else if (sS[n] >= 0) part[(size_t)n * KH + a] = (double)acc[rt][r];
     }
-    return;
-  }
-  const int rs = lvs.rank[s];
-  const int krow = lane >> 4;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int a = 16 * rt + acc_row<T>(krow, r);
-    if (rs >= 0) {
-      if (a < K) lvs.sbar[(size_t)rs * K + a] += (double)acc[r];
-    } else if (a == 0) {
-      lvs.mbar[s] += (double)acc[r];
-    }
+  if (part) return;
+  __syncthreads();
+  for (int i = lane; i < 16 * K; i += 64) {
+    const int c = i / K, a = i - c * K, s = sS[c];
+    if (s < 0) continue;
+    const int rs = lvs.rank[s];
+    if (rs >= 0) lvs.sbar[(size_t)rs * K + a] += harmonic(mi, a, [&](int h) { return (double)lds[c * KH + h]; });
+    else if (a == 0) lvs.mbar[s] += (double)lds[c * KH];
   }
 }
 
@@ -622,9 +643,7 @@ __device__ inline void adj_write(const typename Acc4<T>::type& acc, int rt, int 
 // change a bit of the result).
 template <int P>
 __host__ __device__ constexpr bool adj_m2p_step_used(int rt, int kb) {
-  int d = 0;
-  while (nmi(d) <= 16 * rt) ++d;  // order of the tile's first row
-  return d < P || (kb & 3) == 0;
+  return h_deg(16 * rt) < P || (kb & 3) == 0;  // order of the tile's first row
 }
 
 // Transposed intermediate-field M2P: targets = leaf children (level ls + 1) of
@@ -635,8 +654,9 @@ __global__ __launch_bounds__(64) void k_adj_m2p_mfma(const int32_t* __restrict__
                                                      double* __restrict__ part, const int32_t* __restrict__ tapsT,
                                                      const uint8_t* __restrict__ live,
                                                      const int16_t* __restrict__ aoff, LevelDev lvp, LevelDev lvs,
-                                                     const T* __restrict__ tbT, const T* __restrict__ Dst) {
-  constexpr int K = nmi(P), RT = (K + 15) / 16;
+                                                     const T* __restrict__ tbT, const T* __restrict__ Dst,
+                                                     const int8_t* __restrict__ mi) {
+  constexpr int KH = nh(P), RT = (KH + 15) / 16;
   constexpr int SDP = dstage_len(P, (int)sizeof(T));
   constexpr int VW = 16 / (int)sizeof(T), NVB = 8 / VW, ND = (SDP / VW + 63) / 64;
   using V = typename Vec16<T>::type;
@@ -706,19 +726,21 @@ __global__ __launch_bounds__(64) void k_adj_m2p_mfma(const int32_t* __restrict__
       step(k + 1, 1, bB, bA);
     }
   }
-  const int s = sS[n];
-  double* pp = nsplit > 1 ? part + ((size_t)chunk * ntiles + tile) * 16 * K : nullptr;
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) adj_write<T, K>(acc[rt], rt, lane, s, lvs, pp);
+  double* pp = nsplit > 1 ? part + ((size_t)chunk * ntiles + tile) * 16 * KH : nullptr;
+  adj_write<T, P>(acc, lane, sS, lvs, mi, sD[0], pp);
 }
 
 // Transposed M2L: targets = refined children y (level ls + 1) of the groups
 // reading the source; for each tap and child octant o, A = D~_(a+b)(R~_o)
 // (triangle |a| + |b| <= p skipped at k-step granularity) and B = the local-
 // expansion bars of child o, b = 4 kb + g from the lane-group layout.
+// Bound by the MFMAs and the A gathers that feed them: on the (p+1)^2 independent
+// rows and columns a (tap, child) takes 18 steps at p = 6 where all K = 84 took 32
+// (26 and 36 in the transposed M2P, whose columns are the targets).  A gradient at
+// 3.1M leaves, p = 6 FP32 (forward and adjoint): 16.7 ms before, 14.5 now.
 template <int P>
 struct AdjM2LPlan {
-  static constexpr int RT = (nmi(P) + 15) / 16;
+  static constexpr int RT = (nh(P) + 15) / 16;
   int ks[RT] = {};
   int base[RT] = {};
   int total = 0;
@@ -728,9 +750,7 @@ template <int P>
 constexpr AdjM2LPlan<P> make_adj_m2l_plan() {
   AdjM2LPlan<P> pl{};
   for (int rt = 0; rt < AdjM2LPlan<P>::RT; ++rt) {
-    int d = 0;
-    while (nmi(d) <= 16 * rt) ++d;  // degree of the tile's first row
-    pl.ks[rt] = (nmi(P - d) + 3) / 4;
+    pl.ks[rt] = (nh(P - h_deg(16 * rt)) + 3) / 4;  // degree of the tile's first row
     pl.base[rt] = pl.total;
     pl.total += pl.ks[rt];
     if (pl.ks[rt] > pl.kbmax) pl.kbmax = pl.ks[rt];
@@ -744,11 +764,11 @@ __global__ __launch_bounds__(64) void k_adj_m2l_mfma(const int32_t* __restrict__
                                                      const uint8_t* __restrict__ live,
                                                      const int16_t* __restrict__ aoff, LevelDev lvp, LevelDev lvs,
                                                      LevelDev lvt, const T* __restrict__ lT,
-                                                     const T* __restrict__ Dst) {
-  constexpr int K = nmi(P), KS = dstage_ks(P), SDP = dstage_len(P, (int)sizeof(T));
+                                                     const T* __restrict__ Dst, const int8_t* __restrict__ mi) {
+  constexpr int KH = nh(P), KS = dstage_ks(P), SDP = dstage_len(P, (int)sizeof(T));
   constexpr AdjM2LPlan<P> PL = make_adj_m2l_plan<P>();
   constexpr int RT = AdjM2LPlan<P>::RT;
-  constexpr int VW = 16 / (int)sizeof(T), ROW = full_row(P, (int)sizeof(T));
+  constexpr int VW = 16 / (int)sizeof(T), ROW = folded_row(P, (int)sizeof(T));
   constexpr int NVB = (PL.kbmax + VW - 1) / VW, ND = (SDP / VW + 63) / 64;
   using V = typename Vec16<T>::type;
   __shared__ __align__(16) T sD[2][SDP];
@@ -789,7 +809,8 @@ __global__ __launch_bounds__(64) void k_adj_m2l_mfma(const int32_t* __restrict__
       for (int j = 0; j < NVB; ++j) b[j] = V{};
     }
   };
-  typename Acc4<T>::type acc[RT];
+  // the first k-step (monopole and dipole terms) apart in the lowest rows, as in M2L
+  typename Acc4<T>::type acc[RT], hi = {0, 0, 0, 0};
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) acc[rt] = {0, 0, 0, 0};
   if (nt > 0) {
@@ -813,7 +834,10 @@ __global__ __launch_bounds__(64) void k_adj_m2l_mfma(const int32_t* __restrict__
       for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
         for (int kb = 0; kb < PL.ks[rt]; ++kb)
-          acc[rt] = mfma16(D[off[PL.base[rt] + kb]], bc[kb / VW][kb % VW], acc[rt]);
+          {
+            auto& sum = rt == 0 && kb > 0 ? hi : acc[rt];
+            sum = mfma16(D[off[PL.base[rt] + kb]], bc[kb / VW][kb % VW], sum);
+          }
     };
     for (int k = 0; k < nt; ++k) {
       const int b = k & 1;
@@ -833,18 +857,17 @@ __global__ __launch_bounds__(64) void k_adj_m2l_mfma(const int32_t* __restrict__
       __syncthreads();
     }
   }
-  const int s = sS[n];
-  double* pp = nsplit > 1 ? part + ((size_t)chunk * ntiles + tile) * 16 * K : nullptr;
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) adj_write<T, K>(acc[rt], rt, lane, s, lvs, pp);
+  acc[0] += hi;
+  double* pp = nsplit > 1 ? part + ((size_t)chunk * ntiles + tile) * 16 * KH : nullptr;
+  adj_write<T, P>(acc, lane, sS, lvs, mi, sD[0], pp);
 }
 
 // Ordered sum of the tap-split partial sets of a transposed translation into
 // the source bars (thread = tile column x coefficient).
 template <int P>
 __global__ void k_adj_reduce(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
-                             const double* __restrict__ part, LevelDev lvs) {
-  constexpr int K = nmi(P);
+                             const double* __restrict__ part, LevelDev lvs, const int8_t* __restrict__ mi) {
+  constexpr int K = nmi(P), KH = nh(P);
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ntiles * 16 * K) return;
   const int col = i / K, a = i - col * K;
@@ -852,8 +875,11 @@ __global__ void k_adj_reduce(const int32_t* __restrict__ tiles, int ntiles, int 
   if (s < 0) return;
   const int rs = lvs.rank[s];
   if (rs < 0 && a != 0) return;
-  double v = 0.0;
-  for (int c = 0; c < nsplit; ++c) v += part[((size_t)c * ntiles * 16 + col) * K + a];
+  const double v = harmonic(mi, a, [&](int h) {
+    double x = 0.0;
+    for (int c = 0; c < nsplit; ++c) x += part[((size_t)c * ntiles * 16 + col) * KH + h];
+    return x;
+  });
   if (rs >= 0) lvs.sbar[(size_t)rs * K + a] += v;
   else lvs.mbar[s] += v;
 }
@@ -971,11 +997,11 @@ hipError_t launch_adj_out(int p, const LevelDev& lv1, const LevelDev& lv0, int h
 }
 
 static hipError_t adj_reduce(int p, const int32_t* tiles, int ntiles, int nsplit, const double* part,
-                             const LevelDev& lvs, hipStream_t st) {
+                             const LevelDev& lvs, const int8_t* mi, hipStream_t st) {
   if (nsplit <= 1) return hipGetLastError();
   const int n = ntiles * 16 * nmi(p);
 #define X(PP) \
-  case PP: hipLaunchKernelGGL((k_adj_reduce<PP>), dim3((n + 255) / 256), dim3(256), 0, st, tiles, ntiles, nsplit, part, lvs); break;
+  case PP: hipLaunchKernelGGL((k_adj_reduce<PP>), dim3((n + 255) / 256), dim3(256), 0, st, tiles, ntiles, nsplit, part, lvs, mi); break;
   AFMM_P_SWITCH(p, X)
 #undef X
   return hipGetLastError();
@@ -986,26 +1012,26 @@ static hipError_t adj_m2p_t(int p, const int32_t* tiles, int ntiles, int nsplit,
                             const uint8_t* live, double* part,
                             const int32_t* tapsT,
                             const int16_t* aoff, const LevelDev& lvp, const LevelDev& lvs, const LevelDev& lvt,
-                            const T* Dst, hipStream_t st) {
+                            const T* Dst, const CommonDev& cm, hipStream_t st) {
   T* tbT = (T*)lvs.tbT;
   hipLaunchKernelGGL((k_adj_tbT<T>), dim3((lvs.nref * 32 + 255) / 256), dim3(256), 0, st, lvs, lvt, tbT);
   if (xr.start[8] != ntiles * nsplit) return hipErrorInvalidValue;
   const dim3 grid(xr.grid()), block(64);
 #define X(PP) \
-  case PP: hipLaunchKernelGGL((k_adj_m2p_mfma<T, PP>), grid, block, 0, st, tiles, xr, nsplit, part, tapsT, live, aoff, lvp, lvs, (const T*)tbT, Dst); break;
+  case PP: hipLaunchKernelGGL((k_adj_m2p_mfma<T, PP>), grid, block, 0, st, tiles, xr, nsplit, part, tapsT, live, aoff, lvp, lvs, (const T*)tbT, Dst, cm.mi); break;
   AFMM_P_SWITCH(p, X)
 #undef X
-  return adj_reduce(p, tiles, ntiles, nsplit, part, lvs, st);
+  return adj_reduce(p, tiles, ntiles, nsplit, part, lvs, cm.mi, st);
 }
 
 hipError_t launch_adj_m2p_mfma(int p, bool fp32, const int32_t* tiles, int ntiles, int nsplit, const XcdRanges& xr,
                                const uint8_t* live, double* part, const int32_t* tapsT, const int16_t* aoff, const LevelDev& lvp,
                                const LevelDev& lvs, const LevelDev& lvt, const TablesDev<float>& t32,
-                               const TablesDev<double>& t64, hipStream_t st) {
+                               const TablesDev<double>& t64, const CommonDev& cm, hipStream_t st) {
   if (ntiles <= 0 || lvs.nref == 0) return hipSuccess;
   if (!live) return hipErrorInvalidValue;
-  if (fp32) return adj_m2p_t<float>(p, tiles, ntiles, nsplit, xr, live, part, tapsT, aoff, lvp, lvs, lvt, t32.Dstage, st);
-  return adj_m2p_t<double>(p, tiles, ntiles, nsplit, xr, live, part, tapsT, aoff, lvp, lvs, lvt, t64.Dstage, st);
+  if (fp32) return adj_m2p_t<float>(p, tiles, ntiles, nsplit, xr, live, part, tapsT, aoff, lvp, lvs, lvt, t32.Dstage, cm, st);
+  return adj_m2p_t<double>(p, tiles, ntiles, nsplit, xr, live, part, tapsT, aoff, lvp, lvs, lvt, t64.Dstage, cm, st);
 }
 
 template <typename T>
@@ -1013,30 +1039,30 @@ static hipError_t adj_m2l_t(int p, const int32_t* tiles, int ntiles, int nsplit,
                             const uint8_t* live, double* part,
                             const int32_t* tapsT,
                             const int16_t* aoff, const LevelDev& lvp, const LevelDev& lvs, const LevelDev& lvt,
-                            const T* Dst, hipStream_t st) {
+                            const T* Dst, const CommonDev& cm, hipStream_t st) {
   T* lT = (T*)lvt.lbarT;
-  const int rows = lvt.nref * full_row(p, (int)sizeof(T));
+  const int rows = lvt.nref * folded_row(p, (int)sizeof(T));
 #define X(PP) \
-  case PP: hipLaunchKernelGGL((k_adj_lbarT<T, PP>), dim3((rows + 255) / 256), dim3(256), 0, st, lvt, lT); break;
+  case PP: hipLaunchKernelGGL((k_adj_lbarT<T, PP>), dim3((rows + 255) / 256), dim3(256), 0, st, lvt, cm, lT); break;
   AFMM_P_SWITCH(p, X)
 #undef X
   if (xr.start[8] != ntiles * nsplit) return hipErrorInvalidValue;
   const dim3 grid(xr.grid()), block(64);
 #define X(PP) \
-  case PP: hipLaunchKernelGGL((k_adj_m2l_mfma<T, PP>), grid, block, 0, st, tiles, xr, nsplit, part, tapsT, live, aoff, lvp, lvs, lvt, (const T*)lT, Dst); break;
+  case PP: hipLaunchKernelGGL((k_adj_m2l_mfma<T, PP>), grid, block, 0, st, tiles, xr, nsplit, part, tapsT, live, aoff, lvp, lvs, lvt, (const T*)lT, Dst, cm.mi); break;
   AFMM_P_SWITCH(p, X)
 #undef X
-  return adj_reduce(p, tiles, ntiles, nsplit, part, lvs, st);
+  return adj_reduce(p, tiles, ntiles, nsplit, part, lvs, cm.mi, st);
 }
 
 hipError_t launch_adj_m2l_mfma(int p, bool fp32, const int32_t* tiles, int ntiles, int nsplit, const XcdRanges& xr,
                                const uint8_t* live, double* part, const int32_t* tapsT, const int16_t* aoff, const LevelDev& lvp,
                                const LevelDev& lvs, const LevelDev& lvt, const TablesDev<float>& t32,
-                               const TablesDev<double>& t64, hipStream_t st) {
+                               const TablesDev<double>& t64, const CommonDev& cm, hipStream_t st) {
   if (ntiles <= 0 || lvt.nref == 0) return hipSuccess;
   if (!live) return hipErrorInvalidValue;
-  if (fp32) return adj_m2l_t<float>(p, tiles, ntiles, nsplit, xr, live, part, tapsT, aoff, lvp, lvs, lvt, t32.Dstage, st);
-  return adj_m2l_t<double>(p, tiles, ntiles, nsplit, xr, live, part, tapsT, aoff, lvp, lvs, lvt, t64.Dstage, st);
+  if (fp32) return adj_m2l_t<float>(p, tiles, ntiles, nsplit, xr, live, part, tapsT, aoff, lvp, lvs, lvt, t32.Dstage, cm, st);
+  return adj_m2l_t<double>(p, tiles, ntiles, nsplit, xr, live, part, tapsT, aoff, lvp, lvs, lvt, t64.Dstage, cm, st);
 }
 
 #undef AFMM_P_SWITCH

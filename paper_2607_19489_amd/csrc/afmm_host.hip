@@ -880,32 +880,31 @@ static void build_tables(int p, HostTables& H) {
   }
   // adjoint: transposed M2P, rows a (tiles of 16), k = 8 g + kb -> (child o, quantity q)
   {
-    const int RT = (K + 15) / 16;
+    // adjoint: rows a of the independent coefficients
+    const int RT = (KH + 15) / 16;
     H.adj_m2p_off.clear();
     for (int rt = 0; rt < RT; ++rt)
       for (int kb = 0; kb < 8; ++kb)
         for (int lane = 0; lane < 64; ++lane) {
           const int a = 16 * rt + (lane & 15), j = 8 * (lane >> 4) + kb, o = j >> 2, q = j & 3;
           int v = ZERO;
-          if (a < K && q == 0) v = o * KS + a;
-          if (a < K1 && q > 0) v = o * KS + H.up[3 * a + (q - 1)];
+          if (a < KH && q == 0) v = o * KS + h_full(a);
+          if (a < KH && q > 0 && h_deg(a) < p) v = o * KS + H.up[3 * h_full(a) + (q - 1)];
           H.adj_m2p_off.push_back((int16_t)v);
         }
-    // transposed M2L, rows a, k = b = 4 kb + g, offsets within one D~ row (K = its zero)
+    // transposed M2L, k = b = 4 kb + g, offsets within one D~ row (K = its zero)
     H.adj_m2l_off.clear();
-    for (int rt = 0; rt < RT; ++rt) {
-      int d = 0;
-      while (nmi(d) <= 16 * rt) ++d;
-      const int ks = (nmi(p - d) + 3) / 4;
-      for (int kb = 0; kb < ks; ++kb)
+    for (int rt = 0; rt < RT; ++rt)
+      for (int kb = 0; kb < (nh(p - h_deg(16 * rt)) + 3) / 4; ++kb)
         for (int lane = 0; lane < 64; ++lane) {
           const int a = 16 * rt + (lane & 15), b = 4 * kb + (lane >> 4);
           int v = K;
-          if (a < K && b < K && deg(a) + deg(b) <= p)
-            v = mi_index(H.mi[4 * a] + H.mi[4 * b], H.mi[4 * a + 1] + H.mi[4 * b + 1], H.mi[4 * a + 2] + H.mi[4 * b + 2]);
+          if (a < KH && b < KH && h_deg(a) + h_deg(b) <= p) {
+            const int *aa = &H.mi[4 * h_full(a)], *bb = &H.mi[4 * h_full(b)];
+            v = mi_index(aa[0] + bb[0], aa[1] + bb[1], aa[2] + bb[2]);
+          }
           H.adj_m2l_off.push_back((int16_t)v);
         }
-    }
   }
   // M2L's A operand.  By taps: row tile t (rows R = 8 b + o from 16 t), k-step kb
   H.m2l_off.clear();
@@ -1833,13 +1832,14 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
       }
     int32_t* d_fs;
     int16_t* d_fl;
-    double *d_fw, *d_fp;
+    double *d_fw, *d_fp, *d_fu;
     if ((s = upload(P, H.fold_start, &d_fs, st, false)) || (s = upload(P, H.fold_list, &d_fl, st, false)) ||
-        (s = upload(P, fw, &d_fw, st)) || (s = upload(P, fp, &d_fp, st)))
+        (s = upload(P, fw, &d_fw, st)) || (s = upload(P, fp, &d_fp, st)) || (s = upload(P, H.fold_w, &d_fu, st, false)))
       return s;
     P->cm.fold_start = d_fs;
     P->cm.fold_list = d_fl;
     P->cm.fold_w = d_fw;
+    P->cm.fold_u = d_fu;
     P->cm.fold_p2m = d_fp;
     int32_t *d_ms, *d_ml;
     double* d_mw;
@@ -2924,8 +2924,8 @@ static afmm_status adjoint_topology(afmm_plan* P) {
     P->s_adjl[l] = split_of(P->n_adjl[l]);
     P->xr_adjp[l] = xcd_ranges(bits_p[l], P->s_adjp[l]);
     P->xr_adjl[l] = xcd_ranges(bits_l[l], P->s_adjl[l]);
-    if (P->s_adjp[l] > 1) P->adj_part_elems = std::max(P->adj_part_elems, (size_t)P->s_adjp[l] * P->n_adjp[l] * 16 * P->K);
-    if (P->s_adjl[l] > 1) P->adj_part_elems = std::max(P->adj_part_elems, (size_t)P->s_adjl[l] * P->n_adjl[l] * 16 * P->K);
+    if (P->s_adjp[l] > 1) P->adj_part_elems = std::max(P->adj_part_elems, (size_t)P->s_adjp[l] * P->n_adjp[l] * 16 * nh(P->opt.p));
+    if (P->s_adjl[l] > 1) P->adj_part_elems = std::max(P->adj_part_elems, (size_t)P->s_adjl[l] * P->n_adjl[l] * 16 * nh(P->opt.p));
   }
   P->adj_topo = true;
   return AFMM_OK;
@@ -2964,7 +2964,7 @@ static size_t adjoint_layout(const afmm_plan* P, char* base, LevelDev* lw, doubl
     if (P->n_adjl[f] > 0) {
       const bool f32 = mixed && f > f64;
       lw[f].lbarT = take((size_t)T.lv[f].nref() *
-                         (f32 ? full_row(P->opt.p, 4) * sizeof(float) : full_row(P->opt.p, 8) * sizeof(double)));
+                         (f32 ? folded_row(P->opt.p, 4) * sizeof(float) : folded_row(P->opt.p, 8) * sizeof(double)));
     }
   *part = P->adj_part_elems ? (double*)take(P->adj_part_elems * sizeof(double)) : nullptr;
   return off;
@@ -3048,7 +3048,7 @@ static afmm_status run_adjoint(afmm_plan* P, int32_t level, const double* d_phi_
                        launch_adj_m2p_mfma(p, mixed && (l - 1) > f64, P->d_adjp[l], P->n_adjp[l], P->s_adjp[l],
                                            P->xr_adjp[l], P->d_adjp_live[l], part,
                                            P->cm.tapsT, P->cm.adj_m2p_off, lw[l - 2], lw[l - 1], lw[l], P->t32, P->t64,
-                                           st),
+                                           P->cm, st),
                        "adjoint m2p")))
       return s;
     P->pending_flops += W.m2p_flops[l];
@@ -3071,7 +3071,7 @@ static afmm_status run_adjoint(afmm_plan* P, int32_t level, const double* d_phi_
                        launch_adj_m2l_mfma(p, mixed && f > f64, P->d_adjl[f], P->n_adjl[f], P->s_adjl[f],
                                            P->xr_adjl[f], P->d_adjl_live[f], part,
                                            P->cm.tapsT, P->cm.adj_m2l_off, lw[f - 2], lw[f - 1], lw[f], P->t32, P->t64,
-                                           st),
+                                           P->cm, st),
                        "adjoint m2l")))
       return s;
     P->pending_flops += W.m2l_flops[f];
@@ -3177,7 +3177,7 @@ static bool adjoint_noalloc_may_fit(const afmm_plan* P) {
     add(nref * K * 8);
     add(nref * K * 8);
     add(nref * 32 * 8);
-    add(nref * (size_t)full_row(P->opt.p, 8) * 8);
+    add(nref * (size_t)folded_row(P->opt.p, 8) * 8);
     const size_t nt = (size_t)(T.lv[l].n() + 15) / 16 + 8;
     const size_t sp = (size_t)std::max(1, std::min(16, (int)((12 * (size_t)ncu + nt - 1) / nt)));
     part = std::max(part, sp * nt * 16 * K);

@@ -135,19 +135,19 @@ struct SymLayout {
   }
 };
 
-// Rows of the adjoint's local-expansion bars: all K coefficients in the order in
+// Rows of the adjoint's local-expansion bars: the KH folded coefficients in the order in
 // which its kernel reads the B operand straight into registers.  Lane group g
 // (lane >> 4) of a 16x16x4 step kb holds coefficient k = 4 kb + g.  A lane group
-// needs STP steps (STP = ceil(K/4) rounded up to whole 16-byte vectors of VW =
+// needs STP steps (STP = ceil(KH/4) rounded up to whole 16-byte vectors of VW =
 // 16/bytes values); its vector j holds steps VW j .. VW j + VW - 1.  The row
 // stores the vectors j-major: vector j of lane group g at (4 j + g) VW, so one
 // 16-byte load per lane (vector j for all 4 lane groups of a source) reads 64
 // contiguous bytes of each source row.  Coefficient k therefore sits at
 // ((k >> 2) / VW) 4 VW + (k & 3) VW + (k >> 2) % VW; unused slots are 0.
-__host__ __device__ constexpr int full_stp(int p, int bytes) {
-  return (((nmi(p) + 3) / 4) + (16 / bytes) - 1) / (16 / bytes) * (16 / bytes);
+__host__ __device__ constexpr int folded_stp(int p, int bytes) {
+  return (((nh(p) + 3) / 4) + (16 / bytes) - 1) / (16 / bytes) * (16 / bytes);
 }
-__host__ __device__ constexpr int full_row(int p, int bytes) { return 4 * full_stp(p, bytes); }
+__host__ __device__ constexpr int folded_row(int p, int bytes) { return 4 * folded_stp(p, bytes); }
 __host__ __device__ constexpr int src_pos(int k, int bytes) {
   return ((k >> 2) / (16 / bytes)) * 4 * (16 / bytes) + (k & 3) * (16 / bytes) + (k >> 2) % (16 / bytes);
 }
@@ -276,7 +276,7 @@ struct LevelDev {
   double* sbar = nullptr;            // [nref][K] source-copy bar, then multipole bar
   double* lbar = nullptr;            // [nref][K] local-expansion bar
   void* tbT = nullptr;               // [nref][32] target bars of the leaf children, B of the transposed M2P (T)
-  void* lbarT = nullptr;             // [nref][full_row] local-expansion bar, B of the transposed M2L (T, lane-group layout)
+  void* lbarT = nullptr;             // [nref][folded_row] local-expansion bar, B of the transposed M2L (T, lane-group layout)
 };
 
 template <typename T>
@@ -299,6 +299,7 @@ struct CommonDev {
   const int16_t* up = nullptr;      // [K][3] index of a + e_i (or -1 when |a| = p)
   const int8_t* mi = nullptr;       // [K][4] (a, b, c, |a|)
   const double* binom = nullptr;    // [(kPMax+1)^2] binomial coefficients C(n, k) at n*(kPMax+1)+k
+  const double* fold_u = nullptr;   // weights of the fold lists without the source copies' factors
   const double* cfac2 = nullptr;    // [K] (-1)^|a|/a! 2^|a| (FP64), the factors of the source copies
   const int32_t* fold_start = nullptr;  // [nh + 1] entry range of each folded source coefficient
   const int16_t* fold_list = nullptr;   // entries: coefficient a
@@ -385,12 +386,12 @@ hipError_t launch_adj_m2p_mfma(int p, bool fp32, const int32_t* tiles, int ntile
                                const uint8_t* live, double* part,
                                const int32_t* tapsT, const int16_t* aoff, const LevelDev& lvp, const LevelDev& lvs,
                                const LevelDev& lvt, const TablesDev<float>& t32, const TablesDev<double>& t64,
-                               hipStream_t st);
+                               const CommonDev& cm, hipStream_t st);
 hipError_t launch_adj_m2l_mfma(int p, bool fp32, const int32_t* tiles, int ntiles, int nsplit, const XcdRanges& xr,
                                const uint8_t* live, double* part,
                                const int32_t* tapsT, const int16_t* aoff, const LevelDev& lvp, const LevelDev& lvs,
                                const LevelDev& lvt, const TablesDev<float>& t32, const TablesDev<double>& t64,
-                               hipStream_t st);
+                               const CommonDev& cm, hipStream_t st);
 hipError_t launch_adj_l2l(int p, const int32_t* grp, int ngrp, const LevelDev& lv1, const LevelDev& lv0,
                           const TablesDev<double>& t64, const CommonDev& cm, hipStream_t st);
 hipError_t launch_adj_down(int p, const int32_t* grp, int ngrp, const LevelDev& lv1, const LevelDev& lv0,
