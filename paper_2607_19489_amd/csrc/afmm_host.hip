@@ -1540,14 +1540,22 @@ static int append_m2p_tiles(const Topology& T, int target, const std::vector<int
                             std::vector<int32_t>& out) {
   const HostLevel &L1 = T.lv[target - 1], &L2 = T.lv[target - 2];
   std::vector<int32_t> cls[8], end[8];  // groups per class, and where each tile ends
+  // each class in segments for the threads; a tile ends with its segment
+  constexpr size_t kSeg = 8192;
   for (int32_t F : grp) cls[L1.refcell[F] & 7].push_back(F);
-  parallel_ranges(8, grp.size() > 256 ? 8 : 1, [&](int64_t b, int64_t e, int) {
-    for (int64_t c = b; c < e; ++c) {
+  size_t nseg = 1;
+  for (auto& c : cls) nseg = std::max(nseg, (c.size() + kSeg - 1) / kSeg);
+  std::vector<std::vector<int32_t>> segend(8 * nseg);
+  const int64_t items = (int64_t)(8 * nseg);
+  parallel_ranges(items, grp.size() > 256 ? (int)std::min<int64_t>(items, 32) : 1, [&](int64_t b, int64_t e, int) {
+    for (int64_t it = b; it < e; ++it) {
+      const size_t c = (size_t)it / nseg, g0 = (size_t)it % nseg * kSeg, g1 = std::min(cls[c].size(), g0 + kSeg);
+      std::vector<int32_t>& ends = segend[(size_t)it];
       // fathers of the tile: open addressing, at most nf + 27 of 1024 slots taken
       constexpr uint32_t kSlots = 1024;
       std::vector<int32_t> key(kSlots), of(kSlots, -1);  // rank, and the tile it belongs to
       int cols = 0, fathers = 0, tile = 0;
-      for (size_t i = 0; i < cls[c].size();) {
+      for (size_t i = g0; i < g1;) {
         const int32_t* nb = &L2.nbr[(size_t)(L1.refcell[cls[c][i]] >> 3) * 27];
         int32_t rk[27];
         int add = 0;
@@ -1562,7 +1570,7 @@ static int append_m2p_tiles(const Topology& T, int target, const std::vector<int
           ++add;
         }
         if (cols == nc || fathers + add > nf) {  // the group begins the next tile
-          end[c].push_back((int32_t)i);
+          ends.push_back((int32_t)i);
           cols = fathers = 0;
           ++tile;
           continue;
@@ -1571,9 +1579,11 @@ static int append_m2p_tiles(const Topology& T, int target, const std::vector<int
         fathers += add;
         ++i;
       }
-      if (cols) end[c].push_back((int32_t)cls[c].size());
+      if (cols) ends.push_back((int32_t)g1);
     }
   });
+  for (size_t it = 0; it < segend.size(); ++it)
+    end[it / nseg].insert(end[it / nseg].end(), segend[it].begin(), segend[it].end());
   size_t maxt = 0;
   for (auto& e : end) maxt = std::max(maxt, e.size());
   int n = 0;
