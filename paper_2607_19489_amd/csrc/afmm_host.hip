@@ -1533,10 +1533,17 @@ static int append_tiles(const Topology& T, int target, const std::vector<int32_t
   return n;
 }
 
+static int device_cu_count() {
+  int ncu = 256, dev = 0;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+  return ncu > 0 ? ncu : 256;
+}
+
 // M2P tiles of one level: up to nc groups of one parity class whose sources have
 // at most nf distinct refined fathers (neighbours of the groups' fathers G), tiles
-// of the 8 classes interleaved.  Returns the number of tiles appended.
-static int append_m2p_tiles(const Topology& T, int target, const std::vector<int32_t>& grp, int nc, int nf,
+// of the 8 classes interleaved; or, for groups far apart, direct tiles (below).
+// Returns the number of tiles appended.
+static int append_m2p_tiles(const Topology& T, int target, const std::vector<int32_t>& grp, int nc, int nf, int ncu,
                             std::vector<int32_t>& out) {
   const HostLevel &L1 = T.lv[target - 1], &L2 = T.lv[target - 2];
   std::vector<int32_t> cls[8], end[8];  // groups per class, and where each tile ends
@@ -1584,15 +1591,44 @@ static int append_m2p_tiles(const Topology& T, int target, const std::vector<int
   });
   for (size_t it = 0; it < segend.size(); ++it)
     end[it / nseg].insert(end[it / nseg].end(), segend[it].begin(), segend[it].end());
-  size_t maxt = 0;
-  for (auto& e : end) maxt = std::max(maxt, e.size());
+  size_t maxt = 0, nstaged = 0, nfull = 0;
+  for (int c = 0; c < 8; ++c) {
+    maxt = std::max(maxt, end[c].size());
+    nstaged += end[c].size();
+    nfull += (cls[c].size() + nc - 1) / nc;
+  }
+  // Groups far apart (refined cells scattered over a base grid) share few fathers:
+  // 7 to 9 of them fill a staged tile, whose other columns are padding.  Such a
+  // level takes direct tiles, where no bound on fathers applies, once the staged
+  // ones outnumber full ones by what a direct tile costs more: 1.2 to 1.4 staged
+  // tiles with 48 columns, about 2 with 64.  Finest level alone, staged / direct us:
+  // 64^3 + 30% of its cells (2.4 times as many) 460 / 375 at p = 3 FP64, 849 / 514
+  // at p = 6 FP32; 64^3 + 60% (1.5 times, 1.4 with 48 columns) 612 / 900, 1060 / 1070;
+  // 32^3 + 30% (2.0 times) 107 / 96 at p = 4 FP32.
+  // Their columns: a quad per wave for every six groups per CU.  Narrow tiles spread
+  // a level solved by itself over the CUs, wide ones cost the whole solve less: 3278
+  // groups at p = 6 FP64, M2P and leaf kernel, that level / all levels 85 / 244 us with one
+  // quad, 95 / 189 with two, 115 / 213 with three.
+  int nq = 0;
+  if (2 * nstaged > (nc == 48 ? 3 : 4) * nfull) {
+    nq = (int)std::max<size_t>(1, std::min<size_t>(nc / 16, grp.size() / (6 * (size_t)ncu)));
+    maxt = 0;
+    for (int c = 0; c < 8; ++c) {
+      end[c].clear();
+      for (size_t i = 0; i < cls[c].size(); i += 16 * nq) end[c].push_back((int32_t)std::min(cls[c].size(), i + 16 * nq));
+      maxt = std::max(maxt, end[c].size());
+    }
+  }
   int n = 0;
   for (size_t t = 0; t < maxt; ++t)
     for (int c = 0; c < 8; ++c) {
       if (t >= end[c].size()) continue;
-      out.push_back(target);
-      const int32_t b = t ? end[c][t - 1] : 0;
-      for (int j = 0; j < nc; ++j) out.push_back(b + j < end[c][t] ? cls[c][b + j] : -1);
+      out.push_back(target | nq << 8);
+      int32_t b = t ? end[c][t - 1] : 0;
+      for (int j = 0; j < nc; ++j) {
+        const bool on = nq == 0 || j % (nc / 4) < 4 * nq;  // the first nq quads of each of the 4 waves
+        out.push_back(on && b < end[c][t] ? cls[c][b++] : -1);
+      }
       ++n;
     }
   return n;
@@ -1737,6 +1773,7 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
   const int K = P->K;
   const bool mixed = P->opt.precision == AFMM_FP32_MIXED;
   const int f64 = mixed ? P->opt.fp64_levels : 1 << 20;
+  const int ncu = device_cu_count();
   build_groups(T);  // the plan keeps its topology and tables: their uploads are waited for once, at the end
   P->tabs = tables_for(P->opt.p);
   afmm_status s;
@@ -1935,7 +1972,7 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
     for (int l = 3; l <= T.lmax; ++l) {
       const int pr = (mixed && (l - 1) > f64) ? 1 : 0;
       const int n0 = (int)(m2p_rec[pr].size() / (m2p_nc[pr] + 1));
-      const int n = append_m2p_tiles(T, l, T.leafgrp[l], m2p_nc[pr], m2p_fathers(P->opt.p, pr ? 4 : 8), m2p_rec[pr]);
+      const int n = append_m2p_tiles(T, l, T.leafgrp[l], m2p_nc[pr], m2p_fathers(P->opt.p, pr ? 4 : 8), ncu, m2p_rec[pr]);
       P->m2p_range[l][0] = pr;
       P->m2p_range[l][1] = n0;
       P->m2p_range[l][2] = n;
@@ -2824,12 +2861,6 @@ static afmm_status afmm_batch_autotune_impl(afmm_batch* B, const double* const* 
 // operators' B staging (tbT, lbarT) and the tap-split partial sets -- is laid
 // out in one block: allocated by the plan on the first afmm_solve_adjoint, or
 // taken from the library's static scratch array by afmm_solve_adjoint_noalloc.
-
-static int device_cu_count() {
-  int ncu = 256, dev = 0;
-  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  return ncu > 0 ? ncu : 256;
-}
 
 static afmm_status adjoint_topology(afmm_plan* P) {
   if (P->adj_topo) return AFMM_OK;

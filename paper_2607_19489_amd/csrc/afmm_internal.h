@@ -414,7 +414,8 @@ __host__ __device__ constexpr int m2p_quads(int p, int bytes) { return m2p_vec(p
 __host__ __device__ constexpr int m2p_cols(int p, int bytes) { return 16 * m2p_quads(p, bytes); }
 __host__ __device__ constexpr int m2p_fathers(int p, int bytes) { return m2p_quads(p, bytes) == 3 ? 200 : 240; }
 // MFMA launches over a contiguous range [t0, t0 + n) of tile records; each
-// record is (target level, NC groups).  lvs is the device array of LevelDev.
+// record is (target level, NC groups); a direct M2P tile's has its quads per wave
+// above the level's 8 bits.  lvs is the device array of LevelDev.
 hipError_t launch_m2l(int p, bool fp32, const MfmaTiles& mt, int t0, int n, int nsplit, const MfmaTables& tabs,
                            const LevelDev* lvs, const TablesDev<float>& t32, const TablesDev<double>& t64,
                            hipStream_t st);

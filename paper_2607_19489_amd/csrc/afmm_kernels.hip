@@ -13,6 +13,7 @@
 // Deterministic: no atomics; every sum runs in a fixed order.
 #include <hip/hip_runtime.h>
 #include <algorithm>
+#include <type_traits>
 
 #include "afmm_internal.h"
 #include "afmm_mfma.h"
@@ -652,12 +653,24 @@ __device__ inline void tile_setup(const int32_t* __restrict__ rec, int NC, const
 // (128^3 + 4 levels) at p = 6 FP32: 8.7 ms summed tap by tap over all K
 // coefficients, 6.4 on the folded ones, 4.95 by orbits; 287,680 leaves FP64: 703,
 // 501, 368 us; 64^3 and 128^3 batches at p = 4 and 8 FP32: 1494 to 866, 1903 to 986.
+//
+// Groups far apart fill a tile's fathers long before its columns.  They go to direct
+// tiles (STAGED false; the host's rule is at append_m2p_tiles): the row and the mass of
+// every (neighbour, column) are resolved once per octant of m, the next octant's while
+// this one runs, and the sources' rows come from memory, a quad or the first quad
+// of the next orbit ahead.  Same sums in the same order, so the same bits.  They are
+// bound by the latency of those loads and share k_m2p, for one launch covers the tiles
+// of all levels; the registers of both forms decide the occupancy (FP64 to p = 3 runs
+// three blocks per CU, which the loads of the next octant's sources would exceed).
+// Finest level of 64^3 + 2% of its cells (5243 groups), staged / direct: 93 / 63 us at
+// p = 3 FP64, 110 / 65 at p = 4, 182 / 64 at p = 6 FP32, 316 / 104 at p = 6 FP64; tap
+// by tap, 16 groups per tile wherever they lie, they took 64, 57, 90 and 143.
 template <typename T> struct M2PAcc { typedef f32x4 type; };
 template <> struct M2PAcc<double> { typedef double type; };
 __device__ inline f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 0, 0, 0); }
 __device__ inline double mfma4(double a, double b, double c) { return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0); }
 
-template <typename T, int P>
+template <typename T, int P, bool STAGED>
 struct M2P {
   using SL = SymLayout<P, (int)sizeof(T)>;
   static constexpr int CP = SL::CP, NP = SL::NP, ROW = SL::ROW;
@@ -672,7 +685,7 @@ struct M2P {
     int key[NH];
     uint16_t slot[NH];
   };
-  struct Lds {
+  struct LdsStaged {
     union {
       T rows[(NF + 1) * kSymBlocks * LV];   // the octant's rows (block q of row u at place q ^ (u & 15)), then zeros
       Hash h;
@@ -685,6 +698,14 @@ struct M2P {
     int wsum[4];
     int nf;
   };
+  struct LdsDirect {
+    T a[3][AL];
+    int base[27 * COLS];                    // children of neighbour e of column n's father, or -1
+    int row[27 * COLS];                     // row of the one in the octant (the zero row for a leaf or none)
+    T mass[27 * COLS];                      // its mass if it is a leaf, else 0
+    int F[COLS];
+  };
+  using Lds = std::conditional_t<STAGED, LdsStaged, LdsDirect>;
   Lds& l;
   const T* __restrict__ symA;
   const uint64_t* __restrict__ taps;        // fathers of the class's orbits, a byte each
@@ -692,12 +713,14 @@ struct M2P {
   gptr<double> mass1;
   gptr<T> S;                                // the level's source copy
   int zrow, nf, C, par;
+  int nq;                                   // quads of a wave that hold groups (not STAGED)
+  int ps;                                   // pass of the steps that run (not STAGED)
   int g0, g1;                               // steps (m, pass, j) of this block: [g0, g1) of 56 NP
   int af;                                   // axes on which the operand being loaded has its far offset on the other side
   int ra, wa;                               // ring places: operand of the next step, of the one after
   T sg[3];                                  // sigma^a sign of this lane's block on each axis
   Acc acc[NQ][8];
-  V a[8], an[2];
+  V a[8], an[2], first[STAGED ? 1 : 8];
 
   static constexpr int axis(int pt, int b) {  // b-th axis of the set
     int i = 0;
@@ -809,6 +832,46 @@ struct M2P {
     if (s == NP - 1 && m + 1 < 8) put_source(m + 1, cell, rk);
     __syncthreads();
   }
+  // not STAGED: children of the neighbours of the columns' fathers
+  __device__ inline void find_bases(gptr<int32_t> refcell1, gptr<int32_t> nbr2, gptr<int32_t> rank2) {
+    for (int i = threadIdx.x; i < 27 * COLS; i += kBlock) {
+      const int e = i / COLS, F = l.F[i - e * COLS];
+      const int Q = F >= 0 ? nbr2[(size_t)(refcell1[F] >> 3) * 27 + e] : -1, r = Q >= 0 ? rank2[Q] : -1;
+      l.base[i] = r >= 0 ? 8 * r : -1;
+    }
+    __syncthreads();
+  }
+  // not STAGED: the sources in the octant of m on their way, and into LDS.  The
+  // masses of refined cells are 0 and so are the values of the zero row, so a
+  // source is its row plus its mass.
+  static constexpr int NE = (27 * COLS + kBlock - 1) / kBlock;
+  static constexpr bool AHEAD = sizeof(T) == 4 || P > 3;  // registers
+  struct Sources {
+    int rk[NE];
+    double mm[NE];
+  };
+  __device__ inline void load_sources(int m, Sources& r) const {
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      const int b = l.base[min((int)threadIdx.x + kBlock * k, 27 * COLS - 1)];
+      r.rk[k] = -1;
+      r.mm[k] = 0.0;
+      if (b >= 0) {
+        r.rk[k] = rank1[b + (C ^ m)];
+        r.mm[k] = mass1[b + (C ^ m)];
+      }
+    }
+  }
+  __device__ inline void put_sources(const Sources& r) {
+#pragma unroll
+    for (int k = 0; k < NE; ++k) {
+      const int i = threadIdx.x + kBlock * k;
+      if (i >= 27 * COLS) continue;
+      l.row[i] = r.rk[k] >= 0 ? r.rk[k] : zrow;
+      l.mass[i] = (T)r.mm[k];
+    }
+    __syncthreads();
+  }
   // the block's share of the A operand of step g (the last one past the end):
   // characters wave, wave + 4; put into the ring with the sign of this class: the
   // operator's representative offsets are positive, mirrored on the axes on which
@@ -853,37 +916,72 @@ struct M2P {
         }
     }
   }
-  // one orbit and pass, its sources' fathers in code: the wave's quads
-  template <int PT>
-  __device__ inline void orbit(uint64_t code) {
+  // row of source i of an orbit (its fathers in code) for quad qd of the wave: block q
+  __device__ inline V source_row(uint64_t code, int i, int qd, int lane) const {
+    const int at = ((int)(code >> (8 * i)) & 31) * COLS + (wave_id() * NQ + qd) * 4 + (lane & 3);
+    if constexpr (STAGED) return load_vec<T, CP>((const T*)((const char*)l.rows + (l.tab[at] ^ (lane >> 2) * VB)));
+    else return load_vec<T, CP>(S + (size_t)l.row[at] * ROW + (ps * kSymBlocks + (lane >> 2)) * CP);
+  }
+  // not STAGED: the first quad's rows of the next orbit, of at most N sources (bytes of
+  // code past the orbit's sources are 0, a valid neighbour), on their way
+  template <int N>
+  __device__ inline void load_first(uint64_t code, int lane) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) first[i] = source_row(code, i, 0, lane);
+  }
+  // one orbit and pass: the wave's quads.  Butterflies and products apart: these MFMAs
+  // and the VALU share the units, and every change between them costs some cycles
+  // (32 of each: 541 cycles interleaved, 421 one after the other, two waves).  One
+  // quad's reads ahead, no more (registers).
+  template <int PT, int NEXT>
+  __device__ inline void orbit(uint64_t code, uint64_t next) {
     constexpr int NS = 1 << sym_bits(PT);
-    const int lane = lane_id(), wv = wave_id(), q = lane >> 2, j = lane & 3;
-    int off[NS];
-#pragma unroll
-    for (int i = 0; i < NS; ++i) off[i] = (int)(code >> (8 * i) & 31) * COLS;
-    const uint16_t* tab = l.tab + wv * NQ * 4 + j;
-    auto read_rows = [&](int qd, V* v) {
-#pragma unroll
-      for (int i = 0; i < NS; ++i) v[i] = load_vec<T, CP>((const T*)((const char*)l.rows + (tab[off[i] + 4 * qd] ^ q * VB)));
-    };
-    V v[2][NS];
-    read_rows(0, v[0]);
-#pragma unroll
-    for (int qd = 0; qd < NQ; ++qd) {
-      if (qd + 1 < NQ) read_rows(qd + 1, v[(qd + 1) & 1]);
-      transform<PT>(v[qd & 1]);
-      // butterflies and products apart: these MFMAs and the VALU share the units,
-      // and every change between them costs some cycles (32 of each: 541 cycles
-      // interleaved, 421 one after the other, two waves)
+    const int lane = lane_id();
+    auto products = [&](int qd, V* v) {
+      transform<PT>(v);
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int e = 0; e < CP; ++e)
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[qd][c] = mfma4(a[c][e], v[qd & 1][sub(PT, c)][e], acc[qd][c]);
-      if (qd == NQ - 1)
+        for (int c = 0; c < 8; ++c) acc[qd][c] = mfma4(a[c][e], v[sub(PT, c)][e], acc[qd][c]);
+    };
+    if constexpr (STAGED) {
+      V v[2][NS];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) read_a(c, lane, ra);
-      __builtin_amdgcn_sched_barrier(0);  // one quad's reads ahead, no more (registers)
+      for (int i = 0; i < NS; ++i) v[0][i] = source_row(code, i, 0, lane);
+#pragma unroll
+      for (int qd = 0; qd < NQ; ++qd) {
+        if (qd + 1 < NQ)
+#pragma unroll
+          for (int i = 0; i < NS; ++i) v[(qd + 1) & 1][i] = source_row(code, i, qd + 1, lane);
+        products(qd, v[qd & 1]);
+        if (qd == NQ - 1)
+#pragma unroll
+          for (int c = 0; c < 8; ++c) read_a(c, lane, ra);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      V odd[NS];
+#pragma unroll
+      for (int qd = 0; qd < NQ; ++qd) {
+        if (qd >= nq) break;
+        V *v = qd & 1 ? odd : first, *ahead = qd & 1 ? first : odd;
+        if (qd + 1 < NQ && qd + 1 < nq)
+#pragma unroll
+          for (int i = 0; i < NS; ++i) ahead[i] = source_row(code, i, qd + 1, lane);
+        if (ps == 0) {
+#pragma unroll
+          for (int i = 0; i < NS; ++i) {
+            const T mm = l.mass[((int)(code >> (8 * i)) & 31) * COLS + (wave_id() * NQ + qd) * 4 + (lane & 3)];
+            v[i][0] += lane < 4 ? mm : (T)0;
+          }
+        }
+        products(qd, v);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      load_first<NEXT>(next, lane);
+#pragma unroll
+      for (int c = 0; c < 8; ++c) read_a(c, lane, ra);
     }
   }
   __device__ inline uint64_t sources_of(int g) const {
@@ -900,7 +998,7 @@ struct M2P {
       code = sources_of(g + 1);
       put_a(wa);
       load_a(g + 3);
-      orbit<sym_axes(TY)>(c);
+      orbit<sym_axes(TY), 1 << sym_bits(sym_axes(TY < 7 ? TY + 1 : 7))>(c, code);
       const int x = 3 - ra - wa;  // the place of the operand just used
       ra = wa;
       wa = x;
@@ -912,31 +1010,41 @@ struct M2P {
   __device__ inline void run() {
     int g = g0;
     uint64_t code = sources_of(g);
+    std::conditional_t<STAGED, char, Sources> next;
+    if constexpr (!STAGED && AHEAD) load_sources(g0 / (7 * NP), next);
     while (g < g1) {
       const int ms = g / 7, m = ms / NP;
-      stage(m, ms - m * NP);
+      if constexpr (STAGED) {
+        stage(m, ms - m * NP);
+      } else {
+        ps = ms - m * NP;
+        if (ps == 0 || g == g0) {
+          if (!AHEAD) load_sources(m, next);
+          put_sources(next);
+          if (AHEAD) load_sources(min(m + 1, 7), next);
+        }
+        load_first<8>(code, lane_id());
+      }
       sets<0>(m, 7 * ms, g, code);
     }
   }
 };
 
-template <typename T, int P>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2)))
-void k_m2p(const int32_t* __restrict__ tiles, int ntiles, int nsplit, const int8_t* __restrict__ taps,
-           const LevelDev* __restrict__ lvs, const T* __restrict__ symA) {
-  using MP = M2P<T, P>;
+// One tile (record rec: the target level, the quads per wave << 8 or 0 for a STAGED
+// tile, the groups) and one of nsplit ranges of the orbits.
+template <typename T, int P, bool STAGED>
+__device__ inline void m2p_tile(typename M2P<T, P, STAGED>::Lds& lds, const int32_t* __restrict__ rec, int chunk, int nsplit,
+                                const int8_t* __restrict__ taps, const LevelDev* __restrict__ lvs,
+                                const T* __restrict__ symA) {
+  using MP = M2P<T, P, STAGED>;
   using SL = typename MP::SL;
   static constexpr SL sl{};
-  __shared__ __align__(16) typename MP::Lds lds;
-  const int item = xcd_tile(ntiles * nsplit);
-  if (item >= ntiles * nsplit) return;
-  const int tile = item / nsplit, chunk = item - tile * nsplit;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6, q = lane >> 2, j = lane & 3;
-  const int32_t* rec = tiles + (size_t)tile * (MP::COLS + 1);
-  const LevelDev lv1 = lvs[rec[0] - 1];
-  const LevelDev lv2 = lvs[rec[0] - 2];
+  const int level = rec[0] & 255;
+  const LevelDev lv1 = lvs[level - 1];
+  const LevelDev lv2 = lvs[level - 2];
   if (t < MP::COLS) lds.F[t] = rec[1 + t];
-  lds.h.key[t] = lds.h.key[t + kBlock] = -1;
+  if constexpr (STAGED) lds.h.key[t] = lds.h.key[t + kBlock] = -1;
   static_assert(MP::NH == 2 * kBlock, "two hash slots per thread");
   __syncthreads();
   gptr<int32_t> refcell1 = as_global(lv1.refcell);
@@ -956,15 +1064,18 @@ void k_m2p(const int32_t* __restrict__ tiles, int ntiles, int nsplit, const int8
   for (int d = 0; d < MP::NQ; ++d)
 #pragma unroll
     for (int c = 0; c < 8; ++c) m.acc[d][c] = typename MP::Acc{};
-  m.find_fathers(refcell1, as_global(lv2.nbr), as_global(lv2.rank));
-  m.nf = lds.nf;
   // the A operand of the first two steps into the ring, the third on its way; the
   // first octant's sources; the zero row
-  {
+  if constexpr (STAGED) {
+    m.find_fathers(refcell1, as_global(lv2.nbr), as_global(lv2.rank));
+    m.nf = lds.nf;
     const int mf = m.g0 / (7 * MP::NP), cell = m.source_cell(mf);
     m.put_source(mf, cell, m.rank1[cell]);
+    if (t < kSymBlocks * MP::LV) lds.rows[MP::NF * kSymBlocks * MP::LV + t] = 0;
+  } else {
+    m.nq = rec[0] >> 8;
+    m.find_bases(refcell1, as_global(lv2.nbr), as_global(lv2.rank));
   }
-  if (t < kSymBlocks * MP::LV) lds.rows[MP::NF * kSymBlocks * MP::LV + t] = 0;
   m.load_a(m.g0);
   m.put_a(0);
   m.load_a(m.g0 + 1);
@@ -1039,6 +1150,22 @@ void k_m2p(const int32_t* __restrict__ tiles, int ntiles, int nsplit, const int8
       }
     }
   }
+}
+
+template <typename T, int P>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(M2P<T, P, false>::AHEAD ? 2 : 3)))
+void k_m2p(const int32_t* __restrict__ tiles, int ntiles, int nsplit, const int8_t* __restrict__ taps,
+           const LevelDev* __restrict__ lvs, const T* __restrict__ symA) {
+  __shared__ __align__(16) union {
+    typename M2P<T, P, true>::Lds staged;
+    typename M2P<T, P, false>::Lds direct;
+  } lds;
+  const int item = xcd_tile(ntiles * nsplit);
+  if (item >= ntiles * nsplit) return;
+  const int tile = item / nsplit, chunk = item - tile * nsplit;
+  const int32_t* rec = tiles + (size_t)tile * (m2p_cols(P, (int)sizeof(T)) + 1);
+  if (rec[0] < 256) m2p_tile<T, P, true>(lds.staged, rec, chunk, nsplit, taps, lvs, symA);
+  else m2p_tile<T, P, false>(lds.direct, rec, chunk, nsplit, taps, lvs, symA);
 }
 
 // ---------------------------------------------------------------------------
