@@ -1210,51 +1210,57 @@ constexpr M2LPlan<P> make_m2l_plan() {
 }
 
 // B of one M2L tap in LDS, sB[k][n] (fragment order of the k-steps): thread (n =
-// t & 15, q = t >> 4) loads the vectors of block q of column n's source row and
-// stores each value at its coefficient.  A missing or leaf source reads the zero
-// row; the threads of block 0 store a leaf's mass, which was put into LDS with the
-// source table (loaded in the tap loop by every thread, it took 40% of the kernel
-// at p = 1).
+// t & 15, v = t >> 4) loads 16-byte vector v of column n's source row and stores each
+// value at its coefficient; the waves past the row's last vector have no part in it.
+// (With one value per thread and block of the row, as wide as the layout allows up to
+// p = 3, all four waves looked up 16 lines per tap: 64^3 at p = 1 FP32 48 us, now
+// 33; two ranges of taps.)  A missing or leaf source reads the zero row; the threads of
+// vector 0 store a leaf's mass, which was put into LDS with the source table and is
+// read with the source (loaded from memory in the tap loop by every thread, it took 40%
+// of the kernel at p = 1).
 template <typename T, int P>
 struct BStage {
   using SL = SymLayout<P, (int)sizeof(T)>;
-  static constexpr int CP = SL::CP, NP = SL::NP;
-  typedef typename VecN<T, CP>::type V;
+  typedef typename Vec16<T>::type V;
+  static constexpr int VW = TapStage<T, P>::VW, NV = SL::ROW / VW;
+  static_assert(SL::NP == 1 && NV % 4 == 0 && NV <= 16, "one vector per thread, whole waves");
   struct Regs {
-    V v[NP];
-    int leaf;  // place of the leaf's mass, or -1
+    V v;
+    T m;        // the mass of a leaf
+    bool leaf;
   };
   gptr<T> base;
   const int* src;    // [tap][column]
   const T* mass;     // [tap][column]
   int zrow;
-  int at[NP * CP];   // sB slots of the thread's values
+  int at[VW];        // sB slots of the thread's values
   __device__ inline void init(const LevelDev& lv, const int* s, const T* m) {
     static constexpr SL sl{};
-    const int t = threadIdx.x, n = t & 15, q = t >> 4;
+    const int t = threadIdx.x, n = t & 15, v = t >> 4;
     zrow = lv.nref;
-    base = as_global(level_S<T>(lv)) + q * CP;
+    base = as_global(level_S<T>(lv)) + v * VW;
     src = s;
     mass = m;
+    if (v >= NV) return;
 #pragma unroll
-    for (int i = 0; i < NP * CP; ++i) {
-      const int h = sl.coef[(i / CP * kSymBlocks + q) * CP + i % CP];
+    for (int i = 0; i < VW; ++i) {
+      const int h = sl.coef[v * VW + i];
       at[i] = (h >= 0 ? h : TapStage<T, P>::KP) * 16 + n;
     }
   }
-  // tap k, or none (k < 0)
+  static __device__ inline constexpr bool part(int wave) { return 4 * wave < NV; }
+  // tap k, or none (k < 0); MASS for wave 0, which holds vector 0
+  template <bool MASS>
   __device__ inline void load(int k, Regs& r) const {
-    const int i = k * 16 + ((int)threadIdx.x & 15), sr = k >= 0 ? src[i] : -1;
-    gptr<T> row = base + (size_t)min((uint32_t)sr, (uint32_t)zrow) * SL::ROW;
-#pragma unroll
-    for (int s = 0; s < NP; ++s) r.v[s] = load_vec<T, CP>(row + s * kSymBlocks * CP);
-    r.leaf = threadIdx.x < 16 && sr <= -2 ? i : -1;
+    const int i = max(k, 0) * 16 + ((int)threadIdx.x & 15), s0 = src[i], sr = k >= 0 ? s0 : -1;
+    if (MASS) r.m = mass[i];
+    r.v = *(gptr<V>)(base + (size_t)min((uint32_t)sr, (uint32_t)zrow) * SL::ROW);
+    if (MASS) r.leaf = threadIdx.x < 16 && sr <= -2;
   }
+  template <bool MASS>
   __device__ inline void store(T* sB, const Regs& r) const {
-    T v0 = r.v[0][0];
-    if (r.leaf >= 0) v0 = mass[r.leaf];
 #pragma unroll
-    for (int i = 0; i < NP * CP; ++i) sB[at[i]] = i == 0 ? v0 : r.v[i / CP][i % CP];
+    for (int i = 0; i < VW; ++i) sB[at[i]] = MASS && i == 0 && r.leaf ? r.m : r.v[i];
   }
 };
 
@@ -1313,14 +1319,14 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
   {
     const int k1 = nt > 1 ? 1 : 0;
     load_dstage_nb<T, P, kBlock>(tp[k1], Dst, vDX);
-    bs.load(nt > 1 ? 1 : -1, vBX);
+    if constexpr (BStage<T, P>::part(H)) bs.template load<H == 0>(nt > 1 ? 1 : -1, vBX);
   }
   // one tap: load tap k + 2 into (vDn, vBn), MFMAs of tap k from LDS buffer
   // b, store tap k + 1 from (vDc, vBc) into buffer b ^ 1
   auto step = [&](int k, int b, V* vDc, const BV& vBc, V* vDn, BV& vBn) {
     const int k2 = k + 2 < nt ? k + 2 : nt - 1;
     load_dstage_nb<T, P, kBlock>(tp[k2], Dst, vDn);
-    bs.load(k + 2 < nt ? k2 : -1, vBn);
+    if constexpr (BStage<T, P>::part(H)) bs.template load<H == 0>(k + 2 < nt ? k2 : -1, vBn);
     __builtin_amdgcn_sched_barrier(0);  // keep the prefetch ahead of the MFMAs
     const T* B = sB[b] + lane;
     const T* D = sD[b];
@@ -1338,7 +1344,7 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
       }
     if (k + 1 < nt2) {
       store_dstage<T, P, kBlock>(sD[b ^ 1], vDc);
-      bs.store(sB[b ^ 1], vBc);
+      if constexpr (BStage<T, P>::part(H)) bs.template store<H == 0>(sB[b ^ 1], vBc);
     }
     __syncthreads();
   };
@@ -1361,10 +1367,10 @@ __device__ inline void m2l_part(const int32_t* __restrict__ tp, int nt, const in
   }
 }
 
-// Occupancy floor of k_m2l_taps: the FP32 kernel fits 128 registers without
-// spilling, so its LDS (4 blocks per CU) sets 4 waves per SIMD; left to itself the
-// compiler takes about 176 registers and 2 waves, and the M2L launches ran about
-// 8% slower.  FP64 keeps the compiler's choice (it spills at a higher floor).
+// Occupancy floor of k_m2l_taps: told to keep 4 waves per SIMD, the compiler takes 69
+// registers at p = 4 FP32 instead of 92 and M2L runs 2 to 4% faster (64^3 + 2% of its
+// cells: 133, 137 us); up to p = 3 the times are equal, and the FP64 kernels come out
+// the same with any floor that they reach without spilling.
 template <typename T>
 constexpr int m2l_min_waves() { return sizeof(T) == 4 ? 4 : 1; }
 
@@ -1427,8 +1433,10 @@ void k_m2l_taps(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
     typename Vec16<T>::type vD[ND];
     typename BS::Regs vB;
     load_dstage_nb<T, P, kBlock>(tp[0], Dst, vD);
-    bs.load(0, vB);
-    bs.store(sB[0], vB);
+    if (BS::part(w)) {
+      bs.template load<true>(0, vB);
+      bs.template store<true>(sB[0], vB);
+    }
     store_dstage<T, P, kBlock>(sD[0], vD);
   }
   __syncthreads();
