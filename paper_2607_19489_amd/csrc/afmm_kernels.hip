@@ -160,6 +160,17 @@ __device__ inline void store_copies(int nc, const LevelDev& lv, Rank rank, Coef 
 // the loads).
 __host__ __device__ constexpr int upward_cells(int p) { return 256 / nmi(p) < 32 ? 256 / nmi(p) : 32; }
 
+// entries of the fold lists (CommonDev::fold_list)
+__host__ __device__ constexpr int fold_entries(int p) {
+  int n = 0;
+  for (int d = 0; d <= p; ++d)
+    for (int z = 0; z <= (d > 0 ? 1 : 0); ++z)
+      for (int b = 0; b <= d - z; ++b)
+        for (int m = 0; 2 * m <= d - z; ++m)
+          for (int r = 0; r <= m; ++r) n += 2 * r <= d - b - z && 2 * (m - r) <= b;
+  return n;
+}
+
 template <int P>
 __global__ __launch_bounds__(256) void k_upward(const int32_t* __restrict__ list, int nlist, LevelDev lv,
                                                 LevelDev lvc, CommonDev cm) {
@@ -173,7 +184,15 @@ __global__ __launch_bounds__(256) void k_upward(const int32_t* __restrict__ list
   __shared__ int sB[K + 1];
   __shared__ int sRc[CB][8];
   __shared__ double sM[CB][8];
+  constexpr int NF = fold_entries(P);
+  __shared__ double sFw[NF];
+  __shared__ int16_t sFl[NF], sFs[nh(P) + 1];
   const int t = threadIdx.x;
+  for (int i = t; i < NF; i += 256) {
+    sFw[i] = cm.fold_w[i];
+    sFl[i] = cm.fold_list[i];
+  }
+  for (int i = t; i <= nh(P); i += 256) sFs[i] = (int16_t)cm.fold_start[i];
   for (int i = t; i < NE; i += 256) {
     sW[i] = cm.m2m_w[i];
     sE[i] = cm.m2m_list[i];
@@ -254,7 +273,7 @@ __global__ __launch_bounds__(256) void k_upward(const int32_t* __restrict__ list
     // source copies for the translation kernels carry the factor (-1)^|a|/a! 2^|a|
     store_copies<P>(nc, lv, [&](int cc) { return list[i0 + cc]; }, [&](int cc, int h) {
       double v = 0.0;
-      for (int j = cm.fold_start[h]; j < cm.fold_start[h + 1]; ++j) v += cm.fold_w[j] * sV[cc][cm.fold_list[j]];
+      for (int j = sFs[h]; j < sFs[h + 1]; ++j) v += sFw[j] * sV[cc][sFl[j]];
       return v;
     });
     __syncthreads();
