@@ -2379,7 +2379,8 @@ static afmm_status run_solve(afmm_plan* P, const double* msrc, int fmax, int lo,
     const int ng = chain ? chain->ngrp[f] : (int)T.m2lgrp[f].size();
     const int32_t* grp = chain ? chain->d_grp[f] : P->d_m2lgrp[f];
     const int ns = P->m2l_split[P->m2l_range[f][0]];
-    if (ng == 0) continue;
+    // nothing to add: the first level's own sums, which at p = 1 are all its coefficients
+    if (ng == 0 || (p == 1 && f - 1 < P->l_first && ns == 1)) continue;
     hipEvent_t a = prof_begin(P, st);
     if ((s = dev_check(P,
                        launch_l2l(p, mixed && f > f64, mixed && (f - 1) > f64, f - 1 >= P->l_first, ns, grp, ng,
