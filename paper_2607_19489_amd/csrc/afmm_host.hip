@@ -2067,11 +2067,24 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
         }
         need.swap(up);
       }
+      // A chain of few tiles leaves most CUs idle for as long as a tile takes; in
+      // narrow tiles it takes less, and as long as they run in one round nothing is
+      // lost.  The sums are the same bit by bit, which more splits than the full
+      // solve's would not keep.  Finest of 4 nested levels on 64^3, FP32, 42 tiles
+      // of 32 / 84 of 16: 91 / 72 us at p = 5, 111 / 84 at p = 6.
       std::vector<int32_t> rec[2];
+      int nc[2] = {m2l_nc[0], m2l_nc[1]}, narrow[2] = {0, 0};
+      for (int f = 3; f <= l - 1; ++f) {
+        int n[8] = {};
+        for (int32_t F : grp[f]) ++n[T.lv[f - 1].refcell[F] & 7];
+        for (int c = 0; c < 8; ++c) narrow[P->m2l_range[f][0]] += (n[c] + 15) / 16;
+      }
+      for (int pr = 0; pr < 2; ++pr)
+        if (narrow[pr] * P->m2l_split[pr] <= ncu) nc[pr] = 16;
       for (int f = 3; f <= l - 1; ++f) {
         const int pm = P->m2l_range[f][0];
-        const int m0 = (int)(rec[pm].size() / (m2l_nc[pm] + 1));
-        const int m = append_tiles(T, f, grp[f], m2l_nc[pm], rec[pm]);
+        const int m0 = (int)(rec[pm].size() / (nc[pm] + 1));
+        const int m = append_tiles(T, f, grp[f], nc[pm], rec[pm]);
         A.m2l_range[f][0] = pm;
         A.m2l_range[f][1] = m0;
         A.m2l_range[f][2] = m;
@@ -2081,7 +2094,7 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
       for (int pr = 0; pr < 2; ++pr) {
         int32_t* d = nullptr;
         if ((s = upload(P, rec[pr], &d, st))) return s;
-        A.m2l_all[pr] = {d, (int)(rec[pr].size() / (m2l_nc[pr] + 1)), m2l_nc[pr]};
+        A.m2l_all[pr] = {d, (int)(rec[pr].size() / (nc[pr] + 1)), nc[pr]};
       }
       A.on = true;
     }

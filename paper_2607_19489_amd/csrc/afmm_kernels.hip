@@ -1513,13 +1513,13 @@ __device__ inline f32x4 mfma4q(int quad, float a, float b, f32x4 c) {
   }
 }
 
-template <typename T, int P>
+template <typename T, int P, int NC>
 struct M2L {
   using SL = SymLayout<P, (int)sizeof(T)>;
   using V16 = typename Vec16<T>::type;
   static constexpr int CP = SL::CP, NP = SL::NP, ROW = SL::ROW;
   static constexpr int KH = nh(P), KB = (KH + 3) / 4, RT = (KH + 15) / 16;
-  static constexpr int NC = m2l_cols(P, (int)sizeof(T)), CT = NC / 16;
+  static constexpr int CT = NC / 16;
   static constexpr bool QUADS = sizeof(T) == 4;
   static constexpr int UT = KB * 64 + 16;             // U of one column tile (the tiles 16 banks apart)
   static constexpr int UP = CT * UT + 64;             // U of one character, then places for the unused slots
@@ -1686,15 +1686,15 @@ struct M2L {
 // nsplit == 1 the sums go to the front of the rows of L; otherwise to the level's
 // partial buffer [nsplit][nref][KH], reduced in fixed order by k_l2l, which also
 // forms the coefficients that follow from these.
-template <typename T, int P>
+template <typename T, int P, int NC>
 __global__ __launch_bounds__(kM2LBlock)
 void k_m2l(const int32_t* __restrict__ tiles, int ntiles, int nsplit, const int8_t* __restrict__ taps,
            const int* __restrict__ var, const int16_t* __restrict__ aoff, const LevelDev* __restrict__ lvs,
            const T* __restrict__ symE) {
-  using ML = M2L<T, P>;
+  using ML = M2L<T, P, NC>;
   using SL = typename ML::SL;
   static constexpr SL sl{};
-  constexpr int NC = ML::NC, CT = ML::CT, RT = ML::RT, KB = ML::KB, KH = ML::KH;
+  constexpr int CT = ML::CT, RT = ML::RT, KB = ML::KB, KH = ML::KH;
   __shared__ __align__(16) typename ML::Lds lds;
   const int item = xcd_tile(ntiles * nsplit);
   if (item >= ntiles * nsplit) return;
@@ -2175,16 +2175,23 @@ static hipError_t m2l_dispatch(int p, const MfmaTiles& mt, int t0, int n, int ns
                                const LevelDev* lvs, const TablesDev<T>& td, hipStream_t st) {
   const int items = n * nsplit;
   const dim3 grid(8 * ((items + 7) / 8));
+  // tiles of this order and precision, or the narrow ones of a level solve's short chain
+  const bool narrow = mt.nc == 16 && m2l_cols(p, (int)sizeof(T)) != 16;
+  if ((mt.nc != m2l_cols(p, (int)sizeof(T)) && !narrow) || nsplit < 1 || nsplit > 21) return hipErrorInvalidValue;
   const int32_t* tl = mt.tiles + (size_t)t0 * (mt.nc + 1);
   switch (p) {
 #define AFMM_M2L(PP)                                                                                              \
   case PP:                                                                                                        \
-    if constexpr (m2l_by_taps(PP))                                                                                \
-      hipLaunchKernelGGL((k_m2l_taps<T, PP>), grid, dim3(kBlock), 0, st, tl, n, nsplit, tabs.taps, tabs.m2l_off, \
+    if constexpr (m2l_by_taps(PP)) {                                                                              \
+      hipLaunchKernelGGL((k_m2l_taps<T, PP>), grid, dim3(kBlock), 0, st, tl, n, nsplit, tabs.taps, tabs.m2l_off,  \
                          lvs, td.Dstage);                                                                         \
-    else                                                                                                          \
-      hipLaunchKernelGGL((k_m2l<T, PP>), grid, dim3(kM2LBlock), 0, st, tl, n, nsplit, tabs.symtaps, tabs.symvar,  \
-                         tabs.m2l_off, lvs, td.symE);                                                             \
+    } else if (narrow) {                                                                                          \
+      hipLaunchKernelGGL((k_m2l<T, PP, 16>), grid, dim3(kM2LBlock), 0, st, tl, n, nsplit, tabs.symtaps,           \
+                         tabs.symvar, tabs.m2l_off, lvs, td.symE);                                                \
+    } else {                                                                                                      \
+      hipLaunchKernelGGL((k_m2l<T, PP, m2l_cols(PP, (int)sizeof(T))>), grid, dim3(kM2LBlock), 0, st, tl, n,       \
+                         nsplit, tabs.symtaps, tabs.symvar, tabs.m2l_off, lvs, td.symE);                          \
+    }                                                                                                             \
     break;
     AFMM_M2L(1) AFMM_M2L(2) AFMM_M2L(3) AFMM_M2L(4) AFMM_M2L(5) AFMM_M2L(6) AFMM_M2L(7) AFMM_M2L(8)
 #undef AFMM_M2L
