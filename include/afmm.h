@@ -109,7 +109,8 @@ typedef struct afmm_options {
                                 split over this many blocks and their partial sums reduced in a
                                 fixed order; 0 = automatic (enough blocks to fill the GPU), else
                                 1..21.  Results depend on it only through FP rounding order. */
-  size_t max_device_bytes;   /* cap on the plan's device memory; 0 = no cap */
+  size_t max_device_bytes;   /* cap on the plan's device memory; 0 = no cap.  With tap_split = 0 a plan
+                                whose partial sums would exceed it takes fewer blocks per tile. */
   int32_t m2p_shape;         /* 0..3, the tile shapes of earlier intermediate-field (M2P) launches.
                                 Results never depended on it; every value now runs the one kernel
                                 that is left. */

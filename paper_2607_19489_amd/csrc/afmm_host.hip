@@ -2023,7 +2023,6 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
       while (sp < 8 && nt * sp < ncu) sp *= 2;
       P->m2p_split[pr] = P->opt.tap_split > 0 ? P->opt.tap_split : nt > 0 ? sp : 1;
     }
-    if ((s = alloc_split_buffers(P))) return s;
     for (int pr = 0; pr < 2; ++pr) {
       int32_t* d = nullptr;
       if ((s = upload(P, m2p_rec[pr], &d, st))) return s;
@@ -2099,10 +2098,6 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
       A.on = true;
     }
   }
-  {
-    std::vector<LevelDev> lvh(P->lv, P->lv + kMaxLevel + 1);
-    if ((s = upload(P, lvh, &P->d_lvs, st))) return s;
-  }
   void* p = nullptr;
   if ((s = dev_alloc(P, &p, (size_t)std::max<int64_t>(T.nslots, 1) * sizeof(double)))) return s;
   P->m_snap = (double*)p;
@@ -2128,6 +2123,23 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
   // a plan small enough for the allocation-free adjoint gets its adjoint
   // topology now, so that afmm_solve_adjoint_noalloc never has to allocate it
   if (T.levelmin.size() == 1 && adjoint_noalloc_may_fit(P) && (s = adjoint_topology(P))) return s;
+  // the partial sets last: under a cap that the automatic splits would exceed, the
+  // plan takes fewer sets in what is left
+  auto fits = [&] {
+    return P->bytes + split_buffer_bytes(P, P->m2l_split, P->m2p_split) + sizeof(LevelDev) * (kMaxLevel + 1) <=
+           P->opt.max_device_bytes;
+  };
+  while (P->opt.max_device_bytes && P->opt.tap_split == 0 && !fits()) {
+    const int most = std::max({P->m2l_split[0], P->m2l_split[1], P->m2p_split[0], P->m2p_split[1]});
+    if (most == 1) break;
+    for (int pr = 0; pr < 2; ++pr)
+      for (int* n : {&P->m2l_split[pr], &P->m2p_split[pr]}) *n = std::min(*n, most / 2);
+  }
+  if ((s = alloc_split_buffers(P))) return s;
+  {
+    std::vector<LevelDev> lvh(P->lv, P->lv + kMaxLevel + 1);
+    if ((s = upload(P, lvh, &P->d_lvs, st))) return s;
+  }
   if ((P->opt.flags & AFMM_GRAPH) && hipStreamCreateWithFlags(&P->cap, hipStreamNonBlocking) != hipSuccess)
     return fail(AFMM_E_DEVICE, "capture stream creation failed");
   if (hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking) != hipSuccess ||
