@@ -3041,6 +3041,23 @@ static size_t adjoint_layout(const afmm_plan* P, char* base, LevelDev* lw, doubl
 static afmm_status adjoint_workspace(afmm_plan* P) {
   if (P->adj_ready) return AFMM_OK;
   afmm_status s;
+  // a failure gives back what this call allocated: under a cap a later call starts
+  // again from there
+  struct Undo {
+    afmm_plan* P;
+    size_t allocs, bytes;
+    const float* d32;
+    const double* d64;
+    bool topo;
+    ~Undo() {
+      if (P->adj_ready) return;
+      while (P->allocs.size() > allocs) dev_free(P, P->allocs.back().p, 0);
+      P->bytes = bytes;
+      P->t32.Dstage = d32;
+      P->t64.Dstage = d64;
+      P->adj_topo = topo;
+    }
+  } undo{P, P->allocs.size(), P->bytes, P->t32.Dstage, P->t64.Dstage, P->adj_topo};
   if ((s = adjoint_topology(P))) return s;
   if (hipDeviceSynchronize() != hipSuccess) return fail(AFMM_E_DEVICE, "adjoint topology upload");
   double* part = nullptr;

@@ -2,7 +2,8 @@
 
 The sets of partial sums of the automatic splits are the part of a plan that can be
 smaller: a cap that holds the plan without splits holds the plan, and one that holds the
-automatic splits leaves them as they are.
+automatic splits leaves them as they are.  An adjoint that does not fit leaves the plan
+as it was, however often it is asked for.
 """
 import pytest
 
@@ -49,3 +50,23 @@ def test_fewer_sets_rather_than_no_plan(grid, p, precision):
     # (the tile lists of level solves depend a little on the splits, so `least` is not the last byte)
     with pytest.raises(A.AfmmError, match="max_device_bytes"):
         A.Plan(h, p=p, precision=precision, max_device_bytes=least // 2)
+
+
+# the FP32 copy of the adjoint's D~ rows fits the first cap, both copies and the source tiles fit the second,
+# which the bars exceed
+@pytest.mark.parametrize("more", [2 << 20, 4 << 20])
+def test_a_refused_adjoint_leaves_the_plan_as_it_was(more):
+    h, p = unigrid(6), 6
+    m = cell_masses(h, plummer(1.0, 0.1), 0.01, 900)
+    plan = A.Plan(h, p=p, precision="fp32", max_device_bytes=need(h, p, "fp32") + more)
+    mt = torch.from_numpy(m).cuda()
+    phi, acc = plan.solve(mt)
+    before = plan.info()["device_bytes"]
+    for _ in range(3):
+        with pytest.raises(A.AfmmError, match="max_device_bytes"):
+            plan.solve_adjoint(phi, acc)
+        assert plan.info()["device_bytes"] == before
+    again, _ = plan.solve(mt)
+    torch.cuda.synchronize()
+    assert torch.equal(again, phi)
+    plan.close()
