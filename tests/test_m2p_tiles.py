@@ -15,8 +15,9 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+import oracle  # noqa: E402
 import paper_2607_19489_amd as A  # noqa: E402
-from gpu_util import compare, gate  # noqa: E402
+from gpu_util import check_errors, compare, gate, gpu_solve, rel_l2  # noqa: E402
 
 from synth import cell_masses, plummer  # noqa: E402
 from synth.hierarchy import build_graded  # noqa: E402
@@ -89,3 +90,21 @@ def test_direct_tiles_have_the_bits_of_staged_ones(p):
     for h, (p0, a0), p1, a1 in zip(hs, ind, phis, accs):
         leaf = torch.from_numpy(h.leaf_mask()).cuda()
         assert torch.equal(p0[leaf], p1[leaf]) and torch.equal(a0[leaf], a1[leaf])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("p", [3, 6, 8])
+def test_direct_tiles_of_a_periodic_box(p, precision):
+    # neighbours and their children wrap round the box; the bounds are those of the periodic tests
+    h = GRIDS["narrow"]
+    m = np.random.default_rng(p).uniform(0.2, 1.0, h.total) / 8.0 ** (h.level_of() - h.levelmin)
+    o = oracle.Oracle(h, p, periodic=True)
+    po, ao = o.solve_all(m)
+    o.close()
+    leaf = h.leaf_mask()
+    phi, acc, plan = gpu_solve(h, m, p, precision, periodic=True, tap_split=2, fp64_levels=2)
+    plan.close()
+    check_errors(phi[leaf], acc[leaf], po[leaf], ao[leaf], precision, regression=False, what=f"periodic p={p}")
+    if precision == "fp32":
+        assert rel_l2(acc[leaf], ao[leaf]) <= 2e-5 and rel_l2(phi[leaf], po[leaf]) <= 2e-5
