@@ -17,7 +17,7 @@ torch = pytest.importorskip("torch")
 
 import oracle  # noqa: E402
 import paper_2607_19489_amd as A  # noqa: E402
-from gpu_util import check_errors, compare, gate, gpu_solve, rel_l2  # noqa: E402
+from gpu_util import check_errors, compare, gate, gpu_solve  # noqa: E402
 
 from synth import cell_masses, plummer  # noqa: E402
 from synth.hierarchy import build_graded  # noqa: E402
@@ -76,13 +76,14 @@ def test_against_oracle(grid, split, p, precision):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("p", [4, 7])
-def test_direct_tiles_have_the_bits_of_staged_ones(p):
+@pytest.mark.parametrize("periodic", [False, True])
+@pytest.mark.parametrize("p", [3, 4, 6, 7])
+def test_direct_tiles_have_the_bits_of_staged_ones(p, periodic):
     # far apart alone, the first plan's groups take direct tiles; beside the groups of a dense grid,
     # in a batch, the level is staged: one sum, in one order
     hs = [GRIDS["narrow"], scattered(4, 1.0)]
     ms = [cell_masses(h, plummer(1.0, 0.1), 0.01, 600 + i) for i, h in enumerate(hs)]
-    plans = [A.Plan(h, p=p, precision="fp32", tap_split=2, fp64_levels=2) for h in hs]
+    plans = [A.Plan(h, p=p, precision="fp32", tap_split=2, fp64_levels=2, periodic=periodic) for h in hs]
     masses = [torch.from_numpy(m).cuda() for m in ms]
     ind = [q.solve(mt) for q, mt in zip(plans, masses)]
     phis, accs = A.Batch(plans).solve(masses)
@@ -93,18 +94,16 @@ def test_direct_tiles_have_the_bits_of_staged_ones(p):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("precision", ["fp64", "fp32"])
 @pytest.mark.parametrize("p", [3, 6, 8])
-def test_direct_tiles_of_a_periodic_box(p, precision):
-    # neighbours and their children wrap round the box; the bounds are those of the periodic tests
+def test_direct_tiles_of_a_periodic_box(p):
+    # neighbours and their children wrap round the box.  FP64: the potential of nearly even
+    # masses is a hundredth of a monopole's, so the mixed form's gate says little here; its bits are above
     h = GRIDS["narrow"]
     m = np.random.default_rng(p).uniform(0.2, 1.0, h.total) / 8.0 ** (h.level_of() - h.levelmin)
     o = oracle.Oracle(h, p, periodic=True)
     po, ao = o.solve_all(m)
     o.close()
     leaf = h.leaf_mask()
-    phi, acc, plan = gpu_solve(h, m, p, precision, periodic=True, tap_split=2, fp64_levels=2)
+    phi, acc, plan = gpu_solve(h, m, p, "fp64", periodic=True, tap_split=2)
     plan.close()
-    check_errors(phi[leaf], acc[leaf], po[leaf], ao[leaf], precision, regression=False, what=f"periodic p={p}")
-    if precision == "fp32":
-        assert rel_l2(acc[leaf], ao[leaf]) <= 2e-5 and rel_l2(phi[leaf], po[leaf]) <= 2e-5
+    check_errors(phi[leaf], acc[leaf], po[leaf], ao[leaf], "fp64", what=f"periodic p={p}")
