@@ -292,16 +292,26 @@ def time_form(h, mass_t, p, precision, steps, warmup, overlap=False, autotune=Tr
 
 
 SYMBOLS = {"m2p_f32": "k_m2p<float, {p}>", "m2p_f64": "k_m2p<double, {p}>",
-           "m2l_f32": "k_m2l<float, {p}>", "m2l_f64": "k_m2l<double, {p}>",
            "near_f32": "k_near<float, {p}>", "near_f64": "k_near<double, {p}>", "upward": "k_upward<{p}>"}
 
 
-def executed_share(family, p):
-    """Share of a family's profiled operations that its kernel executes.  The profile
-    counts the Cartesian translation of every (target, source) pair: (p+1)(p+2)(p+3)/6
+def kernel_symbol(family, p):
+    """rocprofv3's name of the kernel that a full solve launches for a family."""
+    if family.startswith("m2l_"):
+        fp32 = family == "m2l_f32"
+        t = "float" if fp32 else "double"
+        return f"k_m2l_taps<{t}, {p}>" if p <= 4 else f"k_m2l<{t}, {p}, {32 if fp32 and p <= 6 else 16}>"
+    return SYMBOLS.get(family, "").format(p=p)
+
+
+def needed_share(family, p):
+    """Share of a family's profiled operations that the form of its kernel needs for a
+    group with all its sources, refined ones.  The profile counts the Cartesian
+    translation of every existing (target, source) pair: (p+1)(p+2)(p+3)/6
     coefficients, 189 sources per group.  The kernels work on the (p+1)^2 independent
     coefficients, and M2P and (from p = 5) M2L on 56 orbits of sources that share an
-    operator."""
+    operator.  Not what they execute: they run the full product for missing and leaf
+    sources, for children that are no targets and for the columns that pad a tile."""
     def n_full(q):
         return (q + 1) * (q + 2) * (q + 3) // 6
 
@@ -323,7 +333,7 @@ def measured_traffic(family, p, workload):
     import glob
     sys.path.insert(0, ROOT)
     from bench_profile import source_hash
-    want = SYMBOLS.get(family, "").format(p=p)
+    want = kernel_symbol(family, p)
     for f in glob.glob(os.path.join(ROOT, "profiles", "traffic_*.json")):
         try:
             t = json.load(open(f))
@@ -335,17 +345,20 @@ def measured_traffic(family, p, workload):
 
 
 def roofline(res, precision, p, workload=None):
-    """Roofline of the kernel family with the largest summed time in the timed region."""
+    """Roofline of the kernel family with the largest summed time in the timed region.
+    flops_per_launch, achieved and frac are useful operations (needed_share); the bytes
+    are the profile's model of unique data, in Cartesian rows, without the completion
+    of the first level's expansions."""
     prof = res["kernels"]
     name, k = max(prof.items(), key=lambda kv: kv[1]["ms"])
     total_ms = sum(v["ms"] for v in prof.values())
     traffic, tsrc = measured_traffic(name, p, workload)
     kname = KERNEL_NAMES.get(name, name)
-    share = executed_share(name, p)
+    share = needed_share(name, p)
     common = {"kernel": kname, "family": name, "launches": k["launches"],
               "traffic_source": tsrc,
               "avg_launch_ms": k["ms"] / max(k["launches"], 1),
-              "flops_per_launch": share * k["flops"] / max(k["launches"], 1), "executed_share": share,
+              "flops_per_launch": share * k["flops"] / max(k["launches"], 1), "needed_share": share,
               "bytes_per_launch": k["bytes"] / max(k["launches"], 1), "share_of_step": k["ms"] / total_ms}
     if name in ("gather", "upward", "l2l"):
         achieved = k["bytes"] / (k["ms"] * 1e-3) / 1e9

@@ -305,7 +305,7 @@ afmm_status afmm_solve_adjoint_noalloc(afmm_plan* plan, int32_t level, const dou
  * afmm_batch_solve: d_mass[i], d_phi[i], d_acc[i] are device pointers laid out as
  * for afmm_solve on plans[i] (host arrays of n pointers, read at the call).  Only
  * leaf entries of the outputs are written.  A solve of the batch gives the same
- * bits as afmm_solve on each plan (same tap_split, no atomics anywhere).
+ * bits as afmm_solve on each plan (same tap_split; every sum in a fixed order).
  * Errors: AFMM_E_INVALID_ARG (null pointer, n < 1, an options mismatch),
  * AFMM_E_DEVICE (capture or launch failure), AFMM_E_OUT_OF_MEMORY.
  */

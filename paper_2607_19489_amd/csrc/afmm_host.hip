@@ -1954,12 +1954,11 @@ static afmm_status plan_finish(afmm_plan* P, hipStream_t st) {
   }
   if (mixed && (s = upload_conv<float>(P, near_vec(4), &P->t32.nearA, st))) return s;
   if ((s = upload_conv<double>(P, H.Dsame, &P->t64.Dsame, st)) ||
-      (s = upload_conv<double>(P, H.cfac2, &P->t64.cfac2, st)) || (s = upload_conv<double>(P, H.cfacn, &P->t64.cfacn, st)) ||
+      (s = upload_conv<double>(P, H.cfacn, &P->t64.cfacn, st)) ||
       (s = upload_conv<double>(P, H.l2lw, &P->t64.l2lw, st)) || (s = upload_conv<double>(P, H.l2p, &P->t64.l2p, st)))
     return s;
   if (mixed) {
     if ((s = upload_conv<float>(P, H.Dsame, &P->t32.Dsame, st)) ||
-        (s = upload_conv<float>(P, H.cfac2, &P->t32.cfac2, st)) || (s = upload_conv<float>(P, H.cfacn, &P->t32.cfacn, st)) ||
         (s = upload_conv<float>(P, H.l2lw, &P->t32.l2lw, st)) || (s = upload_conv<float>(P, H.l2p, &P->t32.l2p, st)))
       return s;
   }

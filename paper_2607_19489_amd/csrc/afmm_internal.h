@@ -191,7 +191,7 @@ __host__ __device__ constexpr int sym_elen(int p, int bytes) {
 // 64^3 + 1 level in FP32, taps / orbits 77 / 90 us at p = 4, 105 / 103 at p = 5,
 // 150 / 126 at p = 6, 329 / 211 at p = 8 (FP64: 115 / 131, 167 / 167, 277 / 203).  The
 // line is one of orders alone: a batch and its members' own plans, of other sizes,
-// give the same bits.
+// give the same bits at equal splits.
 __host__ __device__ constexpr bool m2l_by_taps(int p) { return p <= 4; }
 // Columns of an M2L tile; by orbits, two tiles of 16 per wave share the A operand
 // where both sets of U fit the LDS.
@@ -284,8 +284,7 @@ struct TablesDev {
   const T* Dstage = nullptr;  // [kNumD][dstage_len(p, sizeof(T))] D~ at R~ = -2d + o - 1/2, 8 rows per d,
                               // in the LDS stage layout of the MFMA kernels
   const T* Dsame = nullptr;   // [kNumD][K]      D~ at integer R~ in [-3,3]^3
-  const T* cfac2 = nullptr;   // [K] (-1)^|a|/a! 2^|a|
-  const T* cfacn = nullptr;   // [K] 2^-|a|: same-level M2P from the source copies
+  const T* cfacn = nullptr;   // [K] 2^-|a| (FP64): same-level M2P from the source copies, transposed
   const T* l2lw = nullptr;    // [8][p+1][K] L2L weights 2^(-1-|b|) u^g/g! per child octant and |b|
   const T* l2p = nullptr;     // [8][4][K] L2P weights (phi, ax, ay, az) per child octant
   const T* nearA = nullptr;   // [2][near_ksteps / VW][64][VW] near-field operator, MFMA A layout
@@ -373,7 +372,7 @@ hipError_t launch_adj_l2p(int p, const int32_t* grp, int ngrp, const LevelDev& l
                           const TablesDev<double>& t64, const CommonDev& cm, hipStream_t st);
 // MFMA forms: tiles of 16 source cells (records: target level, 16 cells); with
 // nsplit > 1 the 189 taps of a tile are split over blocks writing partial sets
-// into `part` ([nsplit][ntiles * 16][K] FP64), summed in order afterwards.
+// into `part` ([nsplit][ntiles * 16][nh(p)] FP64), summed in order afterwards.
 // Periodic boxes: the level-2 far operator table ([8][kNumD][K] in level-2
 // units, cached per order) and its kernel (writes L of the 64 level-2 cells).
 std::shared_ptr<const std::vector<double>> periodic_far_table(int p);

@@ -10,7 +10,8 @@
 // every operator: M2L and the intermediate-field M2P become, tap by tap, dense
 // products  OUT[rows x groups] += A_d[rows x K] * S[K x groups]  on MFMA.
 //
-// Deterministic: no atomics; every sum runs in a fixed order.
+// Deterministic: every sum runs in a fixed order.  The only atomics number the fathers
+// of an M2P tile in LDS; their places do not show in the results.
 #include <hip/hip_runtime.h>
 #include <algorithm>
 #include <type_traits>
