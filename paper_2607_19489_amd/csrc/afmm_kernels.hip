@@ -1502,9 +1502,10 @@ void k_m2l_taps(const int32_t* __restrict__ tiles, int ntiles, int nsplit,
 // Bound by instruction issue: one block of 8 waves per CU, whose butterflies,
 // addresses and LDS traffic cost about as much as the products, and the barrier of
 // every orbit.  A wider tile (or a second block) does not fit the registers (253 at
-// p = 6 FP32); a second orbit's loads in flight changed nothing.  Tap by tap / by
-// orbits: 8.08M leaves p = 6 FP32 2.60 / 2.04 ms, 287,680 leaves p = 6 FP64 272 / 184
-// us, 8 hierarchies p = 8 FP32 720 / 457 us.
+// p = 6 FP32); a second orbit's loads in flight changed nothing.  Tap by tap on all
+// coefficients / on the folded ones / by orbits: 8.08M leaves p = 6 FP32 3.9 / 2.60 /
+// 2.04 ms; the last two, 287,680 leaves p = 6 FP64 272 / 184 us, 8 hierarchies p = 8
+// FP32 720 / 457 us.
 __device__ inline f32x4 mfma4q(int quad, float a, float b, f32x4 c) {
   switch (quad) {  // constant at every call
     case 0: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 2, 0, 0);
