@@ -655,9 +655,9 @@ __device__ inline void tile_setup(const int32_t* __restrict__ rec, int NC, const
 // a range of the orbits.  The sources of the 7 orbits of one m sit in one octant of
 // their fathers, so the rows of that octant of all fathers of the tile (their
 // number is bounded by the tile) are staged in LDS once and read from there about
-// six times; read from memory for each use, 50 GB at 8M leaves, they held the
-// kernel at the L2's 10 TB/s.  The distinct fathers are found through a hash table
-// in LDS.
+// six times; read from memory for each use they were 50 GB at 8M leaves (now the
+// L2s give 24 GB, half of it operators).  The distinct fathers are found through a hash
+// table in LDS.
 // 4x4 blocks of MFMA: lane (q = lane >> 2, j = lane & 3) holds the coefficients of
 // block q (SymLayout) of group j of a quad; all coefficients of a block have one
 // parity, so sigma^a is one sign per lane and axis, and the sources' vectors turn
@@ -667,8 +667,8 @@ __device__ inline void tile_setup(const int32_t* __restrict__ rec, int NC, const
 // pass) comes through a ring of three steps in LDS, shared by the block, and stays
 // in registers for the wave's quads.  Output: part[F][i * 8 + o] (accelerations
 // negated), one partial set per orbit range.
-// Matrix and vector instructions of one SIMD do not overlap here (32 of each
-// interleaved take their sum), and at two waves per SIMD the butterflies, the LDS
+// Matrix and vector instructions of one SIMD do not overlap here (32 of each take
+// their sum one after the other, more interleaved), and at two waves per SIMD the butterflies, the LDS
 // reads behind them and the MFMAs share the time about evenly.  8.08M leaves
 // (128^3 + 4 levels) at p = 6 FP32: 8.7 ms summed tap by tap over all K
 // coefficients, 6.4 on the folded ones, 4.95 by orbits; 287,680 leaves FP64: 703,
