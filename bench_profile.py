@@ -59,7 +59,7 @@ def cmd_stats(a):
     for r in trace:
         k = short(r["Kernel_Name"])
         per.setdefault(k, []).append((int(r["Start_Timestamp"]), int(r["End_Timestamp"]) - int(r["Start_Timestamp"])))
-    out = [f"# rocprofv3 kernel statistics: {a.title}", "", "Command (repository root on the MI355X box):", "",
+    out = [f"# rocprofv3 kernel statistics: {a.title}", "", "Command (from the repository root):", "",
            "```", a.command, "```", "",
            "## All dispatches (rocprofv3 --stats)", "",
            "| kernel | calls | total ms | avg us | min us | max us | % |", "|---|---|---|---|---|---|---|"]
@@ -114,7 +114,7 @@ def cmd_mfma(a):
            "include the zero padding of the MFMA tiles; the useful-flop rate is the bench's own figure.  Every",
            "launch of a solve runs on the caller's one stream, so a traced duration is one launch alone.  The",
            "grids other than the autotuned one are the tuner's candidate tap splits.", "",
-           "Commands (repository root on the MI355X box):", "", "```", a.command_pmc, a.command_trace, "```", "",
+           "Commands (from the repository root):", "", "```", a.command_pmc, a.command_trace, "```", "",
            "| kernel | grid | counter | dispatches | issued GFLOP / dispatch | median us (trace) | issued TFLOP/s | of peak |",
            "|---|---|---|---|---|---|---|---|"]
     for counter, peak in PEAK_TFLOPS.items():
@@ -195,7 +195,7 @@ def cmd_counters(a):
            "the GPU's shader engines / instances, one rocprofv3 --pmc pass per group of counters (no pass",
            "exceeds the hardware's counter slots).  Cycle counters named *_CYCLES are per SIMD or per wave as",
            "rocprofv3 documents them; SQ_WAVE_CYCLES, SQ_WAIT_* and SQ_BUSY_CU_CYCLES are in quad-cycles.", "",
-           "Commands (repository root on the MI355X box):", "", "```", *a.command, "```", "",
+           "Commands (from the repository root):", "", "```", *a.command, "```", "",
            "| counter | " + " | ".join(f"`{k}`" for k in kernels) + " |", "|---|" + "---|" * len(kernels)]
     for c in counters:
         out.append(f"| {c} | " + " | ".join(f"{med[(k, c)]:.4g}" if (k, c) in med else "" for k in kernels) + " |")
